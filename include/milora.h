@@ -165,11 +165,12 @@ int milora_route(const void *H, int64_t M_tok, int d, int dtype, const int32_t *
  * d1 % 32 != 0 or d2 % 16 != 0, or with X, W, bias or Y not 16-byte aligned), EWORKSPACE, EHIP.
  */
 size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2, int r_max);
-/* Which kernel milora_routed_linear runs for these sizes when its pointers are 16-byte aligned (host
- * logic only, no device work): MILORA_KERNEL_GENERIC (any shape, fp32 arithmetic), MILORA_KERNEL_STREAM
- * (packed weights, the few-row weight-streaming kernel, M above MILORA_MAX_DECODE_BATCH in slices) or
- * MILORA_KERNEL_TILES (row-major bf16 weights, M >= 64, d1 % 64 == 0, d2 % 16 == 0: 256 x 256 matrix-core
- * tiles).  Negative status for arguments milora_routed_linear itself would reject. */
+/* Which kernel family milora_routed_linear runs for these sizes when its pointers are 16-byte aligned (host
+ * logic only, no device work): MILORA_KERNEL_STREAM (packed weights: up to 32 rows the weight-streaming kernel, more rows
+ * the matrix-core tiles), MILORA_KERNEL_TILES (row-major bf16 weights, M >= 64, d1 % 64 == 0, d2 % 16 == 0: matrix-core
+ * tiles of 64 x 64, 128 x 128 or 256 x 256 by the sizes) or MILORA_KERNEL_GENERIC (everything else: fp32, any shape, and
+ * fewer rows than 64, which take the 64 x 64 matrix-core tiles where the widths allow it).  Negative status for
+ * arguments milora_routed_linear itself would reject. */
 #define MILORA_KERNEL_GENERIC 0
 #define MILORA_KERNEL_STREAM 1
 #define MILORA_KERNEL_TILES 2

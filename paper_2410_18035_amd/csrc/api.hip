@@ -1,7 +1,7 @@
 // C ABI of the routed-LoRA library: argument validation, workspace carving and dispatch between
 // the matrix-core decode path (bf16, packed weights), the matrix-core prefill path (bf16,
 // row-major weights, many rows) and the any-shape path (fp32 and everything else).
-#include "common.h"
+#include "tiles.h"
 
 namespace milora {
 
@@ -36,6 +36,7 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kStreamRows = 32;   // rows up to which a packed linear takes the weight-streaming kernel
 
 template <typename T>
 __device__ __forceinline__ float block_sum(float v, float* sh) {
@@ -219,10 +220,19 @@ extern "C" int milora_last_hip_error(void) { return g_last_hip_error; }
 
 extern "C" size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2, int r_max) {
   if (M < 1 || d1 < 1 || d2 < 1 || r_max < 1) return 0;
-  size_t generic = align_up((size_t)M * r_max * sizeof(float) * kPrefillShrinkParts, 256);
+  // counters of the tile kernel, LoRA shrinks, partial tiles
+  size_t partial = 0;
+  for (int large = 0; large < 2; ++large) {
+    const size_t n = plan_tiles(M <= kTileMaxRows ? M : kTileMaxRows, d1, d2, large != 0).partial_bytes;
+    partial = n > partial ? n : partial;
+    // (a last slice of fewer rows)
+    const size_t rest = M > kTileMaxRows && M % kTileMaxRows ? plan_tiles(M % kTileMaxRows, d1, d2, large != 0).partial_bytes : 0;
+    partial = rest > partial ? rest : partial;
+  }
+  const size_t tiles = kStreamCtrlBytes + kTileCtrlBytes + align_up((size_t)M * r_max * sizeof(float) * shrink_parts(M, d1), 256) + partial;
   const int mp = M <= MILORA_MAX_DECODE_BATCH ? (int)M : MILORA_MAX_DECODE_BATCH;
   size_t packed = routed_linear_packed_workspace_bytes(mp, d1, d2, r_max);
-  return generic > packed ? generic : packed;
+  return tiles > packed ? tiles : packed;
 }
 
 extern "C" int milora_routed_linear_kernel(int64_t M, int d1, int d2, int dtype, int w_layout) {
@@ -253,27 +263,51 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
     return MILORA_EWORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   const AdapterView ad = view_of(adapters);
-  if (w_layout == MILORA_W_PACKED) {
+  const bool packed = w_layout == MILORA_W_PACKED;
+  if (packed) {
     if (dtype != MILORA_BF16 || !packed_shape_ok(d1, d2) || !aligned16(X) || !aligned16(W) || !aligned16(Y) ||
         (bias && !aligned16(bias)))
       return MILORA_EUNSUPPORTED;
     if (!row_to_req && M > MILORA_MAX_DECODE_BATCH) return MILORA_ERANGE;
-    // rows are independent: larger M runs as slices of at most 128 rows (each re-reads W)
-    for (int64_t m0 = 0; m0 < M; m0 += MILORA_MAX_DECODE_BATCH) {
-      const int mc = (int)(M - m0 < MILORA_MAX_DECODE_BATCH ? M - m0 : MILORA_MAX_DECODE_BATCH);
-      rc = routed_linear_packed((const bf16_t*)X + m0 * d1, mc, d1, d2, row_to_req ? row_to_req + m0 : nullptr,
-                                (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
-                                (bf16_t*)Y + m0 * d2, workspace, st);
-      if (rc) return rc;
-    }
-    return MILORA_OK;
+    if (M <= kStreamRows || !tiles_supported(M, d1, d2, true, X, W, Y))
+      // rows are independent: more than 128 of them run as slices (each re-reads W)
+      for (int64_t m0 = 0;; m0 += MILORA_MAX_DECODE_BATCH) {
+        const int mc = (int)(M - m0 < MILORA_MAX_DECODE_BATCH ? M - m0 : MILORA_MAX_DECODE_BATCH);
+        rc = routed_linear_packed((const bf16_t*)X + m0 * d1, mc, d1, d2, row_to_req ? row_to_req + m0 : nullptr,
+                                  (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
+                                  (bf16_t*)Y + m0 * d2, workspace, st);
+        if (rc || m0 + mc >= M) return rc;
+      }
   }
-  float* t = (float*)workspace;
-  if (dtype == MILORA_BF16 && prefill_supported(M, d1, d2, X, W, Y)) {
-    rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, st);
-    if (rc) return rc;
-    return routed_linear_prefill((const bf16_t*)X, M, d1, d2, row_to_req, (const bf16_t*)W, (const bf16_t*)bias, ad,
-                                 site, tenant_id, route, B, t, (bf16_t*)Y, st);
+  // (behind the stream kernels' control words: part counters, shrinks t, partial tiles)
+  int* const cnt = (int*)((char*)workspace + kStreamCtrlBytes);
+  float* const t = (float*)((char*)workspace + kStreamCtrlBytes + kTileCtrlBytes);
+  if (dtype == MILORA_BF16) {
+    const bool large = !packed && prefill_supported(M, d1, d2, X, W, Y);
+    if (large || tiles_supported(M, d1, d2, packed, X, W, Y)) {
+      rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, st);
+      if (rc) return rc;
+      const int parts = shrink_parts(M, d1);
+      const size_t t_stride = (size_t)M * ad.r_max;
+      float* const partial = (float*)((char*)t + align_up(t_stride * sizeof(float) * parts, 256));
+      // more rows than a launch of the smaller tiles takes, and no larger ones for this layout: slices of rows
+      const int64_t slice = large ? M : kTileMaxRows;
+      for (int64_t m0 = 0; m0 < M; m0 += slice) {
+        const int64_t mc = M - m0 < slice ? M - m0 : slice;
+        const TilePlan pl = plan_tiles(mc, d1, d2, large);
+        const bf16_t* const x = (const bf16_t*)X + (size_t)m0 * d1;
+        bf16_t* const y = (bf16_t*)Y + (size_t)m0 * d2;
+        const int32_t* const map = row_to_req ? row_to_req + m0 : nullptr;
+        if (pl.shape == kTiles256)
+          rc = routed_linear_prefill(x, mc, d1, d2, map, (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
+                                     t, y, st);
+        else
+          rc = routed_linear_tiles(x, mc, d1, d2, map, (const bf16_t*)W, packed, (const bf16_t*)bias, ad, site, tenant_id,
+                                   route, B, t + (size_t)m0 * ad.r_max, t_stride, parts, pl, cnt, partial, y, st);
+        if (rc) return rc;
+      }
+      return MILORA_OK;
+    }
   }
   rc = launch_shrink(X, M, d1, dtype, row_to_req, ad, site, tenant_id, route, B, t, st);
   if (rc) return rc;

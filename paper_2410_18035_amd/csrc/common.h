@@ -51,6 +51,42 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// 16-byte stores of data another workgroup reads inside this launch: written through to the memory all XCDs
+// share (a plain store may stay in the writer's L2 until the launch ends).  The two idle cycles behind the store
+// belong to it: a store of more than eight bytes still reads its data registers for two cycles after it issues,
+// the compiler keeps vector writes away from them only for stores it can see, and it reuses these registers at
+// once (seen: the next store's address computed into them, and address bits arriving as partial sums).
+__device__ __forceinline__ void st_through(f32x4* p, f32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+// Eight 16-byte loads that bypass the caches (data written by other workgroups in this launch, into memory that
+// earlier levels and launches have used), complete when the function returns.
+__device__ __forceinline__ void ld_through8(const f32x4* const (&q)[8], f32x4 (&v)[8]) {
+  asm volatile(
+      "global_load_dwordx4 %0, %8, off sc0 sc1\n\t"
+      "global_load_dwordx4 %1, %9, off sc0 sc1\n\t"
+      "global_load_dwordx4 %2, %10, off sc0 sc1\n\t"
+      "global_load_dwordx4 %3, %11, off sc0 sc1\n\t"
+      "global_load_dwordx4 %4, %12, off sc0 sc1\n\t"
+      "global_load_dwordx4 %5, %13, off sc0 sc1\n\t"
+      "global_load_dwordx4 %6, %14, off sc0 sc1\n\t"
+      "global_load_dwordx4 %7, %15, off sc0 sc1\n\t"
+      "s_waitcnt vmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+      : "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(q[4]), "v"(q[5]), "v"(q[6]), "v"(q[7])
+      : "memory");
+}
+// 16 bytes per lane from base + voff (global) to LDS at dst + lane * 16, asynchronously; counted by vmcnt.
+// Written as assembly so that the compiler does not order its own LDS reads behind the copy.
+__device__ __forceinline__ void copy_to_lds16(const void* base, uint32_t voff, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(dst), "v"(voff), "s"(base)
+               : "memory");
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
   static constexpr int kDtype = MILORA_F32;
@@ -108,9 +144,18 @@ struct LaunchMarks {
   int grid = 0, stages = 0;    // filled in by a tracing launch: workgroups and stages it ran
 };
 
-// The many-row LoRA shrink cuts its reduction into this many parts (one workgroup each); the workspace holds
-// one [M][r_max] fp32 array per part.
-constexpr int kPrefillShrinkParts = 4;
+// The matrix-core LoRA shrink: few rows in blocks of 16 (rows of many tenants then meet in few workgroups), many in blocks
+// of 64 (W^A is read less often); its reduction is cut into parts, one workgroup each, so that some 512 workgroups of
+// eight waves are there and no wave is without a chunk.  The workspace holds one [M][r_max] fp32 array per part.
+constexpr int kShrinkChunkK = 128;
+constexpr int64_t kTileMaxRows = 4096;  // rows of one launch of the tile kernel
+inline int shrink_parts(int64_t M, int d1) {
+  const int64_t blocks = M <= kTileMaxRows ? (M + 15) / 16 : (M + 63) / 64;
+  const int most = (d1 + 8 * kShrinkChunkK - 1) / (8 * kShrinkChunkK);
+  int parts = 1;
+  while (parts < 8 && parts * 2 <= most && blocks * parts * 2 <= 512) parts *= 2;
+  return parts;
+}
 
 // ---- internal entry points shared between translation units ------------------------------------
 // LoRA shrink: for every row m whose request is routed to `site`, t[m][0..r) = X[m] . A (fp32).

@@ -24,14 +24,13 @@
 #include <mutex>
 #include <type_traits>
 
-#include "common.h"
+#include "tiles.h"
 
 namespace milora {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x4 gu32x4;  // in global memory: loads count on the vector-memory counter only
 typedef __attribute__((address_space(1))) u32x2 gu32x2;
 typedef __attribute__((address_space(1))) bf16_t gbf16;  // adapter matrices are reached through pointer tables read at run time
@@ -183,15 +182,8 @@ __device__ __forceinline__ void st_agent(float* p, float v) {
 __device__ __forceinline__ void st_agent(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// 16-byte stores of data another workgroup reads inside this launch: written through to the memory all XCDs
-// share (a plain store may stay in the writer's L2 until the launch ends).  The two idle cycles behind the store
-// belong to it: a store of more than eight bytes still reads its data registers for two cycles after it issues,
-// the compiler keeps vector writes away from them only for stores it can see, and it reuses these registers at
-// once (seen: the next store's address computed into them, and address bits arriving as partial sums).
+using milora::st_through;  // (see there)
 __device__ __forceinline__ void st_through(u32x4* p, u32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void st_through(f32x4* p, f32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 // One 16-byte load that bypasses the caches (data stored through by another workgroup in this launch), complete
@@ -1353,25 +1345,7 @@ constexpr int kWideGridMax = 256;   // workgroups the segment tables are sized f
 __device__ __forceinline__ void st_through(u32x2* p, u32x2 v) {
   asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
-// Eight 16-byte loads that bypass the caches (the partial tiles are written by other workgroups in this launch, into
-// memory that earlier levels and launches have used), complete when the function returns.
-__device__ __forceinline__ void ld_through8(const f32x4* const (&q)[8], f32x4 (&v)[8]) {
-  asm volatile(
-      "global_load_dwordx4 %0, %8, off sc0 sc1\n\t"
-      "global_load_dwordx4 %1, %9, off sc0 sc1\n\t"
-      "global_load_dwordx4 %2, %10, off sc0 sc1\n\t"
-      "global_load_dwordx4 %3, %11, off sc0 sc1\n\t"
-      "global_load_dwordx4 %4, %12, off sc0 sc1\n\t"
-      "global_load_dwordx4 %5, %13, off sc0 sc1\n\t"
-      "global_load_dwordx4 %6, %14, off sc0 sc1\n\t"
-      "global_load_dwordx4 %7, %15, off sc0 sc1\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-      : "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(q[4]), "v"(q[5]), "v"(q[6]), "v"(q[7])
-      : "memory");
-}
-
-// The same with two more (the LoRA term tiles of a unit travel with its first eight partial tiles).
+// ld_through8 with two more (the LoRA term tiles of a unit travel with its first eight partial tiles).
 __device__ __forceinline__ void ld_through10(const f32x4* const (&q)[10], f32x4 (&v)[10]) {
   asm volatile(
       "global_load_dwordx4 %0, %10, off sc0 sc1\n\t"
@@ -2279,6 +2253,7 @@ DecodeWs carve_decode_ws(void* base, int M, int d, int F, int r_max, bool wide =
   auto take = [&](size_t n) { size_t o = off; off += align_up(n, 256); return o; };
   const size_t o_fl = take((size_t)(2 * kMaxGrid + 64) * sizeof(int));
   const size_t o_p = take((size_t)kMaxRows * 2 * kSlotsPerRow * sizeof(int));  // at a fixed place whatever M is: the counters must read zero
+  static_assert((2 * kMaxGrid + 64 + kMaxRows * 2 * kSlotsPerRow) * sizeof(int) + 512 <= (size_t)kStreamCtrlBytes, "control words");
   const size_t o_tf = take((size_t)kSlotsPerRow * M * r_max * sizeof(float));
   const size_t o_t = take((size_t)kSlotsPerRow * M * shrink_chunks(big) * r_max * sizeof(float));
   const size_t o_h = take((size_t)M * d * sizeof(float));

@@ -13,21 +13,13 @@
 // The LoRA term enters as extra k steps: t = X W^A (fp32, computed beforehand) split into two bf16 halves
 // (hi + lo, so nothing of t's precision is lost) against W^B of the tenant, masked to that tenant's rows.
 // Bias is added and the result rounded once at the store.
-#include "common.h"
+#include "shrink.h"
 
 namespace milora {
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-// Adapter matrices are reached through pointer tables read at run time; telling the compiler that they lie in
-// global memory keeps their loads off the counter the LDS reads wait on.
-typedef __attribute__((address_space(1))) const bf16_t gbf16;
-__device__ __forceinline__ gbf16* in_global(const void* p) { return (gbf16*)p; }
-
 constexpr int kTM = 256, kTN = 256, kTK = 64;
 constexpr int kThreadsP = 256;
 constexpr int kBlocksM = kTM / 16, kBlocksN = kTN / 16;
@@ -39,14 +31,8 @@ constexpr int kAccTilesRows = 3;
 // Where the sixteen copy instructions of a k step sit among its 64 matrix instructions: those of the first half
 // after instructions 0, kCopyAStride, ..., those of the second half from instruction kCopyB0 on (16 or later: the
 // slot they fill is read until then).
-#ifndef PF_CA
-#define PF_CA 2
-#define PF_CB0 16
-#define PF_CBS 3
-#endif
-constexpr int kCopyAStride = PF_CA, kCopyB0 = PF_CB0, kCopyBStride = PF_CBS;
+constexpr int kCopyAStride = 2, kCopyB0 = 16, kCopyBStride = 3;
 static_assert(kCopyB0 >= 16 && 7 * kCopyAStride < kCopyB0 && kCopyB0 + 7 * kCopyBStride < 64, "copy positions");
-constexpr int kShrinkSplit = kPrefillShrinkParts;  // the shrink's reduction is cut into this many parts, one workgroup each
 constexpr int kGroupM = 4;  // consecutive workgroups of an XCD walk 4 row tiles of one column tile
 
 struct PParams {
@@ -54,8 +40,9 @@ struct PParams {
   const bf16_t* W;
   const bf16_t* bias;
   bf16_t* Y;
-  const float* t;     // kShrinkSplit partial shrinks [part][rows of the whole call][r_max], to be added in part order
+  const float* t;     // `parts` partial shrinks [part][rows of the whole call][r_max], to be added in part order
   size_t t_stride;    // floats from one part to the next
+  int parts;
   const int32_t* row_to_req;
   const int32_t* tenant_id;
   const uint8_t* route;
@@ -73,15 +60,6 @@ __device__ __forceinline__ int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
-}
-
-// 16 bytes per lane from base + voff (global) to LDS at dst + lane * 16, asynchronously; counted by vmcnt.
-// Written as assembly so that the compiler does not order its own LDS reads behind the copy.
-__device__ __forceinline__ void copy_to_lds(const void* base, uint32_t voff, uint32_t dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(dst), "v"(voff), "s"(base)
-               : "memory");
 }
 
 template <int N>
@@ -139,7 +117,7 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
     const int kk = kt < KT ? kt : KT - 1;  // past the end: re-read the last step into a slot nobody reads
     const unsigned char* b = src + (size_t)kk * (kTK * 2);
     const uint32_t dst = lds0 + slot * kHalfBytes + dst_in_half;
-    copy_to_lds(b, voff[hh][j], dst + j * 1024);
+    copy_to_lds16(b, voff[hh][j], dst + j * 1024);
   };
   auto issue = [&](int kt, int hh, int slot) __attribute__((always_inline)) {
 #pragma unroll
@@ -275,7 +253,6 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
     if (cur == 0x7fffffff) break;
     const int r = p.ad.rank[cur];
     gbf16* Bm = in_global(p.ad.B[cur * MILORA_NUM_SITES + p.site]);
-    const int64_t m = m0 + tid;
     const int n = n0 + tid;
     // thread tid fills row tid of the X side and row tid of the W side
     const uint32_t rb = (uint32_t)(tid & 15);
@@ -293,8 +270,8 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
         if (mr < p.M) {
           const float* q = p.t + (size_t)mr * p.ad.r_max + cq;
           if (vec && cq + 3 < p.ad.r_max) {
-#pragma unroll
-            for (int part = 0; part < kShrinkSplit; ++part) {
+#pragma unroll 1
+            for (int part = 0; part < p.parts; ++part) {
               const f32x4 x = *reinterpret_cast<const f32x4*>(q + part * p.t_stride);
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] += x[e];
@@ -302,7 +279,7 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
           } else {
             for (int e = 0; e < 4; ++e)
               if (cq + e < p.ad.r_max)
-                for (int part = 0; part < kShrinkSplit; ++part) v[e] += q[part * p.t_stride + e];
+                for (int part = 0; part < p.parts; ++part) v[e] += q[part * p.t_stride + e];
           }
         }
 #pragma unroll
@@ -367,112 +344,11 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
   }
 }
 
-// ---- LoRA shrink for many rows: t[m][0..r) = X[m] . W^A of the row's tenant, routed rows only --------------
-// One workgroup per 64 rows, 16 per wave.  W^A is [d1][r] (reduction index outermost), the matrix cores
-// want 8 consecutive reduction indices per lane, so 256-row chunks of W^A go through LDS and are read back
-// column-wise; X rows come straight from global memory as operands, a chunk's worth at a time.  A tile
-// whose rows belong to several tenants is computed once per tenant and each row keeps its own tenant's
-// result.  Needs d1 % 32 == 0.
-constexpr int kShrinkRows = 64, kShrinkK = 256, kShrinkC = 64;
-constexpr int kShrinkLd = 66;  // LDS row of 64 columns padded: the 4 k groups of a column read hit distinct banks
-
-__global__ void __launch_bounds__(256, 2) shrink_tiles_kernel(const bf16_t* __restrict__ X, int64_t M, int64_t row_base,
-                                                              int d1, const int32_t* __restrict__ row_to_req,
-                                                              AdapterView ad, int site,
-                                                              const int32_t* __restrict__ tenant_id,
-                                                              const uint8_t* __restrict__ route, int B,
-                                                              float* __restrict__ t, size_t t_stride) {
-  __shared__ bf16_t As[kShrinkK][kShrinkLd];
-  __shared__ int row_ten[kShrinkRows];
-  __shared__ int next_ten;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t m0 = (int64_t)blockIdx.x * kShrinkRows;
-  if (tid < kShrinkRows) {
-    const int64_t m = m0 + tid;
-    int ten = -1;
-    if (m < M) {
-      const int64_t req = row_to_req ? (int64_t)row_to_req[m] : row_base + m;
-      int tenant = 0;
-      if (req >= 0 && req < B && routed_rank(ad, tenant_id, route, (int)req, B, site, &tenant)) ten = tenant;
-    }
-    row_ten[tid] = ten;
-  }
-  __syncthreads();
-  // this workgroup's part of the reduction (whole chunks; the last parts may be empty and then write zeros)
-  const int per_part = ((d1 + kShrinkSplit * kShrinkK - 1) / (kShrinkSplit * kShrinkK)) * kShrinkK;
-  const int k_begin = (int)blockIdx.y * per_part < d1 ? (int)blockIdx.y * per_part : d1;
-  const int k_end = k_begin + per_part < d1 ? k_begin + per_part : d1;
-  t += (size_t)blockIdx.y * t_stride;
-  const int my_row = wave * 16 + (lane & 15);
-  int64_t xrow = m0 + my_row;
-  xrow = xrow < M ? xrow : M - 1;
-  const bf16_t* xp = X + (size_t)xrow * d1 + (lane >> 4) * 8;
-  int last = -1;
-  for (;;) {
-    if (tid == 0) next_ten = 0x7fffffff;
-    __syncthreads();
-    if (tid < kShrinkRows && row_ten[tid] > last) atomicMin(&next_ten, row_ten[tid]);
-    __syncthreads();
-    const int cur = next_ten;
-    if (cur == 0x7fffffff) break;
-    const int r = ad.rank[cur];
-    gbf16* A = in_global(ad.A[cur * MILORA_NUM_SITES + site]);
-    for (int cb = 0; cb < r; cb += kShrinkC) {
-      const int rc = r - cb < kShrinkC ? r - cb : kShrinkC;
-      const int ntile = (rc + 15) >> 4;
-      f32x4 acc[4];
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // this thread stages column c of every fourth row of a chunk; columns past the rank and rows past d1
-      // read a valid element instead (what they produce is never stored / never used)
-      const int c = tid & 63;
-      gbf16* ap = A + cb + (c < rc ? c : 0);
-      for (int k0 = k_begin; k0 < k_end; k0 += kShrinkK) {
-        const int steps = k_end - k0 < kShrinkK ? (k_end - k0) / 32 : kShrinkK / 32;
-        bf16x8 xf[kShrinkK / 32];
-#pragma unroll
-        for (int ks = 0; ks < kShrinkK / 32; ++ks) xf[ks] = *(const bf16x8*)(xp + k0 + (ks < steps ? ks : 0) * 32);
-        __syncthreads();  // the chunk before has been read
-#pragma unroll 16
-        for (int i = 0; i < kShrinkK / 4; ++i) {
-          int k = k0 + (tid >> 6) + 4 * i;
-          k = k < k_end ? k : k_end - 1;
-          As[(tid >> 6) + 4 * i][c] = ap[(size_t)k * r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < kShrinkK / 32; ++ks) {
-          if (ks < steps) {
-            const int kk0 = ks * 32 + (lane >> 4) * 8;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-              if (nt < ntile) {
-                u32x4 w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  w[e] = (uint32_t)As[kk0 + 2 * e][nt * 16 + (lane & 15)] |
-                         ((uint32_t)As[kk0 + 2 * e + 1][nt * 16 + (lane & 15)] << 16);
-                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), xf[ks], acc[nt], 0, 0, 0);
-              }
-            }
-          }
-        }
-      }
-      __syncthreads();
-      // lane holds row lane % 16 of the wave, columns (lane / 16) * 4 .. + 4 of each 16-column tile
-      const int64_t m = m0 + my_row;
-      if (m < M && row_ten[my_row] == cur) {
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int cc = cb + nt * 16 + (lane >> 4) * 4 + e;
-            if (nt < ntile && cc < r) t[(size_t)m * ad.r_max + cc] = acc[nt][e];
-          }
-      }
-    }
-    last = cur;
-  }
+template <int RT>
+__global__ void __launch_bounds__(512, 4) shrink_tiles_kernel(const ShrinkArgs g) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[8 * kShrinkWaveBytes];
+  __shared__ int row_ten[RT * 16];
+  shrink_block<RT, 8>(g, blockIdx.x, blockIdx.y, gridDim.y, smem, row_ten, [](float* p, float v) { *p = v; });
 }
 
 }  // namespace
@@ -508,6 +384,7 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
     p.Y = Y + (size_t)r0 * d2;
     p.t = t + (size_t)r0 * ad.r_max;
     p.t_stride = (size_t)M * ad.r_max;
+    p.parts = shrink_parts(M, d1);
     p.row_to_req = row_to_req ? row_to_req + r0 : nullptr;
     p.row_base = r0;
     p.tenant_id = tenant_id;
@@ -529,15 +406,18 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 }
 
 // LoRA shrink of the rows the tile kernel serves (same conditions as prefill_supported): t receives
-// kPrefillShrinkParts partial results [part][M][r_max] that routed_linear_prefill adds in part order.
+// shrink_parts(M, d1) partial results [part][M][r_max] that routed_linear_prefill adds in part order.
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
                         const int32_t* tenant_id, const uint8_t* route, int B, float* t, hipStream_t stream) {
+  const int parts = shrink_parts(M, d1);
   const int64_t slice = (int64_t)1 << 30;  // rows per launch: the grid index stays well inside 32 bits
   for (int64_t r0 = 0; r0 < M; r0 += slice) {
-    const int64_t mc = M - r0 < slice ? M - r0 : slice;
-    hipLaunchKernelGGL(shrink_tiles_kernel, dim3((unsigned)((mc + kShrinkRows - 1) / kShrinkRows), kShrinkSplit), dim3(256), 0,
-                       stream, X + (size_t)r0 * d1, mc, r0, d1, row_to_req ? row_to_req + r0 : nullptr, ad, site, tenant_id,
-                       route, B, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max);
+    ShrinkArgs g{X + (size_t)r0 * d1, M - r0 < slice ? M - r0 : slice, r0, d1, site, B, row_to_req ? row_to_req + r0 : nullptr,
+                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max};
+    if (M <= kTileMaxRows)
+      hipLaunchKernelGGL((shrink_tiles_kernel<1>), dim3((unsigned)((g.M + 15) / 16), parts), dim3(512), 0, stream, g);
+    else
+      hipLaunchKernelGGL((shrink_tiles_kernel<4>), dim3((unsigned)((g.M + 63) / 64), parts), dim3(512), 0, stream, g);
     const int rc = check_launch();
     if (rc) return rc;
   }

@@ -1,0 +1,29 @@
+// Interface of the matrix-core tile kernel for few to some thousand rows (tiles.hip).
+#pragma once
+#include "common.h"
+
+namespace milora {
+
+// Tiles and parts of the reduction of one launch; a function of the sizes alone, shared by the launch and the sizing of
+// the workspace.
+enum TileShape { kTiles64 = 0, kTiles128 = 1, kTiles256 = 2 };
+struct TilePlan {
+  int shape;  // TileShape: 64 x 64 and 128 x 128 (tiles.hip), 256 x 256 (prefill.hip)
+  int tilesM, tilesN;
+  int S, steps;          // parts of the reduction, stages of 64 k per part
+  size_t partial_bytes;  // fp32 partial tiles in the workspace (0 when S == 1)
+};
+constexpr int kMaxSplitUnits = 512;  // tiles x parts of a launch that cuts its reduction
+// The first bytes of a workspace belong to the control words of the stream kernels (decode.hip), also where a call of
+// other sizes on the same packed weights takes the tile kernel: its status word can be asked for after either.
+constexpr int kStreamCtrlBytes = 16384;
+constexpr int kTileCtrlBytes = kMaxSplitUnits * (int)sizeof(int);  // part counters behind them, zero between launches
+
+// `large`: the 256 x 256 kernel is a choice (row-major weights, 64 rows or more); M up to kTileMaxRows, else it is taken.
+TilePlan plan_tiles(int64_t M, int d1, int d2, bool large);
+bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y);
+int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
+                        const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
+                        int B, const float* t, size_t t_stride, int parts, const TilePlan& pl, int* cnt, float* partial, bf16_t* Y, hipStream_t st);
+
+}  // namespace milora

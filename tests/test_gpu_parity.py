@@ -355,6 +355,25 @@ def test_routed_linear_many_rows_scattered_requests_and_repeatability():
     assert torch.equal(Y, Y2)
 
 
+@pytest.mark.parametrize("layout,M,d,F,site,ranks,T", [
+    (mb.W_ROWMAJOR, 1, 64, 128, 0, (8,), 1),            # one row, one stage of 64 k
+    (mb.W_ROWMAJOR, 63, 192, 1072, 4, (5, 16), 3),      # fewer rows than a tile, a ragged column tile
+    (mb.W_ROWMAJOR, 65, 64, 4160, 6, (64, 256), 4),     # the reduction cut into parts, ranks over one listing of groups
+    (mb.W_ROWMAJOR, 300, 2048, 3520, 5, (8, 32), 6),    # 128 x 128 tiles and parts
+    (mb.W_PACKED, 33, 96, 4128, 6, (8, 12), 33),        # half a stage at the end (d1 % 64 == 32), a tenant per row
+    (mb.W_PACKED, 129, 160, 2064, 4, (16,), 40),        # half a stage at the end, one row in the last row tile
+])
+def test_routed_linear_few_row_tiles(layout, M, d, F, site, ranks, T):
+    """The matrix-core tiles for few and middling rows at the edges of their tiles, stages, parts and rank groups."""
+    wl = small(dtype="bf16", d=d, F=F, T=T, B=min(M, 40), ranks=ranks, tenants="uniform", seed=M + d)
+    g = torch.Generator().manual_seed(M)
+    r2r = torch.sort(torch.randint(0, wl.B, (M,), generator=g))[0]
+    Y, ref = _linear_case(wl, site, M=M, row_to_req=r2r, w_layout=layout, with_bias=(M % 2 == 1), seed=site)
+    assert_rows_close(Y, ref, torch.bfloat16)
+    Y2, _ = _linear_case(wl, site, M=M, row_to_req=r2r, w_layout=layout, with_bias=(M % 2 == 1), seed=site)
+    assert torch.equal(Y, Y2)  # whichever part comes last, the parts are added in their order
+
+
 def test_routed_linear_many_rows_small_integers_bit_exact():
     d1, d2, T, B, r, M, site = 64, 272, 3, 6, 4, 300, 1
     rnd = lambda shape, lo, hi, seed: synth.small_int_tensor(shape, lo, hi, torch.bfloat16, seed, DEV)

@@ -220,7 +220,7 @@ extern "C" int milora_last_hip_error(void) { return g_last_hip_error; }
 
 extern "C" size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2, int r_max) {
   if (M < 1 || d1 < 1 || d2 < 1 || r_max < 1) return 0;
-  // counters of the tile kernel, LoRA shrinks, partial tiles
+  // control words, LoRA shrinks, partial tiles
   size_t partial = 0;
   for (int large = 0; large < 2; ++large) {
     const size_t n = plan_tiles(M <= kTileMaxRows ? M : kTileMaxRows, d1, d2, large != 0).partial_bytes;
@@ -229,7 +229,7 @@ extern "C" size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2
     const size_t rest = M > kTileMaxRows && M % kTileMaxRows ? plan_tiles(M % kTileMaxRows, d1, d2, large != 0).partial_bytes : 0;
     partial = rest > partial ? rest : partial;
   }
-  const size_t tiles = kStreamCtrlBytes + kTileCtrlBytes + align_up((size_t)M * r_max * sizeof(float) * shrink_parts(M, d1), 256) + partial;
+  const size_t tiles = kStreamCtrlBytes + align_up((size_t)M * r_max * sizeof(float) * shrink_parts(M, d1), 256) + partial;
   const int mp = M <= MILORA_MAX_DECODE_BATCH ? (int)M : MILORA_MAX_DECODE_BATCH;
   size_t packed = routed_linear_packed_workspace_bytes(mp, d1, d2, r_max);
   return tiles > packed ? tiles : packed;
@@ -279,9 +279,8 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
         if (rc || m0 + mc >= M) return rc;
       }
   }
-  // (behind the stream kernels' control words: part counters, shrinks t, partial tiles)
-  int* const cnt = (int*)((char*)workspace + kStreamCtrlBytes);
-  float* const t = (float*)((char*)workspace + kStreamCtrlBytes + kTileCtrlBytes);
+  int* const cnt = (int*)((char*)workspace + kTileCtrlOffset);
+  float* const t = (float*)((char*)workspace + kStreamCtrlBytes);
   if (dtype == MILORA_BF16) {
     const bool large = !packed && prefill_supported(M, d1, d2, X, W, Y);
     if (large || tiles_supported(M, d1, d2, packed, X, W, Y)) {

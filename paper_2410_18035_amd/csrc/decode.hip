@@ -2247,13 +2247,15 @@ struct DecodeWs {
   size_t bytes;
 };
 
-DecodeWs carve_decode_ws(void* base, int M, int d, int F, int r_max, bool wide = false) {
+// `linear`: the workspace of a routed linear, whose control words end with the part counters of the tile kernel.
+DecodeWs carve_decode_ws(void* base, int M, int d, int F, int r_max, bool wide = false, bool linear = false) {
   const int big = F > d ? F : d;
   size_t off = 0;
   auto take = [&](size_t n) { size_t o = off; off += align_up(n, 256); return o; };
   const size_t o_fl = take((size_t)(2 * kMaxGrid + 64) * sizeof(int));
   const size_t o_p = take((size_t)kMaxRows * 2 * kSlotsPerRow * sizeof(int));  // at a fixed place whatever M is: the counters must read zero
-  static_assert((2 * kMaxGrid + 64 + kMaxRows * 2 * kSlotsPerRow) * sizeof(int) + 512 <= (size_t)kStreamCtrlBytes, "control words");
+  static_assert((2 * kMaxGrid + 64 + kMaxRows * 2 * kSlotsPerRow) * sizeof(int) + 512 <= (size_t)kTileCtrlOffset, "control words");
+  if (linear) off = kStreamCtrlBytes;
   const size_t o_tf = take((size_t)kSlotsPerRow * M * r_max * sizeof(float));
   const size_t o_t = take((size_t)kSlotsPerRow * M * shrink_chunks(big) * r_max * sizeof(float));
   const size_t o_h = take((size_t)M * d * sizeof(float));
@@ -2474,7 +2476,7 @@ int static_scratch_status(int* status, hipStream_t st) {
 // ---- one routed linear of M <= 128 rows on a packed weight ------------------------------------------
 size_t routed_linear_packed_workspace_bytes(int M, int d1, int d2, int r_max) {
   (void)d2;
-  return carve_decode_ws(nullptr, M, 32, d1, r_max).bytes;
+  return carve_decode_ws(nullptr, M, 32, d1, r_max, false, true).bytes;
 }
 
 int routed_linear_packed(const bf16_t* X, int M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W,
@@ -2483,7 +2485,7 @@ int routed_linear_packed(const bf16_t* X, int M, int d1, int d2, const int32_t* 
   const int MT = mt_for(M);
   const int G = grid_for(MT);
   if (G <= 0) return hip_fail(hipGetLastError());
-  DecodeWs ws = carve_decode_ws(workspace, M, 32, d1, ad.r_max);
+  DecodeWs ws = carve_decode_ws(workspace, M, 32, d1, ad.r_max, false, true);
   Params p;
   fill_common(p, ws, M, B, d1, ad, tenant_id, route, row_to_req);
   Stage l;

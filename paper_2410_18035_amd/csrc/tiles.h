@@ -14,10 +14,12 @@ struct TilePlan {
   size_t partial_bytes;  // fp32 partial tiles in the workspace (0 when S == 1)
 };
 constexpr int kMaxSplitUnits = 512;  // tiles x parts of a launch that cuts its reduction
-// The first bytes of a workspace belong to the control words of the stream kernels (decode.hip), also where a call of
-// other sizes on the same packed weights takes the tile kernel: its status word can be asked for after either.
+// The first bytes of a routed linear's workspace belong to control words: those of the stream kernels (decode.hip), then the
+// part counters of the tile kernel, zero between launches.  Both keep their data behind them, so calls of any sizes and
+// either layout can follow one another on one workspace, and the status word can be asked for after either.
 constexpr int kStreamCtrlBytes = 16384;
-constexpr int kTileCtrlBytes = kMaxSplitUnits * (int)sizeof(int);  // part counters behind them, zero between launches
+constexpr int kTileCtrlBytes = kMaxSplitUnits * (int)sizeof(int);
+constexpr int kTileCtrlOffset = kStreamCtrlBytes - kTileCtrlBytes;
 
 // `large`: the 256 x 256 kernel is a choice (row-major weights, 64 rows or more); M up to kTileMaxRows, else it is taken.
 TilePlan plan_tiles(int64_t M, int d1, int d2, bool large);

@@ -374,6 +374,26 @@ def test_routed_linear_few_row_tiles(layout, M, d, F, site, ranks, T):
     assert torch.equal(Y, Y2)  # whichever part comes last, the parts are added in their order
 
 
+def test_routed_linear_calls_of_other_sizes_on_one_workspace():
+    """Stream kernel, tiles of both layouts with the reduction in parts, in turn on one workspace: the control words
+    of either keep their places whatever the other left behind them."""
+    wl = small(dtype="bf16", d=4160, F=64, T=4, B=4, ranks=(64, 256), tenants="uniform", seed=77)
+    W, ad, tab = device_layer(wl)
+    tid, route = synth.tenant_ids(wl).to(DEV), torch.full((wl.B,), 4, dtype=torch.uint8, device=DEV)
+    Wp = mb.milora_pack_weight(W[4])
+    g = torch.Generator(device=DEV).manual_seed(3)
+    need = [mb.routed_linear_workspace_bytes(M, wl.d, wl.F, tab.r_max) for M in (16, 65, 130)]
+    ws = torch.zeros(max(need), dtype=torch.uint8, device=DEV)
+    for i, (M, layout) in enumerate([(16, mb.W_PACKED), (65, mb.W_PACKED), (32, mb.W_PACKED), (65, mb.W_ROWMAJOR),
+                                     (130, mb.W_ROWMAJOR), (16, mb.W_PACKED), (130, mb.W_PACKED)]):
+        X = torch.empty(M, wl.d, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+        r2r = (torch.arange(M, dtype=torch.int32, device=DEV) * wl.B) // M
+        args = (X, Wp if layout == mb.W_PACKED else W[4], tab, 4, tid, route, r2r)
+        shared = mb.milora_routed_linear(*args, w_layout=layout, d2=wl.F, out=torch.full((M, wl.F), 7.0, dtype=X.dtype, device=DEV), workspace=ws)
+        fresh = mb.milora_routed_linear(*args, w_layout=layout, d2=wl.F)
+        assert torch.equal(shared, fresh), f"call {i}: {M} rows, layout {layout}"
+
+
 def test_routed_linear_many_rows_small_integers_bit_exact():
     d1, d2, T, B, r, M, site = 64, 272, 3, 6, 4, 300, 1
     rnd = lambda shape, lo, hi, seed: synth.small_int_tensor(shape, lo, hi, torch.bfloat16, seed, DEV)

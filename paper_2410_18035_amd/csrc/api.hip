@@ -50,17 +50,17 @@ __device__ __forceinline__ float block_sum(float v, float* sh) {
 }
 
 // out[m] = T(n(in[m])) with n = weightless RMS normalisation (one workgroup per row).
-template <typename T>
-__global__ void __launch_bounds__(kThreads) rmsnorm_rows_kernel(const T* __restrict__ in, int d, T* __restrict__ out) {
+template <typename Tin, typename T>
+__global__ void __launch_bounds__(kThreads) rmsnorm_rows_kernel(const Tin* __restrict__ in, int d, T* __restrict__ out) {
   __shared__ float sh[kThreads / 64];
   const size_t m = blockIdx.x;
   float ss = 0.f;
   for (int i = threadIdx.x; i < d; i += kThreads) {
-    const float v = Elem<T>::load(in, m * d + i);
+    const float v = Elem<Tin>::load(in, m * d + i);
     ss += v * v;
   }
   const float inv = rsqrtf(block_sum<T>(ss, sh) / (float)d + 1e-5f);
-  for (int i = threadIdx.x; i < d; i += kThreads) Elem<T>::store(out, m * d + i, Elem<T>::load(in, m * d + i) * inv);
+  for (int i = threadIdx.x; i < d; i += kThreads) Elem<T>::store(out, m * d + i, Elem<Tin>::load(in, m * d + i) * inv);
 }
 
 // h = x + o in fp32; hn = T(n(h)) or T(h).
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(kThreads) interleave_qkv_kernel(const T* __res
 
 // Workspace of the any-shape layer path.
 struct GenericWs {
-  float* t;   // [B][r_max]
+  float* t;   // [3][B][r_max]
   float* h;   // [B][d]
   char* xn;   // [B][d]   T
   char* qkv;  // [3][B][d] T
@@ -124,7 +124,7 @@ GenericWs carve_generic(void* base, int B, int d, int F, int r_max, size_t es) {
   auto take = [&](size_t n) { size_t o = off; off += align_up(n, 256); return o; };
   char* b = (char*)base;
   GenericWs w;
-  w.t = (float*)(b + take((size_t)B * r_max * 4));
+  w.t = (float*)(b + take((size_t)3 * B * r_max * 4));
   w.h = (float*)(b + take((size_t)B * d * 4));
   w.xn = b + take((size_t)B * d * es);
   w.qkv = b + take((size_t)3 * B * d * es);
@@ -138,24 +138,69 @@ GenericWs carve_generic(void* base, int B, int d, int F, int r_max, size_t es) {
   return w;
 }
 
+// Up to kFewRows rows: four launches with the glue in their stores (two more with normalisation).
+template <typename T>
+int layer_decode_few(const void* x, int B, int d, int F, int dtype, const milora_layer_weights* wts, const AdapterView& ad,
+                     const int32_t* tenant_id, const uint8_t* route, int norm, const void* attn_out, void* y, void* qkv_out,
+                     const GenericWs& w, hipStream_t st) {
+  int rc;
+  FewArgs g{};
+  g.M = g.B = B;
+  g.tenant_id = tenant_id;
+  g.route = route;
+  g.ad = ad;
+  auto run = [&](int site0, int sites, int mode, const void* in, int64_t ldx) {
+    g.X = in;
+    g.ldx = ldx;
+    site_dims(site0, d, F, &g.d1, &g.d2);
+    for (int s = 0; s < sites; ++s) { g.site[s] = site0 + s; g.W[s] = wts->W[site0 + s]; }
+    return launch_few_rows(g, dtype, sites, mode, w.t, st);
+  };
+  const void* xin = x;
+  if (norm) {
+    hipLaunchKernelGGL((rmsnorm_rows_kernel<T, T>), dim3(B), dim3(kThreads), 0, st, (const T*)x, d, (T*)w.xn);
+    if ((rc = check_launch())) return rc;
+    xin = w.xn;
+  }
+  T* const qkv = qkv_out ? (T*)qkv_out : (T*)w.qkv;  // [B][3 d]
+  for (int s = 0; s < 3; ++s) g.Y[s] = qkv + (size_t)s * d;
+  g.ldy = 3 * (int64_t)d;
+  if ((rc = run(0, 3, kFewPlain, xin, d))) return rc;
+  const bool h_is_input = !norm && sizeof(T) == 4;
+  g.x_res = x;
+  g.h = w.h;
+  g.Y[0] = norm || h_is_input ? nullptr : w.hn;
+  rc = attn_out ? run(3, 1, kFewResid, attn_out, d) : run(3, 1, kFewResid, qkv + 2 * (size_t)d, 3 * (int64_t)d);
+  if (rc) return rc;
+  if (norm) {
+    hipLaunchKernelGGL((rmsnorm_rows_kernel<float, T>), dim3(B), dim3(kThreads), 0, st, w.h, d, (T*)w.hn);
+    if ((rc = check_launch())) return rc;
+  }
+  g.Y[0] = w.mm;
+  g.ldy = F;
+  if ((rc = run(4, 2, kFewGateUp, h_is_input ? (const void*)w.h : (const void*)w.hn, d))) return rc;
+  g.Y[0] = y;
+  return run(6, 1, kFewDown, w.mm, F);
+}
+
 template <typename T>
 int layer_decode_generic(const void* x, int B, int d, int F, int dtype, const milora_layer_weights* wts,
                          const AdapterView& ad, const int32_t* tenant_id, const uint8_t* route, uint32_t flags,
                          const void* attn_out, void* y, void* qkv_out, void* workspace, hipStream_t st) {
   GenericWs w = carve_generic(workspace, B, d, F, ad.r_max, sizeof(T));
   const int norm = (flags & MILORA_LAYER_RMSNORM) ? 1 : 0;
+  if (B <= kFewRows)
+    return layer_decode_few<T>(x, B, d, F, dtype, wts, ad, tenant_id, route, norm, attn_out, y, qkv_out, w, st);
   int rc;
   auto lin = [&](const void* in, int site, void* out) -> int {
     int d1, d2;
     site_dims(site, d, F, &d1, &d2);
-    int r = launch_shrink(in, B, d1, dtype, nullptr, ad, site, tenant_id, route, B, w.t, st);
-    if (r) return r;
     return launch_linear_generic(in, B, d1, d2, dtype, nullptr, wts->W[site], nullptr, ad, site, tenant_id, route, B,
                                  w.t, out, st);
   };
   const void* xin = x;
   if (norm) {
-    hipLaunchKernelGGL(rmsnorm_rows_kernel<T>, dim3(B), dim3(kThreads), 0, st, (const T*)x, d, (T*)w.xn);
+    hipLaunchKernelGGL((rmsnorm_rows_kernel<T, T>), dim3(B), dim3(kThreads), 0, st, (const T*)x, d, (T*)w.xn);
     if ((rc = check_launch())) return rc;
     xin = w.xn;
   }
@@ -308,8 +353,6 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
       return MILORA_OK;
     }
   }
-  rc = launch_shrink(X, M, d1, dtype, row_to_req, ad, site, tenant_id, route, B, t, st);
-  if (rc) return rc;
   return launch_linear_generic(X, M, d1, d2, dtype, row_to_req, W, bias, ad, site, tenant_id, route, B, t, Y, st);
 }
 

@@ -158,16 +158,45 @@ inline int shrink_parts(int64_t M, int d1) {
 }
 
 // ---- internal entry points shared between translation units ------------------------------------
-// LoRA shrink: for every row m whose request is routed to `site`, t[m][0..r) = X[m] . A (fp32).
-// t is [M][r_max] floats; rows that carry no LoRA term are left untouched.
-int launch_shrink(const void* X, int64_t M, int d1, int dtype, const int32_t* row_to_req, const AdapterView& ad,
-                  int site, const int32_t* tenant_id, const uint8_t* route, int B, float* t, hipStream_t stream);
+// LoRA shrink in fp32: for every row m whose request is routed to site `site + i`, i < sites, t[i][m][0..r) = X[m] . A.
+// X has rows of ldx elements, t is [sites][M][r_max] floats; rows that carry no LoRA term are left untouched.
+int launch_shrink(const void* X, int64_t ldx, int64_t M, int d1, int dtype, const int32_t* row_to_req, const AdapterView& ad,
+                  int site, int sites, const int32_t* tenant_id, const uint8_t* route, int B, float* t, hipStream_t stream);
 
-// Any-shape linear with the LoRA expand fused before the single rounding:
-// Y[m] = X[m] W + bias + t[m] . B for routed rows.  W row-major [d2][d1].
+// Any-shape linear with the LoRA term added before the single rounding:
+// Y[m] = X[m] W + bias + (X[m] A) B for routed rows.  W row-major [d2][d1]; t: scratch of [M][r_max] floats.
 int launch_linear_generic(const void* X, int64_t M, int d1, int d2, int dtype, const int32_t* row_to_req,
                           const void* W, const void* bias, const AdapterView& ad, int site,
-                          const int32_t* tenant_id, const uint8_t* route, int B, const float* t, void* Y,
-                          hipStream_t stream);
+                          const int32_t* tenant_id, const uint8_t* route, int B, float* t, void* Y, hipStream_t stream);
+
+// The same for up to kFewRows rows, with the glue of a layer's decode step in its store.
+constexpr int kFewRows = 16;
+constexpr int kFuseRank = 16;  // ranks up to here are shrunk inside the launch
+enum FewMode {
+  kFewPlain,   // Y[i] = the linear at site[i], i < sites
+  kFewResid,   // h = x_res + linear (fp32); Y[0] = h rounded, if given
+  kFewGateUp,  // Y[0] = silu(linear at site[0]) * linear at site[1]
+  kFewDown,    // Y[0] = h + linear
+};
+struct FewArgs {
+  const void* X;  // M rows of ldx elements
+  int64_t ldx;
+  int M, d1, d2;
+  const void* W[3];
+  const void* bias;
+  void* Y[3];     // rows of ldy elements
+  int64_t ldy;
+  int site[3];    // consecutive
+  const int32_t* row_to_req;
+  const int32_t* tenant_id;
+  const uint8_t* route;
+  int B;
+  AdapterView ad;
+  const void* x_res;
+  float* h;
+  const float* t;  // filled in by the launch
+};
+// t: scratch of [sites][M][r_max] floats
+int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t stream);
 
 }  // namespace milora

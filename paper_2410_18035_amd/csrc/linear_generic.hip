@@ -1,144 +1,495 @@
-// Any-shape, any-dtype routed LoRA linear (paper Eq. 1 with the layer-level gate of Sec. 3.3).
-// This is the path for fp32 tensors, row-major weights with unaligned sizes and for whatever the
-// matrix-core kernels do not cover.  Two kernels: the LoRA shrink t = x W^A for routed rows, and a
-// tiled fp32 GEMM whose epilogue adds bias and t W^B before the single rounding to the output type.
+// Any-shape, any-dtype routed LoRA linear (paper Eq. 1 with the layer-level gate of Sec. 3.3): fp32 tensors, and bf16 ones
+// of widths or alignments that the bf16 matrix-core kernels do not take.  All arithmetic is fp32, on the fp32 matrix
+// instructions (157 TFLOP/s on the chip, twice the rate of vector FMA, each product and sum rounded as there).
+//
+// Operands are taken four consecutive k per lane (any element alignment; the row's last k one by one): instruction e of
+// four multiplies element e of both sides, so the k of a block of 8 or 16 are taken in another order than memory's, the
+// same one on both sides.  All sums run in a fixed order.
 #include "common.h"
 
 namespace milora {
 
 namespace {
 
-constexpr int kThreads = 256;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 
-// One workgroup per row m: t[m][c] = sum_k X[m][k] * A[k][c], c < r.  Threads are laid out with the
-// rank index fastest (coalesced reads of A's rows); the k-lanes are summed through LDS in a fixed order.
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4_a4*>(p); }
+__device__ __forceinline__ f32x4 load4(const bf16_t* p) {
+  const u16x4_a2 v = *reinterpret_cast<const u16x4_a2*>(p);
+  return f32x4{bf16_to_f32(v[0]), bf16_to_f32(v[1]), bf16_to_f32(v[2]), bf16_to_f32(v[3])};
+}
+// Elements k .. k + 3 of a row of K, zero past its end.
 template <typename T>
-__global__ void __launch_bounds__(kThreads) shrink_rows_kernel(const T* __restrict__ X, int64_t M, int d1,
+__device__ __forceinline__ f32x4 load4_end(const T* row, int k, int K) {
+  f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (k + 4 <= K) v = load4(row + k);
+  else
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + e < K) v[e] = Elem<T>::load(row, k + e);
+  return v;
+}
+__device__ __forceinline__ int pow2_above(int r) {
+  int p = 1;
+  while (p < r) p <<= 1;
+  return p;
+}
+
+// ---- LoRA shrink: t[m][c] = sum_k X[m][k] * A[k][c], c < r, one workgroup per (row, site) -------------------------
+// Threads are laid out with the rank index fastest (coalesced reads of A's rows), eight rows of A per thread on their
+// way; the k-lanes are summed through LDS in a fixed order.  Bound by the latency of those loads: 512 threads instead of
+// 256 and eight loads in flight instead of one.
+constexpr int kShrinkT = 512;
+template <typename T>
+__global__ void __launch_bounds__(kShrinkT) shrink_rows_kernel(const T* __restrict__ X, int64_t ldx, int64_t M, int d1,
                                                                const int32_t* __restrict__ row_to_req, AdapterView ad,
-                                                               int site, const int32_t* __restrict__ tenant_id,
+                                                               int site0, const int32_t* __restrict__ tenant_id,
                                                                const uint8_t* __restrict__ route, int B,
                                                                float* __restrict__ t) {
-  __shared__ float red[kThreads];
+  __shared__ float red[kShrinkT];
   const int64_t m = blockIdx.x;
+  const int site = site0 + blockIdx.y;
   const int64_t req = row_to_req ? (int64_t)row_to_req[m] : m;
   int tenant = 0;
   const int r = (req >= 0 && req < B) ? routed_rank(ad, tenant_id, route, (int)req, B, site, &tenant) : 0;
   if (r == 0) return;
   const T* A = (const T*)ad.A[tenant * MILORA_NUM_SITES + site];
-  int rpad = 1;
-  while (rpad < r) rpad <<= 1;
-  const int c = threadIdx.x % rpad, krow = threadIdx.x / rpad, rpp = kThreads / rpad;
+  const int rpad = pow2_above(r);
+  const int c = threadIdx.x & (rpad - 1), krow = threadIdx.x / rpad, rpp = kShrinkT / rpad;
+  const T* x = X + (size_t)m * ldx;
   float acc = 0.f;
-  if (c < r)
-    for (int k = krow; k < d1; k += rpp) acc += Elem<T>::load(X, (size_t)m * d1 + k) * Elem<T>::load(A, (size_t)k * r + c);
+  if (c < r) {
+    int k = krow;
+    for (; k + 7 * rpp < d1; k += 8 * rpp) {
+      float xv[8], av[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        xv[u] = Elem<T>::load(x, k + u * rpp);
+        av[u] = Elem<T>::load(A, (size_t)(k + u * rpp) * r + c);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += xv[u] * av[u];
+    }
+    for (; k < d1; k += rpp) acc += Elem<T>::load(x, k) * Elem<T>::load(A, (size_t)k * r + c);
+  }
   red[threadIdx.x] = acc;
   __syncthreads();
   if (krow == 0 && c < r) {
     float s = 0.f;
     for (int j = 0; j < rpp; ++j) s += red[j * rpad + c];
-    t[(size_t)m * ad.r_max + c] = s;
+    t[((size_t)blockIdx.y * M + m) * ad.r_max + c] = s;
   }
 }
 
-// 64x64 output tile per workgroup, 16-deep k slices through LDS, 4x4 outputs per thread, fp32 FMA.
-// W is row-major [d2][d1].  Epilogue: + bias, + t[m] . B for rows that carry a LoRA term at `site`.
+// ---- few rows: up to 16 --------------------------------------------------------------------------------------------
+// A workgroup takes 16 columns of one linear (gate and up: of both) and the whole reduction, dealt to its eight waves in
+// blocks of 16 k that go straight from global memory into matrix operands; the waves' sums meet in LDS.  Ranks up to
+// kFuseRank are shrunk here too, each wave over its share of k (every workgroup does it again: the sums of a row are
+// 16 times less than the workgroup's share of the linear or about as many), others come from shrink_rows_kernel.
+// The layer's glue is part of the store: a decode step of a layer is four launches instead of eighteen.
+// Bound: launches and the chain of dependent loads (route -> adapter tables -> A) of each.  A decode step of 4 rows
+// through the 256 x 688 fp32 layer, rank 8: 284 us with eighteen launches, 24.8 us with these.
+constexpr int kFewT = 512, kFewW = kFewT / 64;
+constexpr int kFewBlocks = 4;  // blocks of 16 k per wave on their way
+
 template <typename T>
-__global__ void __launch_bounds__(kThreads) linear_tile_kernel(const T* __restrict__ X, int64_t M, int d1, int d2,
-                                                               const int32_t* __restrict__ row_to_req,
-                                                               const T* __restrict__ W, const T* __restrict__ bias,
-                                                               AdapterView ad, int site,
-                                                               const int32_t* __restrict__ tenant_id,
-                                                               const uint8_t* __restrict__ route, int B,
-                                                               const float* __restrict__ t, T* __restrict__ Y) {
-  constexpr int TM = 64, TN = 64, TK = 16;
-  __shared__ float xs[TK][TM + 1];
-  __shared__ float ws[TK][TN + 1];
-  const int64_t m0 = (int64_t)blockIdx.y * TM;
-  const int n0 = blockIdx.x * TN;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4];
+__device__ __forceinline__ float round_to(float v) {
+  T q;
+  Elem<T>::store(&q, 0, v);
+  return Elem<T>::load(&q, 0);
+}
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
+  constexpr int NW = MODE == kFewGateUp ? 2 : 1;
+  __shared__ float red[NW][kFewW][16][17];
+  __shared__ float tpart[NW][kFewW][16][kFuseRank];
+  __shared__ float ts[NW][16][kFuseRank];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int s0 = MODE == kFewGateUp ? 0 : blockIdx.y, n0 = blockIdx.x * 16;
+  const int d1 = g.d1;
+  const bool fused = g.t == nullptr;
+
+  // rank and tenant of row li at the workgroup's sites (route byte and tenant id are asked for together)
+  int rank[NW], ten[NW];
+  {
+    const int64_t req = li < g.M ? (g.row_to_req ? (int64_t)g.row_to_req[li] : li) : -1;
+    const bool in = req >= 0 && req < g.B;
+    const uint8_t rt = in ? g.route[req] : (uint8_t)MILORA_ROUTE_NONE;
+    const int tn = in ? g.tenant_id[req] : -1;
+    const bool known = tn >= 0 && tn < g.ad.n_tenants;
+    const int r = known ? g.ad.rank[tn] : 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < d1; k0 += TK) {
-    // 64 rows x 16 k of X and of W: 1024 elements each, 4 per thread, k fastest (contiguous in memory)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = threadIdx.x + e * kThreads;
-      const int kk = idx % TK, rr = idx / TK;
-      const int k = k0 + kk;
-      const int64_t m = m0 + rr;
-      const int n = n0 + rr;
-      xs[kk][rr] = (m < M && k < d1) ? Elem<T>::load(X, (size_t)m * d1 + k) : 0.f;
-      ws[kk][rr] = (n < d2 && k < d1) ? Elem<T>::load(W, (size_t)n * d1 + k) : 0.f;
+    for (int j = 0; j < NW; ++j) {
+      const bool has = known && route_has(rt, g.site[s0 + j]) && r >= 1 && r <= g.ad.r_max;
+      rank[j] = has ? r : 0;
+      ten[j] = has ? tn : 0;
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = xs[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = ws[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-    }
-    __syncthreads();
   }
+
+  // ---- base linear ----
+  const T* const xr = (const T*)g.X + (size_t)(li < g.M ? li : g.M - 1) * g.ldx;  // (rows past the end: results dropped)
+  const int col = n0 + li < g.d2 ? n0 + li : g.d2 - 1;
+  const T* wr[NW];
+  f32x4 acc[NW];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-    const int64_t req = row_to_req ? (int64_t)row_to_req[m] : m;
-    int tenant = 0;
-    const int r = (req >= 0 && req < B) ? routed_rank(ad, tenant_id, route, (int)req, B, site, &tenant) : 0;
-    const T* Bm = r ? (const T*)ad.B[tenant * MILORA_NUM_SITES + site] : nullptr;
+  for (int j = 0; j < NW; ++j) {
+    wr[j] = (const T*)g.W[s0 + j] + (size_t)col * d1;
+    acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const int full = d1 >> 4;
+  for (int b0 = w; b0 < full; b0 += kFewW * kFewBlocks) {
+    f32x4 xv[kFewBlocks], wv[NW][kFewBlocks];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= d2) continue;
-      float v = acc[i][j];
-      if (bias) v += Elem<T>::load(bias, n);
-      if (r) {
-        float delta = 0.f;
-        for (int c = 0; c < r; ++c) delta += t[(size_t)m * ad.r_max + c] * Elem<T>::load(Bm, (size_t)c * d2 + n);
-        v += delta;
+    for (int u = 0; u < kFewBlocks; ++u) {
+      const int b = b0 + u * kFewW < full ? b0 + u * kFewW : full - 1;
+      xv[u] = load4(xr + b * 16 + lq * 4);
+#pragma unroll
+      for (int j = 0; j < NW; ++j) wv[j][u] = load4(wr[j] + b * 16 + lq * 4);
+    }
+#pragma unroll
+    for (int u = 0; u < kFewBlocks; ++u)
+      if (b0 + u * kFewW < full)
+#pragma unroll
+        for (int j = 0; j < NW; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[j][u][e], xv[u][e], acc[j], 0, 0, 0);
+  }
+  if (full * 16 < d1 && w == full % kFewW) {
+    const f32x4 x = load4_end(xr, full * 16 + lq * 4, d1);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      const f32x4 v = load4_end(wr[j], full * 16 + lq * 4, d1);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], x[e], acc[j], 0, 0, 0);
+    }
+  }
+  // (lane: row li, columns 4 lq .. + 3 of the 16)
+#pragma unroll
+  for (int j = 0; j < NW; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[j][w][li][lq * 4 + e] = acc[j][e];
+
+  // ---- shrinks of the routed rows over this wave's share of k ----
+  if (fused) {
+    const int share = (d1 + kFewW - 1) / kFewW, k0 = w * share, k1 = k0 + share < d1 ? k0 + share : d1;
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+      for (unsigned long long left = __ballot(lane < 16 && rank[j] > 0); left; left &= left - 1) {
+        const int m = __builtin_ctzll(left);
+        const int r = __builtin_amdgcn_readlane(rank[j], m), tn = __builtin_amdgcn_readlane(ten[j], m);
+        const T* const A = (const T*)g.ad.A[tn * MILORA_NUM_SITES + g.site[s0 + j]];
+        const T* const x = (const T*)g.X + (size_t)m * g.ldx;
+        const int rpad = pow2_above(r), c = lane & (rpad - 1), kpl = 64 / rpad;
+        float sum = 0.f;
+        for (int k = k0 + lane / rpad; __any(k < k1); k += 8 * kpl) {
+          float xv[8], av[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int kk = k + u * kpl < k1 ? k + u * kpl : d1 - 1;
+            xv[u] = Elem<T>::load(x, kk);
+            av[u] = Elem<T>::load(A, (size_t)kk * r + (c < r ? c : 0));
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) sum += k + u * kpl < k1 ? xv[u] * av[u] : 0.f;
+        }
+        for (int off = rpad; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+        if (lane < r) tpart[j][w][m][lane] = sum;
       }
-      Elem<T>::store(Y, (size_t)m * d2 + n, v);
+  }
+  __syncthreads();
+  const int m = tid >> 4, n = n0 + (tid & 15);  // threads 0 .. 255: one output each; their lanes' rows are 4 (tid / 64) ..
+  int rm[NW], tm[NW];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) {
+    rm[j] = __shfl(rank[j], m & 15, 64);
+    tm[j] = __shfl(ten[j], m & 15, 64);
+  }
+  if (fused && tid < 256) {
+    const int c = tid & 15;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      float s = 0.f;
+      if (c < rm[j])
+        for (int k = 0; k < kFewW; ++k) s += tpart[j][k][m][c];
+      ts[j][m][c] = s;  // (read by the same sixteen lanes)
     }
   }
+  __syncthreads();
+  if (tid >= 256 || m >= g.M || n >= g.d2) return;
+
+  // ---- bias, LoRA expand, glue, one rounding ----
+  float val[NW];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < kFewW; ++k) v += red[j][k][m][tid & 15];
+    if (g.bias) v += Elem<T>::load((const T*)g.bias, n);
+    if (rm[j] > 0) {
+      const T* const Bm = (const T*)g.ad.B[tm[j] * MILORA_NUM_SITES + g.site[s0 + j]] + n;
+      const float* const tg = fused ? nullptr : g.t + ((size_t)(s0 + j) * g.M + m) * g.ad.r_max;
+      float delta = 0.f;
+      for (int c0 = 0; c0 < rm[j]; c0 += 8) {
+        float bv[8], tv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int c = c0 + u < rm[j] ? c0 + u : rm[j] - 1;
+          bv[u] = Elem<T>::load(Bm, (size_t)c * g.d2);
+          tv[u] = fused ? ts[j][m][c & (kFuseRank - 1)] : tg[c];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) delta += c0 + u < rm[j] ? tv[u] * bv[u] : 0.f;
+      }
+      v += delta;
+    }
+    val[j] = v;
+  }
+  if constexpr (MODE == kFewPlain) {
+    Elem<T>::store((T*)g.Y[s0], (size_t)m * g.ldy + n, val[0]);
+  } else if constexpr (MODE == kFewResid) {
+    const size_t i = (size_t)m * g.d2 + n;
+    const float h = Elem<T>::load((const T*)g.x_res, i) + round_to<T>(val[0]);
+    g.h[i] = h;
+    if (g.Y[0]) Elem<T>::store((T*)g.Y[0], i, h);
+  } else if constexpr (MODE == kFewGateUp) {
+    Elem<T>::store((T*)g.Y[0], (size_t)m * g.ldy + n, silu(round_to<T>(val[0])) * round_to<T>(val[1]));
+  } else {
+    const size_t i = (size_t)m * g.d2 + n;
+    Elem<T>::store((T*)g.Y[0], i, g.h[i] + round_to<T>(val[0]));
+  }
+}
+
+// ---- more rows ------------------------------------------------------------------------------------------------------
+// A workgroup of eight waves computes a BM x BN tile: KQ groups of waves share a stage's k, the waves of a group the tile,
+// 32 x 32 each (v_mfma_f32_32x32x2_f32).  Stages go through registers (two on their way) into one of two LDS buffers.
+template <int BM_, int BN_, int KW_>
+struct GenCfg {
+  static constexpr int BM = BM_, BN = BN_, KW = KW_;                 // KW: k of a stage per wave
+  static constexpr int WM = BM / 32, WN = BN / 32, KQ = 8 / (WM * WN);
+  static constexpr int SK = KQ * KW, Ld = SK + 4;                    // rows padded: 16 rows at one k hit all banks
+  static constexpr int T = 512;
+  static constexpr int Items = (BM + BN) * (SK / 4) / T;             // 16-byte pieces of a stage per thread
+  static constexpr int BufFloats = (BM + BN) * Ld;
+  static constexpr int LdR = BN + 4;
+  static constexpr int Outs = BM * BN / T;                           // outputs per thread
+  static constexpr int TsOff = KQ * BM * LdR;                        // after the sums: t of the rows, 32 ranks at a time
+  static constexpr int LdsBytes = (2 * BufFloats > TsOff + BM * 32 ? 2 * BufFloats : TsOff + BM * 32) * 4;
+  static_assert((BM + BN) * (SK / 4) % T == 0 && BM * BN % T == 0 && KW % 8 == 0 && 2 * LdsBytes <= 158 * 1024, "tile shape");
+};
+typedef GenCfg<32, 32, 16> GenSmall;
+typedef GenCfg<64, 64, 32> GenLarge;
+constexpr int kGenLargeTiles = 128;
+
+template <typename T, class C>
+__global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restrict__ X, int64_t M, int d1, int d2,
+                                                           const int32_t* __restrict__ row_to_req, const T* __restrict__ W,
+                                                           const T* __restrict__ bias, AdapterView ad, int site,
+                                                           const int32_t* __restrict__ tenant_id,
+                                                           const uint8_t* __restrict__ route, int B,
+                                                           const float* __restrict__ t, T* __restrict__ Y) {
+  extern __shared__ __attribute__((aligned(16))) float buf[];
+  __shared__ int s_rank[C::BM], s_ten[C::BM], s_most;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = w / (C::WM * C::WN), wm = w % (C::WM * C::WN) % C::WM, wn = w % (C::WM * C::WN) / C::WM;
+  const int64_t m0 = (int64_t)blockIdx.y * C::BM;
+  const int n0 = blockIdx.x * C::BN;
+
+  const T* src[C::Items];
+  const int kq = tid % (C::SK / 4) * 4;
+  int dst[C::Items];
+#pragma unroll
+  for (int i = 0; i < C::Items; ++i) {
+    const int row = tid / (C::SK / 4) + i * (C::T / (C::SK / 4));
+    if (row < C::BM) {
+      const int64_t m = m0 + row < M ? m0 + row : M - 1;  // past the edge: the last row again, its results are dropped
+      src[i] = X + (size_t)m * d1;
+    } else {
+      const int n = n0 + row - C::BM < d2 ? n0 + row - C::BM : d2 - 1;
+      src[i] = W + (size_t)n * d1;
+    }
+    dst[i] = row * C::Ld + kq;
+  }
+  const int stages = (d1 + C::SK - 1) / C::SK;
+  f32x4 ra[C::Items], rb[C::Items];
+  auto load = [&](int st, f32x4 (&r)[C::Items]) __attribute__((always_inline)) {
+    if (st < stages)
+#pragma unroll
+      for (int i = 0; i < C::Items; ++i) r[i] = load4_end(src[i], st * C::SK + kq, d1);
+  };
+  auto store = [&](int b, const f32x4 (&r)[C::Items]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < C::Items; ++i) *reinterpret_cast<f32x4*>(buf + b * C::BufFloats + dst[i]) = r[i];
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  const int xo = (wm * 32 + l32) * C::Ld + q * C::KW + lh * 4, wo = (C::BM + wn * 32 + l32) * C::Ld + q * C::KW + lh * 4;
+  auto compute = [&](int b) __attribute__((always_inline)) {
+    const float* const s = buf + b * C::BufFloats;
+#pragma unroll
+    for (int k = 0; k < C::KW; k += 8) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(s + xo + k), v = *reinterpret_cast<const f32x4*>(s + wo + k);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], x[e], acc, 0, 0, 0);
+    }
+  };
+  load(0, ra);
+  load(1, rb);
+  if (tid == 0) s_most = 0;
+  store(0, ra);
+  load(2, ra);
+  __syncthreads();
+  if (tid < C::BM) {  // which rows carry a LoRA term
+    const int64_t m = m0 + tid;
+    int tenant = 0, r = 0;
+    if (m < M) {
+      const int64_t req = row_to_req ? (int64_t)row_to_req[m] : m;
+      r = (req >= 0 && req < B) ? routed_rank(ad, tenant_id, route, (int)req, B, site, &tenant) : 0;
+    }
+    s_rank[tid] = r;
+    s_ten[tid] = tenant;
+    if (r) atomicMax(&s_most, r);
+  }
+  for (int st = 0; st < stages; st += 2) {
+    compute(0);
+    if (st + 1 < stages) store(1, rb);
+    load(st + 3, rb);
+    __syncthreads();
+    if (st + 1 >= stages) break;
+    compute(1);
+    if (st + 2 < stages) store(0, ra);
+    load(st + 4, ra);
+    __syncthreads();
+  }
+
+  // the groups' sums meet in LDS (lane: row l % 32 of the 32 x 32 tile; registers 4 g .. + 3: columns 8 g + 4 (l / 32) ..)
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    *reinterpret_cast<f32x4*>(buf + (size_t)(q * C::BM + wm * 32 + l32) * C::LdR + wn * 32 + g * 8 + lh * 4) =
+        f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+  __syncthreads();
+  const int nc = tid % C::BN, r0 = tid / C::BN, n = n0 + nc;
+  constexpr int kStep = C::T / C::BN;
+  const int ns = n < d2 ? n : d2 - 1;
+  const float bv = bias ? Elem<T>::load(bias, ns) : 0.f;
+  float val[C::Outs];
+#pragma unroll
+  for (int i = 0; i < C::Outs; ++i) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < C::KQ; ++k) v += buf[(size_t)(k * C::BM + r0 + i * kStep) * C::LdR + nc];
+    val[i] = v + bv;
+  }
+
+  // LoRA expand, 32 ranks at a time, eight rows of W^B on their way
+  const int most = s_most;
+  float* const ts = buf + C::TsOff;
+  for (int c0 = 0; c0 < most; c0 += 32) {
+    for (int e = tid; e < C::BM * 32; e += C::T) {
+      const int row = e >> 5, c = c0 + (e & 31);
+      ts[e] = c < s_rank[row] ? t[(size_t)(m0 + row) * ad.r_max + c] : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < C::Outs; ++i) {
+      const int row = r0 + i * kStep, r = s_rank[row];
+      if (r <= c0) continue;
+      const T* const Bm = (const T*)ad.B[s_ten[row] * MILORA_NUM_SITES + site] + ns;
+      float delta = 0.f;
+      for (int c1 = 0; c1 < 32 && c0 + c1 < r; c1 += 8) {
+        float b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = Elem<T>::load(Bm, (size_t)(c0 + c1 + u < r ? c0 + c1 + u : r - 1) * d2);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) delta += c0 + c1 + u < r ? ts[row * 32 + c1 + u] * b[u] : 0.f;
+      }
+      val[i] += delta;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < C::Outs; ++i) {
+    const int64_t m = m0 + r0 + i * kStep;
+    if (m < M && n < d2) Elem<T>::store(Y, (size_t)m * d2 + n, val[i]);
+  }
+}
+
+template <typename T, class C>
+int launch_tile(const void* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const void* W, const void* bias,
+                const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route, int B, const float* t, void* Y,
+                hipStream_t stream) {
+  static thread_local int lds_set_for = -1;
+  int dev = 0;
+  MILORA_HIP(hipGetDevice(&dev));
+  if (lds_set_for != dev) {
+    MILORA_HIP(hipFuncSetAttribute((const void*)linear_tile_kernel<T, C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LdsBytes));
+    lds_set_for = dev;
+  }
+  dim3 grid((unsigned)((d2 + C::BN - 1) / C::BN), (unsigned)((M + C::BM - 1) / C::BM));
+  hipLaunchKernelGGL((linear_tile_kernel<T, C>), grid, dim3(C::T), C::LdsBytes, stream, (const T*)X, M, d1, d2, row_to_req,
+                     (const T*)W, (const T*)bias, ad, site, tenant_id, route, B, t, (T*)Y);
+  return check_launch();
 }
 
 }  // namespace
 
-int launch_shrink(const void* X, int64_t M, int d1, int dtype, const int32_t* row_to_req, const AdapterView& ad,
-                  int site, const int32_t* tenant_id, const uint8_t* route, int B, float* t, hipStream_t stream) {
+int launch_shrink(const void* X, int64_t ldx, int64_t M, int d1, int dtype, const int32_t* row_to_req, const AdapterView& ad,
+                  int site, int sites, const int32_t* tenant_id, const uint8_t* route, int B, float* t, hipStream_t stream) {
   if (dtype == MILORA_BF16)
-    hipLaunchKernelGGL((shrink_rows_kernel<bf16_t>), dim3((unsigned)M), dim3(kThreads), 0, stream, (const bf16_t*)X, M,
-                       d1, row_to_req, ad, site, tenant_id, route, B, t);
+    hipLaunchKernelGGL((shrink_rows_kernel<bf16_t>), dim3((unsigned)M, sites), dim3(kShrinkT), 0, stream, (const bf16_t*)X,
+                       ldx, M, d1, row_to_req, ad, site, tenant_id, route, B, t);
   else
-    hipLaunchKernelGGL((shrink_rows_kernel<float>), dim3((unsigned)M), dim3(kThreads), 0, stream, (const float*)X, M,
-                       d1, row_to_req, ad, site, tenant_id, route, B, t);
+    hipLaunchKernelGGL((shrink_rows_kernel<float>), dim3((unsigned)M, sites), dim3(kShrinkT), 0, stream, (const float*)X, ldx,
+                       M, d1, row_to_req, ad, site, tenant_id, route, B, t);
   return check_launch();
+}
+
+template <typename T>
+static int launch_few_rows_t(const FewArgs& g, int sites, int mode, hipStream_t st) {
+  const dim3 grid((unsigned)((g.d2 + 15) / 16), (unsigned)sites);
+  switch (mode) {
+    case kFewPlain: hipLaunchKernelGGL((few_rows_kernel<T, kFewPlain>), grid, dim3(kFewT), 0, st, g); break;
+    case kFewResid: hipLaunchKernelGGL((few_rows_kernel<T, kFewResid>), grid, dim3(kFewT), 0, st, g); break;
+    case kFewGateUp: hipLaunchKernelGGL((few_rows_kernel<T, kFewGateUp>), dim3(grid.x), dim3(kFewT), 0, st, g); break;
+    default: hipLaunchKernelGGL((few_rows_kernel<T, kFewDown>), grid, dim3(kFewT), 0, st, g); break;
+  }
+  return check_launch();
+}
+
+int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t st) {
+  FewArgs g = args;
+  g.t = nullptr;
+  if (g.ad.r_max > kFuseRank) {
+    const int rc = launch_shrink(g.X, g.ldx, g.M, g.d1, dtype, g.row_to_req, g.ad, g.site[0], sites, g.tenant_id, g.route, g.B, t, st);
+    if (rc) return rc;
+    g.t = t;
+  }
+  return dtype == MILORA_BF16 ? launch_few_rows_t<bf16_t>(g, sites, mode, st) : launch_few_rows_t<float>(g, sites, mode, st);
 }
 
 int launch_linear_generic(const void* X, int64_t M, int d1, int d2, int dtype, const int32_t* row_to_req,
                           const void* W, const void* bias, const AdapterView& ad, int site,
-                          const int32_t* tenant_id, const uint8_t* route, int B, const float* t, void* Y,
-                          hipStream_t stream) {
-  dim3 grid((unsigned)((d2 + 63) / 64), (unsigned)((M + 63) / 64));
-  if (grid.y > 65535) return MILORA_ERANGE;
-  if (dtype == MILORA_BF16)
-    hipLaunchKernelGGL((linear_tile_kernel<bf16_t>), grid, dim3(kThreads), 0, stream, (const bf16_t*)X, M, d1, d2,
-                       row_to_req, (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B, t,
-                       (bf16_t*)Y);
-  else
-    hipLaunchKernelGGL((linear_tile_kernel<float>), grid, dim3(kThreads), 0, stream, (const float*)X, M, d1, d2,
-                       row_to_req, (const float*)W, (const float*)bias, ad, site, tenant_id, route, B, t, (float*)Y);
-  return check_launch();
+                          const int32_t* tenant_id, const uint8_t* route, int B, float* t, void* Y, hipStream_t stream) {
+  if ((M + 63) / 64 > 65535) return MILORA_ERANGE;
+  if (M <= kFewRows) {
+    FewArgs g{};
+    g.X = X; g.ldx = d1; g.M = (int)M; g.d1 = d1; g.d2 = d2;
+    g.W[0] = W; g.bias = bias; g.Y[0] = Y; g.ldy = d2; g.site[0] = site;
+    g.row_to_req = row_to_req; g.tenant_id = tenant_id; g.route = route; g.B = B; g.ad = ad;
+    return launch_few_rows(g, dtype, 1, kFewPlain, t, stream);
+  }
+  const int rc = launch_shrink(X, d1, M, d1, dtype, row_to_req, ad, site, 1, tenant_id, route, B, t, stream);
+  if (rc) return rc;
+  const int64_t large = ((M + 63) / 64) * (int64_t)((d2 + 63) / 64);
+#define MILORA_TILE(T, C) launch_tile<T, C>(X, M, d1, d2, row_to_req, W, bias, ad, site, tenant_id, route, B, t, Y, stream)
+  if (large >= kGenLargeTiles) return dtype == MILORA_BF16 ? MILORA_TILE(bf16_t, GenLarge) : MILORA_TILE(float, GenLarge);
+  return dtype == MILORA_BF16 ? MILORA_TILE(bf16_t, GenSmall) : MILORA_TILE(float, GenSmall);
+#undef MILORA_TILE
 }
 
 }  // namespace milora

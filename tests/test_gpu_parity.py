@@ -525,6 +525,35 @@ def test_layer_decode_generic_fp32(rmsnorm, with_attn):
     _layer_case(wl, rmsnorm, mb.W_ROWMAJOR, with_attn)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,d,F,site,ranks", [
+    (1, 3, 5, 4, (1,)),            # less than one piece of four k, less than one block of columns
+    (16, 67, 33, 6, (16,)),        # the last ranks formed inside the few-row launch, a reduction with one odd k
+    (16, 130, 515, 5, (17, 100)),  # ranks formed beforehand
+    (17, 127, 129, 4, (3, 256)),   # the first row count of the tiles, one k short of a stage
+    (33, 257, 70, 6, (40,)),       # one k past a stage, a ragged column tile
+    (513, 65, 1030, 5, (8, 33)),   # the larger tiles, one row past a tile, one k past a stage
+])
+def test_routed_linear_any_shape_edges(dtype, M, d, F, site, ranks):
+    """The fp32 matrix-core kernels at the edges of their row counts, tiles, stages and rank pieces."""
+    wl = small(dtype=dtype, d=d, F=F, T=3, B=min(M, 9), ranks=ranks, tenants="uniform", seed=M + d)
+    g = torch.Generator().manual_seed(M)
+    r2r = torch.sort(torch.randint(0, wl.B, (M,), generator=g))[0]
+    Y, ref = _linear_case(wl, site, M=M, row_to_req=r2r, with_bias=(M % 2 == 1), seed=site)
+    assert_rows_close(Y, ref, wl.torch_dtype)
+
+
+@pytest.mark.parametrize("dtype,B,ranks,top_k", [("f32", 16, (5, 16), 3), ("f32", 17, (5, 16), 1), ("f32", 3, (24,), 3),
+                                                 ("bf16", 16, (5, 24), 1), ("bf16", 1, (8,), 2)])
+@pytest.mark.parametrize("rmsnorm,with_attn", [(False, False), (True, True)])
+def test_layer_decode_rowmajor_few_rows(dtype, B, ranks, top_k, rmsnorm, with_attn):
+    """The launches with the layer's glue in their stores, at their last row count and one past it (that no LoRA term gets
+    lost is the fp32 cases' to show: at rank 5 and bf16's tolerance a single term is not visible through the layer)."""
+    wl = small(dtype=dtype, d=210, F=333, T=4, B=B, ranks=ranks, tenants="uniform", seed=500 + B)
+    route = _route_sets(B, top_k, B) if top_k > 1 else None
+    _layer_case(wl, rmsnorm, mb.W_ROWMAJOR, with_attn=with_attn, route=route, visible=VISIBLE if dtype == "f32" else 0)
+
+
 @pytest.mark.parametrize("B", [4, 16, 32, 48, 64, 128])
 @pytest.mark.parametrize("rmsnorm", [False, True])
 def test_layer_decode_packed_bf16(B, rmsnorm):

@@ -253,37 +253,59 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
     if (cur == 0x7fffffff) break;
     const int r = p.ad.rank[cur];
     gbf16* Bm = in_global(p.ad.B[cur * MILORA_NUM_SITES + p.site]);
-    const int n = n0 + tid;
-    // thread tid fills row tid of the X side and row tid of the W side
-    const uint32_t rb = (uint32_t)(tid & 15);
-    const uint32_t blk = (uint32_t)(tid >> 7) * kHalfBytes + (uint32_t)((tid >> 4) & 7) * kBlockBytes + rb * 128;
     for (int c0 = 0; c0 < r; c0 += 32) {
+      int tb = tid;  // opaque: addresses formed from it stay inside the loop instead of being spilled in front of it
+      asm volatile("" : "+v"(tb));
+      const int n = n0 + tb;
+      // thread tid fills row tid of the X side and row tb of the W side
+      const uint32_t rb = (uint32_t)(tb & 15);
+      const uint32_t blk = (uint32_t)(tb >> 7) * kHalfBytes + (uint32_t)((tb >> 4) & 7) * kBlockBytes + rb * 128;
+      // this column's 32 values of W^B: asked for first, used last
+      uint16_t bv[32];
+#pragma unroll
+      for (int c = 0; c < 32; ++c) bv[c] = Bm[(size_t)(c0 + c < r ? c0 + c : r - 1) * p.d2 + (n < p.d2 ? n : p.d2 - 1)];
       // t of the tile's 256 rows for these 32 ranks, the shrink's parts added in part order, through LDS: eight
       // lanes read the 128 bytes of a row (whole lines), then every thread picks up its own row
       float* const ts = reinterpret_cast<float*>(lds + 2 * kHalfBytes + 1024);  // [256][33]
-      const bool vec = (p.ad.r_max & 3) == 0;
+      const int cq = c0 + (tb & 7) * 4;
+      const bool vec = (p.ad.r_max & 3) == 0 && cq + 3 < p.ad.r_max;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int row = (tid >> 3) + 32 * i, cq = c0 + (tid & 7) * 4;
-        const int64_t mr = m0 + row;
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        if (mr < p.M) {
-          const float* q = p.t + (size_t)mr * p.ad.r_max + cq;
-          if (vec && cq + 3 < p.ad.r_max) {
-#pragma unroll 1
-            for (int part = 0; part < p.parts; ++part) {
-              const f32x4 x = *reinterpret_cast<const f32x4*>(q + part * p.t_stride);
+      for (int i0 = 0; i0 < 8; i0 += 4) {
+        f32x4 v[4];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] += x[e];
-            }
-          } else {
+        for (int i = 0; i < 4; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const float* q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t mr = m0 + (tb >> 3) + 32 * (i0 + i);
+          q[i] = p.t + (size_t)(mr < p.M ? mr : p.M - 1) * p.ad.r_max + cq;
+        }
+        if (vec) {
+          for (int k0 = 0; k0 < p.parts; k0 += 4) {  // four rows and four parts in flight
+            f32x4 x[4][4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                x[k][i] = *reinterpret_cast<const f32x4*>(q[i] + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (k0 + k < p.parts)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] += x[k][i];
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
             for (int e = 0; e < 4; ++e)
               if (cq + e < p.ad.r_max)
-                for (int part = 0; part < p.parts; ++part) v[e] += q[part * p.t_stride + e];
-          }
+                for (int part = 0; part < p.parts; ++part) v[i][e] += q[i][part * p.t_stride + e];
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ts[row * 33 + (tid & 7) * 4 + e] = v[e];
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ts[((tb >> 3) + 32 * (i0 + i)) * 33 + (tb & 7) * 4 + e] = v[i][e];
       }
       __syncthreads();
 #pragma unroll
@@ -296,8 +318,8 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const int c = c0 + g * 8 + e * 2 + h;
-            tv[h] = (my_ten == cur && c < r) ? ts[tid * 33 + (c - c0)] : 0.f;
-            bw[h] = (c < r && n < p.d2) ? (uint32_t)Bm[(size_t)c * p.d2 + n] : 0u;
+            tv[h] = (my_ten == cur && c < r) ? ts[tb * 33 + (c - c0)] : 0.f;
+            bw[h] = (c < r && n < p.d2) ? (uint32_t)bv[g * 8 + e * 2 + h] : 0u;
           }
           const bf16_t h0b = f32_to_bf16(tv[0]), h1b = f32_to_bf16(tv[1]);
           hi[e] = (uint32_t)h0b | ((uint32_t)h1b << 16);
@@ -348,7 +370,7 @@ template <int RT>
 __global__ void __launch_bounds__(512, 4) shrink_tiles_kernel(const ShrinkArgs g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[8 * kShrinkWaveBytes];
   __shared__ int row_ten[RT * 16];
-  shrink_block<RT, 8>(g, blockIdx.x, blockIdx.y, gridDim.y, smem, row_ten, [](float* p, float v) { *p = v; });
+  shrink_block<RT, 8>(g, blockIdx.x, blockIdx.y, gridDim.y, blockIdx.z, gridDim.z, smem, row_ten, [](float* p, float v) { *p = v; });
 }
 
 }  // namespace
@@ -414,8 +436,14 @@ int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_t
   for (int64_t r0 = 0; r0 < M; r0 += slice) {
     ShrinkArgs g{X + (size_t)r0 * d1, M - r0 < slice ? M - r0 : slice, r0, d1, site, B, row_to_req ? row_to_req + r0 : nullptr,
                  tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max};
-    if (M <= kTileMaxRows)
-      hipLaunchKernelGGL((shrink_tiles_kernel<1>), dim3((unsigned)((g.M + 15) / 16), parts), dim3(512), 0, stream, g);
+    if (M <= kTileMaxRows) {
+      // up to four workgroups share the units of a block while all of them are resident at once (two per compute unit; beams,
+      // 96 rows of 24 requests: 13.6 us a launch with one, 7.4 with four)
+      const int64_t blocks = (g.M + 15) / 16;
+      int shares = 1;
+      while (shares < 4 && blocks * parts * shares * 2 <= 512) shares *= 2;
+      hipLaunchKernelGGL((shrink_tiles_kernel<1>), dim3((unsigned)blocks, parts, shares), dim3(512), 0, stream, g);
+    }
     else
       hipLaunchKernelGGL((shrink_tiles_kernel<4>), dim3((unsigned)((g.M + 63) / 64), parts), dim3(512), 0, stream, g);
     const int rc = check_launch();

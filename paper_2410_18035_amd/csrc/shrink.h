@@ -6,7 +6,8 @@
 // want 8 consecutive reduction indices per lane: a lane loads eight 16-byte pieces (8 ranks at 8 consecutive k), turns
 // the 8 x 8 block with byte permutes and puts it into the wave's own LDS as [rank][k].  X rows come straight from
 // global memory as operands.  Rows of several tenants are computed once per tenant and each row keeps its own tenant's
-// result.  Needs d1 % 32 == 0.
+// result; where workgroups are few, the block's units (32 ranks of a tenant) are dealt to several of them: a unit is a chain
+// of table, W^A and LDS round trips, about 3 us.  Needs d1 % 32 == 0.
 #pragma once
 #include "common.h"
 
@@ -66,8 +67,8 @@ __device__ __forceinline__ u32x4 load8(gbf16* p, int left, bool vec) {
 
 // STORE(float* p, float v) stores one element of t.  `smem`: NW * kShrinkWaveBytes, `row_ten`: 16 * RT ints.
 template <int RT, int NW, class STORE>
-__device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block, int part, int parts, unsigned char* smem,
-                                             int* row_ten, STORE store) {
+__device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block, int part, int parts, int share, int shares,
+                                             unsigned char* smem, int* row_ten, STORE store) {
   constexpr int kRows = RT * 16;
   static_assert(kRows * kShrinkC * 4 <= kShrinkWaveBytes, "sums of a wave");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -95,7 +96,7 @@ __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block,
     m = m < g.M ? m : g.M - 1;
     xp[rt] = g.X + (size_t)m * g.d1 + (lane >> 4) * 8;
   }
-  int last = -1;
+  int last = -1, unit = 0;  // (unit % shares)
   for (;;) {
     int cur = my_ten > last ? my_ten : 0x7fffffff;
 #pragma unroll
@@ -110,6 +111,9 @@ __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block,
     gbf16* A = in_global(g.ad.A[cur * MILORA_NUM_SITES + g.site]);
     const bool vec = (r & 7) == 0 && ((uintptr_t)A & 15) == 0;
     for (int cb = 0; cb < r; cb += kShrinkC) {
+      const bool ours = unit == share;
+      unit = unit + 1 == shares ? 0 : unit + 1;
+      if (!ours) continue;
       const int rc = r - cb < kShrinkC ? r - cb : kShrinkC;
       const int groups = (rc + 7) >> 3, ntile = (rc + 15) >> 4;
       f32x4 acc[RT][2];

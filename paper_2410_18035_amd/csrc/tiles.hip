@@ -18,8 +18,8 @@
 //
 // Bound: few rows, the stream of the weights (a 4096 x 11008 linear at 45 rows: 23 us = 3.9 TB/s); from some hundred rows on
 // the copies through the L2 (0.58 us per 128 x 128 x 64 stage and compute unit, 56 GB/s each).  The seven linears of the 7B
-// layer: 45 rows 4940 us with the any-shape kernel, 160 us here; 777 rows 966 us with 256 x 256 tiles only, 517 us;
-// packed weights, 96 rows, three sites a request: 495 us with the stream kernel of decode.hip, 350 us.
+// layer: 45 rows 4940 us with the any-shape kernel, 160 us here; 777 rows 966 us with 256 x 256 tiles only, 500 us;
+// packed weights, 96 rows, three sites a request: 495 us with the stream kernel of decode.hip, 272 us.
 #include "shrink.h"
 #include "tiles.h"
 
@@ -27,6 +27,8 @@ namespace milora {
 namespace {
 
 typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef __attribute__((address_space(1))) const u32x4_a2 gu32x4_a2;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kT = 512;        // threads: eight waves
@@ -223,7 +225,8 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   __syncthreads();
 
   // ---- LoRA term of the routed rows (by the workgroup of the last part): more stages of 64 k -----------------------
-  // A stage takes four groups of 8 ranks.  t = X W^A (fp32) enters as bf16 hi + lo, hi against the groups' rows of W^B in
+  // A stage takes four groups of 8 ranks, and as many stages as the ring holds are filled together (one round trip for t and
+  // W^B instead of one per stage; packed 96 rows of 24 requests, three sites each: 27.4 -> 22.3 us a call on 4096 x 4096).  t = X W^A (fp32) enters as bf16 hi + lo, hi against the groups' rows of W^B in
   // the first 32 k, lo against the same rows in the second.  Consecutive rows of one tenant are a run; a run's ranks get
   // groups of their own, in which the other rows of the tile are zero, so tenants share stages.
   bool lora = false;
@@ -262,30 +265,31 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
       __syncthreads();
       n_groups = ctl[0];
       const int g1 = n_groups < g0 + kMaxGroups ? n_groups : g0 + kMaxGroups;
-      // X side: (row, group of the stage) by thread; W side: (8 columns, group) by threads of the last wave
-      constexpr int kXUnits = C::BM * 4, kWUnits = C::BN / 8 * 4;
-      static_assert(kXUnits <= kT && kWUnits <= 64, "one piece per thread");
-      const int xr = tid >> 2, xg = tid & 3;
-      const bool has_x = tid < kXUnits;
-      const int my_ten = has_x ? row_ten[xr] : -1, my_first = has_x ? row_group[xr] : 0, my_rank = has_x ? row_rank[xr] : 0;
-      const int wg = lane & 3, wc = (lane >> 2) * 8;
-      for (int s0 = g0; s0 < g1; s0 += 4) {
-        float tv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) tv[e] = 0.f;
-        const int c0 = (s0 + xg - my_first) * 8;
-        if (my_ten >= 0 && c0 >= 0 && c0 < my_rank) {
+      // X side: a row's groups by kRowT threads; W side: (8 columns, group) by thread
+      constexpr int kBatch = C::NS * 4, kRowT = kT / C::BM, kPieces = C::BN / 8;
+      static_assert(kPieces * kBatch <= kT && kT % C::BM == 0, "one piece of W^B per thread");
+      for (int s0 = g0; s0 < g1; s0 += kBatch) {
+        int tb = tid;  // opaque: addresses formed from it stay inside the loop instead of being spilled in front of it
+        asm volatile("" : "+v"(tb));
+        const int xr = tb / kRowT;
+        const int my_first = row_group[xr], my_rank = row_ten[xr] >= 0 ? row_rank[xr] : 0;
+        const int wc = tb % kPieces * 8, wg = tb / kPieces;
+        const bool tvec = (p.ad.r_max & 3) == 0;
+        auto load_t = [&](int c0, float (&tv)[8]) __attribute__((always_inline)) {  // ranks c0 .. c0 + 7 of row xr
           const float* tp = p.t + (size_t)(m0 + xr) * p.ad.r_max + c0;
-          if ((p.ad.r_max & 3) == 0 && c0 + 8 <= my_rank) {
-            for (int k0 = 0; k0 < p.parts; k0 += 4) {  // four parts in flight
-              f32x4 v[2][4];
 #pragma unroll
-              for (int k = 0; k < 4; ++k)
+          for (int e = 0; e < 8; ++e) tv[e] = 0.f;
+          if (tvec && c0 + 8 <= my_rank) {
+            constexpr int kFly = C::OCC == 1 ? 4 : 2;  // parts in flight: registers of half a compute unit allow two
+            for (int k0 = 0; k0 < p.parts; k0 += kFly) {
+              f32x4 v[2][kFly];
+#pragma unroll
+              for (int k = 0; k < kFly; ++k)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                   v[h][k] = *reinterpret_cast<const f32x4*>(tp + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride + h * 4);
 #pragma unroll
-              for (int k = 0; k < 4; ++k)
+              for (int k = 0; k < kFly; ++k)
                 if (k0 + k < p.parts)
 #pragma unroll
                   for (int e = 0; e < 8; ++e) tv[e] += v[e >> 2][k][e & 3];
@@ -295,8 +299,8 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
               if (c0 + e < my_rank)
                 for (int k = 0; k < p.parts; ++k) tv[e] += tp[k * p.t_stride + e];
           }
-        }
-        if (has_x) {
+        };
+        auto put_t = [&](int group, const float (&tv)[8]) __attribute__((always_inline)) {  // group of the batch
           u32x4 hi, lo;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -304,37 +308,62 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
             hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
             lo[e] = pack_bf16x2(tv[2 * e] - bf16_to_f32(h0), tv[2 * e + 1] - bf16_to_f32(h1));
           }
-          *reinterpret_cast<u32x4*>(ring + xr * 128 + ((xg ^ swz(xr & 15)) << 4)) = hi;
-          *reinterpret_cast<u32x4*>(ring + xr * 128 + (((xg + 4) ^ swz(xr & 15)) << 4)) = lo;
+          unsigned char* const row = ring + (group >> 2) * C::StageBytes + xr * 128;
+          *reinterpret_cast<u32x4*>(row + (((group & 3) ^ swz(xr & 15)) << 4)) = hi;
+          *reinterpret_cast<u32x4*>(row + ((((group & 3) + 4) ^ swz(xr & 15)) << 4)) = lo;
+        };
+        const int stages = ((g1 - s0 < kBatch ? g1 - s0 : kBatch) + 3) >> 2;
+        // this thread's groups of the row in this batch: k, k + kRowT, ... < k_end (counted from the row's first)
+        const int off = s0 - my_first, end = g1 - my_first < off + kBatch ? g1 - my_first : off + kBatch;
+        const int ng = (my_rank + 7) >> 3, k_end = end < ng ? end : ng;
+        int k = (off > 0 ? off : 0) + tb % kRowT;
+        float tv[8];
+        const bool has = k < k_end;
+        u32x4 a[8];
+        const bool wput = wg < stages * 4;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = u32x4{0u, 0u, 0u, 0u};
+        if (wput && s0 + wg < g1 && wc < cols) {
+          const int2 gr = groups[s0 + wg - g0];
+          const int r = p.ad.rank[gr.x];
+          gbf16* b = in_global(p.ad.B[gr.x * MILORA_NUM_SITES + p.site]) + n0 + wc;
+          // (whole pieces of 8 columns, d2 % 16 == 0, at whatever alignment the adapter has: one load each)
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (gr.y + i < r) a[i] = *(gu32x4_a2*)(b + (size_t)(gr.y + i) * p.d2);
         }
-        if (w == 7 && lane < kWUnits) {
-          u32x4 a[8], at[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) a[i] = u32x4{0u, 0u, 0u, 0u};
-          if (s0 + wg < g1 && wc < cols) {
-            const int2 gr = groups[s0 + wg - g0];
-            const int r = p.ad.rank[gr.x];
-            gbf16* b = in_global(p.ad.B[gr.x * MILORA_NUM_SITES + p.site]) + n0 + wc;
-            const bool vec = ((uintptr_t)b & 15) == 0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-              if (gr.y + i < r) a[i] = load8(b + (size_t)(gr.y + i) * p.d2, 8, vec);
-          }
+        auto put_w = [&]() __attribute__((always_inline)) {
+          u32x4 at[8];
           transpose8(a, at);
+          unsigned char* const wst = ring + (wg >> 2) * C::StageBytes + C::BM * 128;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const int n = wc + j;
-            *reinterpret_cast<u32x4*>(ring + C::BM * 128 + n * 128 + ((wg ^ swz(n & 15)) << 4)) = at[j];
-            *reinterpret_cast<u32x4*>(ring + C::BM * 128 + n * 128 + (((wg + 4) ^ swz(n & 15)) << 4)) = at[j];
+            *reinterpret_cast<u32x4*>(wst + n * 128 + (((wg & 3) ^ swz(n & 15)) << 4)) = at[j];
+            *reinterpret_cast<u32x4*>(wst + n * 128 + ((((wg & 3) + 4) ^ swz(n & 15)) << 4)) = at[j];
           }
-        }
+        };
+        // (two workgroups share a compute unit's registers: W^B and t one after the other)
+        if (C::OCC > 1 && wput) put_w();
+        if (C::OCC > 1) __builtin_amdgcn_sched_barrier(0);
+        if (has) load_t(k * 8, tv);
+        for (int e = tb; e < stages * C::BM * 8; e += kT)
+          *reinterpret_cast<u32x4*>(ring + e / (C::BM * 8) * C::StageBytes + e % (C::BM * 8) * 16) = u32x4{0u, 0u, 0u, 0u};
         __syncthreads();
-#pragma unroll
-        for (int s = 0; s < C::KS; ++s) {
-          const int ks = q * C::KS + s;
-          const int n = wn * (C::BN / C::WNC) + l32;
-          mma(ring, xrd[s], C::BM * 128 + n * 128 + (((2 * ks + lh) ^ swz(l32 & 15)) << 4));
+        if (has) put_t(k - off, tv);
+        for (k += kRowT; k < k_end; k += kRowT) {
+          load_t(k * 8, tv);
+          put_t(k - off, tv);
         }
+        if (C::OCC == 1 && wput) put_w();
+        __syncthreads();
+        for (int st = 0; st < stages; ++st)
+#pragma unroll
+          for (int s = 0; s < C::KS; ++s) {
+            const int ks = q * C::KS + s;
+            const int n = wn * (C::BN / C::WNC) + l32;
+            mma(ring + st * C::StageBytes, xrd[s], C::BM * 128 + n * 128 + (((2 * ks + lh) ^ swz(l32 & 15)) << 4));
+          }
         __syncthreads();
       }
       if (g1 == n_groups) break;

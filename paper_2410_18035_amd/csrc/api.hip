@@ -1,6 +1,6 @@
 // C ABI of the routed-LoRA library: argument validation, workspace carving and dispatch between
-// the matrix-core decode path (bf16, packed weights), the matrix-core prefill path (bf16,
-// row-major weights, many rows) and the any-shape path (fp32 and everything else).
+// the decode kernels (bf16, packed weights), the matrix-core tiles (bf16, row-major weights or packed ones
+// of many rows) and the any-shape path (fp32 and everything else).
 #include "tiles.h"
 
 namespace milora {

@@ -265,7 +265,14 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
 
 // ---- more rows ------------------------------------------------------------------------------------------------------
 // A workgroup of eight waves computes a BM x BN tile: KQ groups of waves share a stage's k, the waves of a group the tile,
-// 32 x 32 each (v_mfma_f32_32x32x2_f32).  Stages go through registers (two on their way) into one of two LDS buffers.
+// 32 x 32 each (v_mfma_f32_32x32x2_f32).  Stages go through registers (four on their way) into one of two LDS buffers.
+// WIDE (d1 >= 4): every load is four elements without a branch, a row's end read from its last four and shifted when it
+// is stored (a branch around the loads makes the compiler wait for all of them at each store: 28.9 us a call of 300 rows on
+// 1000 x 2730 without LoRA rows against 27.5 us).
+// Bound: the matrix instructions (13.7 us of that call) and the chain of look-ups, t and W^B behind them (10 us where rows
+// carry a LoRA term).  Seven fp32 linears of 300 rows, 1000 x 2730: 1757 us with vector FMA out of single-buffered tiles,
+// 190 us here.  64 x 64 tiles where they are at least half the compute units, 32 x 32 with the reduction over eight waves
+// below (300 rows on 1000 x 1000: 17.6 us).
 template <int BM_, int BN_, int KW_>
 struct GenCfg {
   static constexpr int BM = BM_, BN = BN_, KW = KW_;                 // KW: k of a stage per wave
@@ -284,7 +291,7 @@ typedef GenCfg<32, 32, 16> GenSmall;
 typedef GenCfg<64, 64, 32> GenLarge;
 constexpr int kGenLargeTiles = 128;
 
-template <typename T, class C>
+template <typename T, class C, bool WIDE>
 __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restrict__ X, int64_t M, int d1, int d2,
                                                            const int32_t* __restrict__ row_to_req, const T* __restrict__ W,
                                                            const T* __restrict__ bias, AdapterView ad, int site,
@@ -315,15 +322,28 @@ __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restric
     dst[i] = row * C::Ld + kq;
   }
   const int stages = (d1 + C::SK - 1) / C::SK;
-  f32x4 ra[C::Items], rb[C::Items];
-  auto load = [&](int st, f32x4 (&r)[C::Items]) __attribute__((always_inline)) {
-    if (st < stages)
+  constexpr int kSets = 4;
+  f32x4 r[kSets][C::Items];
+  auto load = [&](int st, f32x4 (&v)[C::Items]) __attribute__((always_inline)) {
+    const int k = (st < stages ? st : stages - 1) * C::SK + kq;  // past the end: the last stage again, never stored
 #pragma unroll
-      for (int i = 0; i < C::Items; ++i) r[i] = load4_end(src[i], st * C::SK + kq, d1);
+    for (int i = 0; i < C::Items; ++i) v[i] = WIDE ? load4(src[i] + (k < d1 - 4 ? k : d1 - 4)) : load4_end(src[i], k, d1);
+    __builtin_amdgcn_sched_barrier(0);  // the sets in their order: the oldest can then be waited for alone
   };
-  auto store = [&](int b, const f32x4 (&r)[C::Items]) __attribute__((always_inline)) {
+  auto store = [&](int st, f32x4 (&r)[C::Items]) __attribute__((always_inline)) {
+    const int shift = st * C::SK + kq - (d1 - 4);  // k by which a load past d1 - 4 was moved back
+    if (WIDE && (st + 1) * C::SK > d1)
 #pragma unroll
-    for (int i = 0; i < C::Items; ++i) *reinterpret_cast<f32x4*>(buf + b * C::BufFloats + dst[i]) = r[i];
+      for (int i = 0; i < C::Items; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float v = shift <= 0 ? r[i][e] : 0.f;
+#pragma unroll
+          for (int h = 1; e + h < 4; ++h) v = shift == h ? r[i][e + h] : v;
+          r[i][e] = v;
+        }
+#pragma unroll
+    for (int i = 0; i < C::Items; ++i) *reinterpret_cast<f32x4*>(buf + (st & 1) * C::BufFloats + dst[i]) = r[i];
   };
   f32x16 acc;
 #pragma unroll
@@ -338,11 +358,11 @@ __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restric
       for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], x[e], acc, 0, 0, 0);
     }
   };
-  load(0, ra);
-  load(1, rb);
+#pragma unroll
+  for (int j = 0; j < kSets; ++j) load(j, r[j]);
   if (tid == 0) s_most = 0;
-  store(0, ra);
-  load(2, ra);
+  store(0, r[0]);
+  load(kSets, r[0]);
   __syncthreads();
   if (tid < C::BM) {  // which rows carry a LoRA term
     const int64_t m = m0 + tid;
@@ -355,16 +375,16 @@ __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restric
     s_ten[tid] = tenant;
     if (r) atomicMax(&s_most, r);
   }
-  for (int st = 0; st < stages; st += 2) {
-    compute(0);
-    if (st + 1 < stages) store(1, rb);
-    load(st + 3, rb);
-    __syncthreads();
-    if (st + 1 >= stages) break;
-    compute(1);
-    if (st + 2 < stages) store(0, ra);
-    load(st + 4, ra);
-    __syncthreads();
+  for (int s0 = 0; s0 < stages; s0 += kSets) {
+#pragma unroll
+    for (int j = 0; j < kSets; ++j) {
+      const int st = s0 + j;
+      if (st >= stages) break;
+      compute(j & 1);
+      if (st + 1 < stages) store(st + 1, r[(j + 1) % kSets]);
+      load(st + 1 + kSets, r[(j + 1) % kSets]);
+      __syncthreads();
+    }
   }
 
   // the groups' sums meet in LDS (lane: row l % 32 of the 32 x 32 tile; registers 4 g .. + 3: columns 8 g + 4 (l / 32) ..)
@@ -386,31 +406,41 @@ __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restric
     val[i] = v + bv;
   }
 
-  // LoRA expand, 32 ranks at a time, eight rows of W^B on their way
+  // LoRA expand, 32 ranks at a time; eight rows of W^B for all of a thread's outputs on their way together (one output after
+  // the other, each waited for its own loads: 43.4 us a call of 300 rows on 1000 x 2730 against 37.8 us)
   const int most = s_most;
   float* const ts = buf + C::TsOff;
-  for (int c0 = 0; c0 < most; c0 += 32) {
-    for (int e = tid; e < C::BM * 32; e += C::T) {
-      const int row = e >> 5, c = c0 + (e & 31);
-      ts[e] = c < s_rank[row] ? t[(size_t)(m0 + row) * ad.r_max + c] : 0.f;
-    }
-    __syncthreads();
+  if (most > 0) {
+    const T* Bm[C::Outs];
+    int last[C::Outs];
 #pragma unroll
     for (int i = 0; i < C::Outs; ++i) {
-      const int row = r0 + i * kStep, r = s_rank[row];
-      if (r <= c0) continue;
-      const T* const Bm = (const T*)ad.B[s_ten[row] * MILORA_NUM_SITES + site] + ns;
-      float delta = 0.f;
-      for (int c1 = 0; c1 < 32 && c0 + c1 < r; c1 += 8) {
-        float b[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) b[u] = Elem<T>::load(Bm, (size_t)(c0 + c1 + u < r ? c0 + c1 + u : r - 1) * d2);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) delta += c0 + c1 + u < r ? ts[row * 32 + c1 + u] * b[u] : 0.f;
-      }
-      val[i] += delta;
+      const int row = r0 + i * kStep;
+      last[i] = s_rank[row] - 1;
+      Bm[i] = last[i] >= 0 ? (const T*)ad.B[s_ten[row] * MILORA_NUM_SITES + site] + ns : nullptr;
     }
-    __syncthreads();
+    for (int c0 = 0; c0 < most; c0 += 32) {
+      for (int e = tid; e < C::BM * 32; e += C::T) {
+        const int row = e >> 5, c = c0 + (e & 31);
+        ts[e] = c < s_rank[row] ? t[(size_t)(m0 + row) * ad.r_max + c] : 0.f;
+      }
+      __syncthreads();
+      for (int c1 = 0; c1 < 32 && c0 + c1 < most; c1 += 8) {
+        float b[C::Outs][8];
+#pragma unroll
+        for (int i = 0; i < C::Outs; ++i)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int c = c0 + c1 + u;
+            b[i][u] = c <= last[i] ? Elem<T>::load(Bm[i], (size_t)c * d2) : 0.f;
+          }
+#pragma unroll
+        for (int i = 0; i < C::Outs; ++i)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) val[i] += ts[(r0 + i * kStep) * 32 + c1 + u] * b[i][u];
+      }
+      __syncthreads();
+    }
   }
 #pragma unroll
   for (int i = 0; i < C::Outs; ++i) {
@@ -419,7 +449,7 @@ __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restric
   }
 }
 
-template <typename T, class C>
+template <typename T, class C, bool WIDE>
 int launch_tile(const void* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const void* W, const void* bias,
                 const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route, int B, const float* t, void* Y,
                 hipStream_t stream) {
@@ -427,11 +457,11 @@ int launch_tile(const void* X, int64_t M, int d1, int d2, const int32_t* row_to_
   int dev = 0;
   MILORA_HIP(hipGetDevice(&dev));
   if (lds_set_for != dev) {
-    MILORA_HIP(hipFuncSetAttribute((const void*)linear_tile_kernel<T, C>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LdsBytes));
+    MILORA_HIP(hipFuncSetAttribute((const void*)linear_tile_kernel<T, C, WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LdsBytes));
     lds_set_for = dev;
   }
   dim3 grid((unsigned)((d2 + C::BN - 1) / C::BN), (unsigned)((M + C::BM - 1) / C::BM));
-  hipLaunchKernelGGL((linear_tile_kernel<T, C>), grid, dim3(C::T), C::LdsBytes, stream, (const T*)X, M, d1, d2, row_to_req,
+  hipLaunchKernelGGL((linear_tile_kernel<T, C, WIDE>), grid, dim3(C::T), C::LdsBytes, stream, (const T*)X, M, d1, d2, row_to_req,
                      (const T*)W, (const T*)bias, ad, site, tenant_id, route, B, t, (T*)Y);
   return check_launch();
 }
@@ -486,9 +516,12 @@ int launch_linear_generic(const void* X, int64_t M, int d1, int d2, int dtype, c
   const int rc = launch_shrink(X, d1, M, d1, dtype, row_to_req, ad, site, 1, tenant_id, route, B, t, stream);
   if (rc) return rc;
   const int64_t large = ((M + 63) / 64) * (int64_t)((d2 + 63) / 64);
-#define MILORA_TILE(T, C) launch_tile<T, C>(X, M, d1, d2, row_to_req, W, bias, ad, site, tenant_id, route, B, t, Y, stream)
-  if (large >= kGenLargeTiles) return dtype == MILORA_BF16 ? MILORA_TILE(bf16_t, GenLarge) : MILORA_TILE(float, GenLarge);
-  return dtype == MILORA_BF16 ? MILORA_TILE(bf16_t, GenSmall) : MILORA_TILE(float, GenSmall);
+#define MILORA_TILE(T, C, WIDE) \
+  launch_tile<T, C, WIDE>(X, M, d1, d2, row_to_req, W, bias, ad, site, tenant_id, route, B, t, Y, stream)
+  const bool bf = dtype == MILORA_BF16;
+  if (d1 < 4) return bf ? MILORA_TILE(bf16_t, GenLarge, false) : MILORA_TILE(float, GenLarge, false);
+  if (large >= kGenLargeTiles) return bf ? MILORA_TILE(bf16_t, GenLarge, true) : MILORA_TILE(float, GenLarge, true);
+  return bf ? MILORA_TILE(bf16_t, GenSmall, true) : MILORA_TILE(float, GenSmall, true);
 #undef MILORA_TILE
 }
 

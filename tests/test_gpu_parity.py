@@ -532,6 +532,7 @@ def test_layer_decode_generic_fp32(rmsnorm, with_attn):
     (16, 130, 515, 5, (17, 100)),  # ranks formed beforehand
     (17, 127, 129, 4, (3, 256)),   # the first row count of the tiles, one k short of a stage
     (33, 257, 70, 6, (40,)),       # one k past a stage, a ragged column tile
+    (20, 3, 65, 4, (2,)),          # the tiles with less than one piece of four k
     (513, 65, 1030, 5, (8, 33)),   # the larger tiles, one row past a tile, one k past a stage
 ])
 def test_routed_linear_any_shape_edges(dtype, M, d, F, site, ranks):

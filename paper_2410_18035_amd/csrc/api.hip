@@ -346,7 +346,7 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
           rc = routed_linear_prefill(x, mc, d1, d2, map, (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
                                      t, y, st);
         else
-          rc = routed_linear_tiles(x, mc, d1, d2, map, (const bf16_t*)W, packed, (const bf16_t*)bias, ad, site, tenant_id,
+          rc = routed_linear_tiles(x, mc, m0, d1, d2, map, (const bf16_t*)W, packed, (const bf16_t*)bias, ad, site, tenant_id,
                                    route, B, t + (size_t)m0 * ad.r_max, t_stride, parts, pl, cnt, partial, y, st);
         if (rc) return rc;
       }

@@ -24,7 +24,7 @@ constexpr int kTileCtrlOffset = kStreamCtrlBytes - kTileCtrlBytes;
 // `large`: the 256 x 256 kernel is a choice (row-major weights, 64 rows or more); M up to kTileMaxRows, else it is taken.
 TilePlan plan_tiles(int64_t M, int d1, int d2, bool large);
 bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y);
-int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
+int routed_linear_tiles(const bf16_t* X, int64_t M, int64_t row_base, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
                         const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
                         int B, const float* t, size_t t_stride, int parts, const TilePlan& pl, int* cnt, float* partial, bf16_t* Y, hipStream_t st);
 

@@ -66,7 +66,8 @@ struct TParams {
   const int32_t* tenant_id;
   const uint8_t* route;
   AdapterView ad;
-  int64_t M;
+  int64_t M;         // rows of this launch
+  int64_t row_base;  // index of its first row in the caller's matrix (requests of unmapped rows)
   int d1, d2, site, B;
   int tilesM, tilesN;
   int S, steps;    // parts of the reduction and stages (64 k) per part
@@ -197,7 +198,7 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
     int tenant = -1, r = 0;
     if (tid < rows) {
       const int64_t m = m0 + tid;
-      const int64_t req = p.row_to_req ? (int64_t)p.row_to_req[m] : m;
+      const int64_t req = p.row_to_req ? (int64_t)p.row_to_req[m] : p.row_base + m;
       r = (req >= 0 && req < p.B) ? routed_rank(p.ad, p.tenant_id, p.route, (int)req, p.B, p.site, &tenant) : 0;
     }
     row_ten[tid] = r ? tenant : -1;
@@ -512,12 +513,12 @@ bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, cons
   return (uint64_t)d1 * 128u * 2u < (1ull << 31);  // byte offsets inside a tile's lines
 }
 
-int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
+int routed_linear_tiles(const bf16_t* X, int64_t M, int64_t row_base, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
                         const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
                         int B, const float* t, size_t t_stride, int parts, const TilePlan& pl, int* cnt, float* partial, bf16_t* Y, hipStream_t st) {
   TParams p;
   p.X = X; p.W = W; p.bias = bias; p.Y = Y; p.t = t; p.t_stride = t_stride; p.parts = parts;
-  p.row_to_req = row_to_req; p.tenant_id = tenant_id; p.route = route; p.ad = ad; p.M = M; p.d1 = d1; p.d2 = d2;
+  p.row_to_req = row_to_req; p.tenant_id = tenant_id; p.route = route; p.ad = ad; p.M = M; p.row_base = row_base; p.d1 = d1; p.d2 = d2;
   p.site = site; p.B = B; p.tilesM = pl.tilesM; p.tilesN = pl.tilesN; p.S = pl.S; p.steps = pl.steps;
   p.partial = partial; p.cnt = cnt;
   if (pl.shape == kTiles128) return packed ? launch_tiles<CfgMid, true>(p, st) : launch_tiles<CfgMid, false>(p, st);

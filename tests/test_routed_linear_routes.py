@@ -1,0 +1,69 @@
+"""milora_routed_linear where its launches change hands: slices of rows, tenants that share a tile, workspaces that served
+other calls.  Host-side answers are checked on the CPU, results on the GPU against the fp64 oracle or fp64 torch."""
+import pytest
+import torch
+
+import oracle
+from paper_2410_18035_amd import binding as mb
+from paper_2410_18035_amd import synth
+from tests.util import assert_rows_close, oracle_adapters
+
+DEV = "cuda:0"
+gpu = pytest.mark.gpu
+
+
+def _adapters(T, d1, d2, ranks, sigma, seed, dtype=torch.bfloat16):
+    """Adapter matrices of T tenants for one linear of d1 x d2, the same at all seven sites."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, sigma, generator=g).to(dtype)
+    rank = [ranks[t % len(ranks)] for t in range(T)]
+    A = [[rnd(d1, r)] * 7 for r in rank]
+    B = [[rnd(r, d2)] * 7 for r in rank]
+    return A, B, rank
+
+
+@gpu
+def test_second_slice_of_unmapped_rows_keeps_its_requests():
+    """A row-major weight of 4 GiB is beyond the 256 x 256 kernel's offsets: its rows go in slices of 4096 through the smaller
+    tiles.  Without a row map, row m belongs to request m in every slice: the requests behind row 4096 have a tenant of their
+    own, those of the same place in the first slice no LoRA term."""
+    d1, d2, M = 1 << 18, 1 << 13, 4100
+    assert 2 * d1 * d2 >= 1 << 32
+    g = torch.Generator(device=DEV).manual_seed(5)
+    W = torch.empty(d2, d1, dtype=torch.bfloat16, device=DEV)
+    for n in range(0, d2, 512):
+        W[n:n + 512] = torch.empty(512, d1, dtype=torch.float32, device=DEV).normal_(0, d1 ** -0.5, generator=g)
+    X = torch.empty(M, d1, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    A, B, rank = _adapters(3, d1, d2, (8, 16), 0.03, 6)
+    tab = mb.AdapterTable.from_tensors(A, B, rank)
+    tid = torch.tensor([2 if m >= 4096 else m % 2 for m in range(M)], dtype=torch.int32)
+    route = torch.full((M,), 4, dtype=torch.uint8)
+    route[:4] = mb.ROUTE_NONE
+    Y = mb.milora_routed_linear(X, W, tab, 4, tid.to(DEV), route.to(DEV))
+    rows = [0, 1, 4, 5, 4094, 4095, 4096, 4097, 4099]
+    x = X[rows].double()
+    ref = torch.cat([x @ W[n:n + 512].double().T for n in range(0, d2, 512)], 1)
+    for i, m in enumerate(rows):
+        if route[m] == 4:
+            delta = (x[i] @ A[tid[m]][4].double()) @ B[tid[m]][4].double()
+            assert delta.abs().max() > 0.2 * ref[i].abs().max()  # a lost or foreign term shows
+            ref[i] += delta
+    assert_rows_close(Y[rows], ref.cpu().numpy(), torch.bfloat16)
+
+
+@gpu
+def test_slices_of_mapped_rows_on_packed_weights():
+    """Packed rows beyond 4096 go in slices of their own, the last of them ragged."""
+    wl = synth.Workload("s", "bf16", 96, 208, 1, 5, 9, (5, 16), (3, 40), tenants="uniform", seed=8, sigma_w=0.05, sigma_lora=0.15)
+    W, ad = synth.base_weights(wl, 0, DEV), synth.adapters(wl, 0, DEV)
+    tab = mb.AdapterTable.from_tensors(ad.A, ad.B, ad.rank)
+    g = torch.Generator().manual_seed(9)
+    M, site = 4096 + 33, 5
+    X = torch.randn(M, wl.d, generator=g).to(torch.bfloat16).to(DEV)
+    r2r = torch.randint(0, wl.B, (M,), generator=g).to(torch.int32)
+    tid, route = synth.tenant_ids(wl), torch.tensor([5, 5, 0, 5, 5, 2, 5, 255, 5], dtype=torch.uint8)
+    Y = mb.milora_routed_linear(X, mb.milora_pack_weight(W[site]), tab, site, tid.to(DEV), route.to(DEV), r2r.to(DEV),
+                                w_layout=mb.W_PACKED, d2=wl.F)
+    ref = oracle.routed_linear(synth.as_numpy(X), synth.as_numpy(W[site]), oracle_adapters(ad), site, tid.numpy(), route.numpy(),
+                               row_to_req=r2r.numpy())
+    assert_rows_close(Y, ref, torch.bfloat16)

@@ -159,7 +159,8 @@ int milora_route(const void *H, int64_t M_tok, int d, int dtype, const int32_t *
  *   adapters    host struct, see milora_adapters
  *   tenant_id   device [B] int32; route: device [B] uint8 (this layer's row of the route table)
  *   Y           device [M][d2], `dtype`
- *   workspace   device, milora_routed_linear_workspace_bytes(M, d1, d2, r_max) bytes
+ *   workspace   device, milora_routed_linear_workspace_bytes(M, d1, d2, r_max) bytes; the size never goes down when an
+ *               argument goes up, so one workspace sized for the largest call serves every smaller one
  * A row whose request index, tenant id or tenant rank is out of range gets the base term only.
  * Errors: EINVAL, ERANGE (r_max > MILORA_MAX_RANK), EUNSUPPORTED (packed layout with fp32, with
  * d1 % 32 != 0 or d2 % 16 != 0, or with X, W, bias or Y not 16-byte aligned), EWORKSPACE, EHIP.

@@ -265,18 +265,16 @@ extern "C" int milora_last_hip_error(void) { return g_last_hip_error; }
 
 extern "C" size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2, int r_max) {
   if (M < 1 || d1 < 1 || d2 < 1 || r_max < 1) return 0;
-  // control words, LoRA shrinks, partial tiles
-  size_t partial = 0;
-  for (int large = 0; large < 2; ++large) {
-    const size_t n = plan_tiles(M <= kTileMaxRows ? M : kTileMaxRows, d1, d2, large != 0).partial_bytes;
-    partial = n > partial ? n : partial;
-    // (a last slice of fewer rows)
-    const size_t rest = M > kTileMaxRows && M % kTileMaxRows ? plan_tiles(M % kTileMaxRows, d1, d2, large != 0).partial_bytes : 0;
-    partial = rest > partial ? rest : partial;
+  // Control words, LoRA shrinks, partial tiles.  What a call needs of the last two goes up and down with M (fewer rows are cut
+  // into more parts); a caller sizes once for the largest call, so each is bounded by something that no size lowers.
+  const size_t t_bytes = align_up(shrink_rows_bound(M, d1) * r_max * sizeof(float), 256);
+  const size_t tiles = kStreamCtrlBytes + t_bytes + partial_bytes_bound(M, d1, d2);
+  // (the stream kernel's space for swapped tiles belongs to calls of up to 32 rows only)
+  size_t packed = 0;
+  for (int most : {32, MILORA_MAX_DECODE_BATCH}) {
+    const size_t n = routed_linear_packed_workspace_bytes(M <= most ? (int)M : most, d1, d2, r_max);
+    packed = n > packed ? n : packed;
   }
-  const size_t tiles = kStreamCtrlBytes + align_up((size_t)M * r_max * sizeof(float) * shrink_parts(M, d1), 256) + partial;
-  const int mp = M <= MILORA_MAX_DECODE_BATCH ? (int)M : MILORA_MAX_DECODE_BATCH;
-  size_t packed = routed_linear_packed_workspace_bytes(mp, d1, d2, r_max);
   return tiles > packed ? tiles : packed;
 }
 

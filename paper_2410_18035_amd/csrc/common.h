@@ -157,6 +157,16 @@ inline int shrink_parts(int64_t M, int d1) {
   return parts;
 }
 
+// The most rows x parts over all calls of up to M rows and d1 inputs (a call of more than one part has at most 512 blocks x parts).
+inline size_t shrink_rows_bound(int64_t M, int d1) {
+  const int most = (d1 + 8 * kShrinkChunkK - 1) / (8 * kShrinkChunkK);
+  int parts = 1;
+  while (parts < 8 && parts * 2 <= most) parts *= 2;
+  const int64_t cut = M * parts, cap = 512 * (M <= kTileMaxRows ? 16 : 64);
+  const int64_t n = parts > 1 && cut < cap ? cut : cap;
+  return (size_t)(parts == 1 || n < M ? M : n);
+}
+
 // ---- internal entry points shared between translation units ------------------------------------
 // LoRA shrink in fp32: for every row m whose request is routed to site `site + i`, i < sites, t[i][m][0..r) = X[m] . A.
 // X has rows of ldx elements, t is [sites][M][r_max] floats; rows that carry no LoRA term are left untouched.

@@ -14,6 +14,7 @@ struct TilePlan {
   size_t partial_bytes;  // fp32 partial tiles in the workspace (0 when S == 1)
 };
 constexpr int kMaxSplitUnits = 512;  // tiles x parts of a launch that cuts its reduction
+constexpr int kMaxParts = 8;         // of one reduction
 // The first bytes of a routed linear's workspace belong to control words: those of the stream kernels (decode.hip), then the
 // part counters of the tile kernel, zero between launches.  Both keep their data behind them, so calls of any sizes and
 // either layout can follow one another on one workspace, and the status word can be asked for after either.
@@ -23,6 +24,8 @@ constexpr int kTileCtrlOffset = kStreamCtrlBytes - kTileCtrlBytes;
 
 // `large`: the 256 x 256 kernel is a choice (row-major weights, 64 rows or more); M up to kTileMaxRows, else it is taken.
 TilePlan plan_tiles(int64_t M, int d1, int d2, bool large);
+// The most partial_bytes over the plans of all calls of up to these sizes; never less for a larger size.
+size_t partial_bytes_bound(int64_t M, int d1, int d2);
 bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y);
 int routed_linear_tiles(const bf16_t* X, int64_t M, int64_t row_base, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
                         const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,

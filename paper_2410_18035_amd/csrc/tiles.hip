@@ -496,7 +496,7 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool large) {
     if (best.S > 1) best.partial_bytes = (size_t)(tm * tn) * best.S * side * side * sizeof(float);
   };
   if (M <= kTileMaxRows)
-    for (int S = 1; S <= 8; ++S) {
+    for (int S = 1; S <= kMaxParts; ++S) {
       offer(kTiles64, 64, 26, 200, S, 400 + 70 * S);
       offer(kTiles128, 128, 58, 400, S, 250 + 220 * S);
     }
@@ -505,6 +505,21 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool large) {
     offer(kTiles256, 256, 125 + 50 * (tiles < 256 ? tiles : 256) / 256, 800, 1, 0);
   }
   return best;
+}
+
+// A plan's own need rises and falls with the sizes (4096 x 4096: 12.6 MB at 300 rows, 16.8 at 512, none at 777); what bounds
+// every plan is the number of tiles, the parts of each and the units of a launch.
+size_t partial_bytes_bound(int64_t M, int d1, int d2) {
+  const int64_t KT = ((int64_t)d1 + 63) / 64, rows = M < kTileMaxRows ? M : kTileMaxRows;
+  const int64_t parts = KT < kMaxParts ? KT : kMaxParts;
+  if (parts < 2) return 0;
+  size_t bytes = 0;
+  for (int side = 64; side <= 128; side *= 2) {
+    const int64_t units = ((rows + side - 1) / side) * (((int64_t)d2 + side - 1) / side) * parts;
+    const size_t n = (size_t)(units < kMaxSplitUnits ? units : kMaxSplitUnits) * side * side * sizeof(float);
+    bytes = n > bytes ? n : bytes;
+  }
+  return bytes;
 }
 
 bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y) {

@@ -67,3 +67,21 @@ def test_slices_of_mapped_rows_on_packed_weights():
     ref = oracle.routed_linear(synth.as_numpy(X), synth.as_numpy(W[site]), oracle_adapters(ad), site, tid.numpy(), route.numpy(),
                                row_to_req=r2r.numpy())
     assert_rows_close(Y, ref, torch.bfloat16)
+
+
+def test_workspace_for_the_largest_call_serves_every_smaller_one():
+    """A caller sizes its workspace once: no fewer rows, narrower weights or smaller ranks may need more."""
+    size = mb.routed_linear_workspace_bytes
+    rows = [1, 16, 17, 32, 33, 63, 64, 65, 96, 128, 129, 255, 256, 257, 300, 512, 513, 777, 1024, 1025, 2048, 2049, 4095, 4096,
+            4097, 4160, 8192, 8193, 16384, 32768, 32769, 1 << 20]
+    widths = [1, 3, 16, 64, 96, 128, 1000, 1024, 1025, 2048, 2049, 4096, 4160, 8193, 11008, 13824, 100_000]
+    for r in (1, 5, 8, 64, 256):
+        for a in widths:
+            for b in widths:
+                assert all(x <= y for x, y in zip(*[[size(M, a, b, r) for M in rows][i:] for i in (0, 1)])), (a, b, r)
+        for M in (1, 45, 96, 300, 512, 4096, 5000):
+            for a in widths:
+                along = [size(M, a, b, r) for b in widths], [size(M, b, a, r) for b in widths]
+                assert all(x <= y for s in along for x, y in zip(s, s[1:])), (M, a, r)
+    for M in rows:
+        assert size(M, 4096, 4096, 8) <= size(M, 4096, 4096, 9) <= size(M, 4096, 4096, 64)

@@ -428,14 +428,14 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 }
 
 // LoRA shrink of the rows the tile kernel serves (same conditions as prefill_supported): t receives
-// shrink_parts(M, d1) partial results [part][M][r_max] that routed_linear_prefill adds in part order.
+// shrink_parts(M, d1) partial results [part][M][r_max], to be added in part order, row_info (or null) the rows' look-ups.
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
-                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, hipStream_t stream) {
+                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, RowLora* row_info, hipStream_t stream) {
   const int parts = shrink_parts(M, d1);
   const int64_t slice = (int64_t)1 << 30;  // rows per launch: the grid index stays well inside 32 bits
   for (int64_t r0 = 0; r0 < M; r0 += slice) {
     ShrinkArgs g{X + (size_t)r0 * d1, M - r0 < slice ? M - r0 : slice, r0, d1, site, B, row_to_req ? row_to_req + r0 : nullptr,
-                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max};
+                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max, row_info ? row_info + r0 : nullptr};
     if (M <= kTileMaxRows) {
       // up to four workgroups share the units of a block while all of them are resident at once (two per compute unit; beams,
       // 96 rows of 24 requests: 13.6 us a launch with one, 7.4 with four)

@@ -35,6 +35,7 @@ struct ShrinkArgs {
   AdapterView ad;
   float* t;        // [part][M][r_max]
   size_t t_stride;
+  RowLora* row_info;  // [M] or null
 };
 
 // Two by two bf16 of two words a (k) and b (k + 1): the pair of low halves, the pair of high halves.
@@ -75,11 +76,13 @@ __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block,
   const int64_t m0 = (int64_t)row_block * kRows;
   if (tid < kRows) {
     const int64_t m = m0 + tid;
-    int ten = -1;
+    int ten = -1, r = 0;
     if (m < g.M) {
       const int64_t req = g.row_to_req ? (int64_t)g.row_to_req[m] : g.row_base + m;
       int tenant = 0;
-      if (req >= 0 && req < g.B && routed_rank(g.ad, g.tenant_id, g.route, (int)req, g.B, g.site, &tenant)) ten = tenant;
+      if (req >= 0 && req < g.B) r = routed_rank(g.ad, g.tenant_id, g.route, (int)req, g.B, g.site, &tenant);
+      if (r) ten = tenant;
+      if (g.row_info && part == 0 && share == 0) g.row_info[m] = RowLora{r ? g.ad.B[tenant * MILORA_NUM_SITES + g.site] : nullptr, r, 0};
     }
     row_ten[tid] = ten;
   }

@@ -13,13 +13,16 @@
 // adds the parts in part order and finishes the tile.  Nobody waits for anybody, so any number of workgroups may
 // be resident, and the sums do not depend on timing.  The counters are zero between launches.
 //
-// The LoRA term of the routed rows enters as more stages: t = X W^A (fp32, computed beforehand) split into two bf16 halves
-// (hi + lo) against W^B.  Then bias, one rounding, 16-byte stores.
+// The LoRA term of the routed rows (t = X W^A is computed beforehand, in fp32) enters in one of two ways.  ROWS: after the matrix
+// work every thread adds t W^B of its own outputs in fp32, the ranks dealt to the parts; what one tenant's adapter holds, Inf and NaN
+// too, reaches that tenant's rows only.  This serves packed weights and calls of fewer than 64 rows, where rows of many tenants
+// meet.  Else as more stages of the matrix work: t split into two bf16 halves (hi + lo, about 17 bits of it) against
+// W^B, the rows of other tenants entering as zeros.  Then bias, one rounding, 16-byte stores.
 //
 // Bound: few rows, the stream of the weights (a 4096 x 11008 linear at 45 rows: 23 us = 3.9 TB/s); from some hundred rows on
 // the copies through the L2 (0.58 us per 128 x 128 x 64 stage and compute unit, 56 GB/s each).  The seven linears of the 7B
-// layer: 45 rows 4940 us with the any-shape kernel, 160 us here; 777 rows 966 us with 256 x 256 tiles only, 500 us;
-// packed weights, 96 rows, three sites a request: 495 us with the stream kernel of decode.hip, 272 us.
+// layer: 45 rows 4940 us with the any-shape kernel, 160 us here; 777 rows 966 us with 256 x 256 tiles only, 505 us;
+// packed weights, 96 rows, three sites a request: 495 us with the stream kernel of decode.hip, 253 us.
 #include "shrink.h"
 #include "tiles.h"
 
@@ -35,6 +38,7 @@ constexpr int kT = 512;        // threads: eight waves
 constexpr int kCtlBytes = 4096;
 constexpr int kMaxGroups = 256;  // groups of 8 ranks of the LoRA phase listed at a time
 constexpr int kGroupM = 6;
+constexpr int kTs = MILORA_MAX_RANK + 4;  // t of a row in LDS
 
 template <int BM_, int BN_, int KQ_, int WMC_, int WNC_, int NS_, int OCC_>
 struct TileCfg {
@@ -48,6 +52,7 @@ struct TileCfg {
   static constexpr int RedBytes = KQ * BM * Ld * 4;
   static constexpr int RingBytes = NS * StageBytes;
   static constexpr int LdsBytes = kCtlBytes + (RedBytes > RingBytes ? RedBytes : RingBytes);
+  static_assert(BM * kTs * 4 <= LdsBytes - kCtlBytes, "t of the tile's rows");
   static_assert(KQ * WMC * WNC == 8 && (BM + BN) % 64 == 0 && BM * BN % (8 * kT) == 0, "tile shape");
   static_assert(CPW * (NS - 2) < 63 && LdsBytes * OCC <= 160 * 1024 && BM * 12 + kMaxGroups * 8 + 64 <= kCtlBytes, "resources");
 };
@@ -66,8 +71,8 @@ struct TParams {
   const int32_t* tenant_id;
   const uint8_t* route;
   AdapterView ad;
-  int64_t M;         // rows of this launch
-  int64_t row_base;  // index of its first row in the caller's matrix (requests of unmapped rows)
+  int64_t M;
+  const RowLora* row_info;  // [M], ROWS
   int d1, d2, site, B;
   int tilesM, tilesN;
   int S, steps;    // parts of the reduction and stages (64 k) per part
@@ -85,7 +90,7 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
 
-template <class C, bool PK>
+template <class C, bool PK, bool ROWS>
 __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   int* const row_ten = reinterpret_cast<int*>(lds);   // [BM] tenant of each row of the tile, -1: no LoRA term
@@ -93,6 +98,10 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   int* const row_group = row_rank + C::BM;            // [BM] first rank group of the row's run
   int2* const groups = reinterpret_cast<int2*>(row_group + C::BM);  // [kMaxGroups] tenant, first rank
   int* const ctl = reinterpret_cast<int*>(groups + kMaxGroups);     // 0: arrivals before this one, 1: rows with a LoRA term
+  // (ROWS: W^B of the row at the first rank of this part and the tile's first column; that rank; ranks in this part)
+  const bf16_t** const row_b = reinterpret_cast<const bf16_t**>(lds);  // [BM]
+  int* const row_c0 = reinterpret_cast<int*>(row_b + C::BM);           // [BM]
+  int* const row_cnt = row_c0 + C::BM;                                 // [BM]
   unsigned char* const ring = lds + kCtlBytes;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -194,17 +203,34 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   for (int s = 0; s < C::NS - 1; ++s) issue(s, s);
   // which rows carry a LoRA term (looked up while the first stages are on their way)
   const bool with_lora = part == p.S - 1;
-  if (with_lora && tid < C::BM) {
-    int tenant = -1, r = 0;
-    if (tid < rows) {
-      const int64_t m = m0 + tid;
-      const int64_t req = p.row_to_req ? (int64_t)p.row_to_req[m] : p.row_base + m;
-      r = (req >= 0 && req < p.B) ? routed_rank(p.ad, p.tenant_id, p.route, (int)req, p.B, p.site, &tenant) : 0;
+  if ((ROWS || with_lora) && tid < C::BM) {
+    if constexpr (ROWS) {
+      RowLora info{nullptr, 0, 0};
+      if (tid < rows) info = p.row_info[m0 + tid];
+      const int r = info.rank;
+      const int ng = (r + 7) >> 3, c0 = part * ng / p.S * 8, c1 = (part + 1) * ng / p.S * 8, cnt = (c1 < r ? c1 : r) - c0;
+      row_c0[tid] = c0;
+      row_cnt[tid] = cnt > 0 ? cnt : 0;
+      if (cnt > 0) row_b[tid] = (const bf16_t*)info.B + (size_t)c0 * p.d2 + n0;
+      int most = cnt;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_xor(most, off, 64);
+        most = o > most ? o : most;
+      }
+      if (lane == 0) ctl[1 + w] = most;
+    } else {
+      int tenant = -1, r = 0;
+      if (tid < rows) {
+        const int64_t m = m0 + tid;
+        const int64_t req = p.row_to_req ? (int64_t)p.row_to_req[m] : m;
+        r = (req >= 0 && req < p.B) ? routed_rank(p.ad, p.tenant_id, p.route, (int)req, p.B, p.site, &tenant) : 0;
+      }
+      row_ten[tid] = r ? tenant : -1;
+      row_rank[tid] = r;
+      const unsigned long long any = __ballot(r > 0);
+      if (lane == 0) ctl[1 + w] = any != 0;
     }
-    row_ten[tid] = r ? tenant : -1;
-    row_rank[tid] = r;
-    const unsigned long long any = __ballot(r > 0);
-    if (lane == 0) ctl[1 + w] = any != 0;
   }
   int slot = 0;
   for (int st = 0; st < n_steps; ++st) {
@@ -227,11 +253,12 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
 
   // ---- LoRA term of the routed rows (by the workgroup of the last part): more stages of 64 k -----------------------
   // A stage takes four groups of 8 ranks, and as many stages as the ring holds are filled together (one round trip for t and
-  // W^B instead of one per stage; packed 96 rows of 24 requests, three sites each: 27.4 -> 22.3 us a call on 4096 x 4096).  t = X W^A (fp32) enters as bf16 hi + lo, hi against the groups' rows of W^B in
-  // the first 32 k, lo against the same rows in the second.  Consecutive rows of one tenant are a run; a run's ranks get
-  // groups of their own, in which the other rows of the tile are zero, so tenants share stages.
+  // W^B instead of one per stage: 777 rows of 5 requests, ranks 8 to 64, 4096 x 4096: 47.8 -> 46.0 us a call).  t = X W^A (fp32)
+  // enters as bf16 hi + lo, hi against the groups' rows of W^B in the first 32 k, lo against the same rows in the second.
+  // Consecutive rows of one tenant are a run; a run's ranks get groups of their own, in which the other rows of the tile are
+  // zero, so tenants share stages.
   bool lora = false;
-  if (with_lora)
+  if (!ROWS && with_lora)
 #pragma unroll
     for (int i = 0; i < C::BM / 64; ++i) lora = lora || ctl[1 + i];
   if (lora) {
@@ -399,6 +426,77 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
       val[it][h] = v;
     }
 
+  // ---- ROWS: LoRA term of this part's ranks: t of the tile's rows through LDS (the shrink's parts added in part order), then
+  // kU rows of W^B for all of a thread's rows on their way together.  Bound by the reads of W^B where every row has a tenant of
+  // its own: 64 packed rows, rank 64, 4096 x 4096: 143 us a call with the term as matrix stages, 56 us so.  A tile of one tenant
+  // reads its W^B again for each row: 300 rows of 4 tenants, rank 64, 4096 x 11008: 77 -> 89 us.
+  if constexpr (ROWS) {
+    int most = ctl[1];
+    if (C::BM > 64) most = ctl[2] > most ? ctl[2] : most;
+    if (most > 0) {
+      constexpr int kU = C::Items == 1 ? 16 : 8;
+      float* const ts = reinterpret_cast<float*>(ring);  // [BM][kTs]: rows 16 bytes past a multiple of all banks
+      gbf16* bp[C::Items];
+      int cnt[C::Items], ranks = 0;
+#pragma unroll
+      for (int it = 0; it < C::Items; ++it) {
+        cnt[it] = cg * 8 < cols ? row_cnt[r0 + it * kRowStep] : 0;
+        bp[it] = cnt[it] > 0 ? in_global(row_b[r0 + it * kRowStep]) + cg * 8 : in_global(p.W);  // (no rank: any valid 16 bytes)
+        ranks = cnt[it] > ranks ? cnt[it] : ranks;
+      }
+      __syncthreads();  // the sums are read
+      const int pieces = (most + kU - 1) / kU * (kU / 4), total4 = C::BM * pieces;  // of four ranks, whole steps of kU
+      for (int e = tid; e < total4; e += kT) {
+        const int row = e / pieces, c = (e - row * pieces) * 4, left = row_cnt[row] - c;
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (left > 0) {
+          const float* const tp = p.t + (size_t)(m0 + row) * p.ad.r_max + row_c0[row] + c;
+          if ((p.ad.r_max & 3) == 0) {
+            for (int k0 = 0; k0 < p.parts; k0 += 4) {
+              f32x4 x[4];
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                x[k] = *reinterpret_cast<const f32x4*>(tp + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride);
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                if (k0 + k < p.parts) v += x[k];
+            }
+#pragma unroll
+            for (int i = 1; i < 4; ++i) v[i] = i < left ? v[i] : 0.f;  // (past the rank: never written)
+          } else {
+            for (int k = 0; k < p.parts; ++k)
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (i < left) v[i] += tp[k * p.t_stride + i];
+          }
+        }
+        *reinterpret_cast<f32x4*>(ts + row * kTs + c) = v;
+      }
+      __syncthreads();
+      for (int c0 = 0; __any(ranks > c0); c0 += kU) {
+        u32x4 b[C::Items][kU];
+#pragma unroll
+        for (int it = 0; it < C::Items; ++it)
+#pragma unroll
+          for (int u = 0; u < kU; ++u) b[it][u] = *(gu32x4_a2*)(bp[it] + (size_t)(c0 + u < cnt[it] ? c0 + u : 0) * p.d2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int it = 0; it < C::Items; ++it)
+#pragma unroll
+          for (int u = 0; u < kU; ++u) {
+            const float t = ts[(r0 + it * kRowStep) * kTs + c0 + u];
+            const bool in = c0 + u < cnt[it];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const uint32_t x = in ? b[it][u][e] : 0u;
+              val[it][e >> 1][2 * (e & 1)] += t * __uint_as_float(x << 16);
+              val[it][e >> 1][2 * (e & 1) + 1] += t * __uint_as_float(x & 0xffff0000u);
+            }
+          }
+      }
+    }
+  }
+
   if (p.S > 1) {
     f32x4* const mine = reinterpret_cast<f32x4*>(p.partial) + ((size_t)tile * p.S + part) * (C::BM * C::BN / 4);
 #pragma unroll
@@ -460,17 +558,17 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   }
 }
 
-template <class C, bool PK>
+template <class C, bool PK, bool ROWS>
 int launch_tiles(const TParams& p, hipStream_t st) {
   static thread_local int lds_set_for = -1;
   int dev = 0;
   MILORA_HIP(hipGetDevice(&dev));
   if (lds_set_for != dev) {
-    MILORA_HIP(hipFuncSetAttribute((const void*)tile_kernel<C, PK>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LdsBytes));
+    MILORA_HIP(hipFuncSetAttribute((const void*)tile_kernel<C, PK, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LdsBytes));
     lds_set_for = dev;
   }
   const int total = p.tilesM * p.tilesN * p.S;
-  hipLaunchKernelGGL((tile_kernel<C, PK>), dim3(8 * ((total + 7) / 8)), dim3(kT), C::LdsBytes, st, p);
+  hipLaunchKernelGGL((tile_kernel<C, PK, ROWS>), dim3(8 * ((total + 7) / 8)), dim3(kT), C::LdsBytes, st, p);
   return check_launch();
 }
 
@@ -528,16 +626,18 @@ bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, cons
   return (uint64_t)d1 * 128u * 2u < (1ull << 31);  // byte offsets inside a tile's lines
 }
 
-int routed_linear_tiles(const bf16_t* X, int64_t M, int64_t row_base, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
-                        const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
+int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
+                        const RowLora* row_info, const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
                         int B, const float* t, size_t t_stride, int parts, const TilePlan& pl, int* cnt, float* partial, bf16_t* Y, hipStream_t st) {
   TParams p;
   p.X = X; p.W = W; p.bias = bias; p.Y = Y; p.t = t; p.t_stride = t_stride; p.parts = parts;
-  p.row_to_req = row_to_req; p.tenant_id = tenant_id; p.route = route; p.ad = ad; p.M = M; p.row_base = row_base; p.d1 = d1; p.d2 = d2;
+  p.row_to_req = row_to_req; p.tenant_id = tenant_id; p.route = route; p.ad = ad; p.M = M; p.row_info = row_info; p.d1 = d1; p.d2 = d2;
   p.site = site; p.B = B; p.tilesM = pl.tilesM; p.tilesN = pl.tilesN; p.S = pl.S; p.steps = pl.steps;
   p.partial = partial; p.cnt = cnt;
-  if (pl.shape == kTiles128) return packed ? launch_tiles<CfgMid, true>(p, st) : launch_tiles<CfgMid, false>(p, st);
-  return packed ? launch_tiles<CfgSmall, true>(p, st) : launch_tiles<CfgSmall, false>(p, st);
+  const bool mid = pl.shape == kTiles128;
+  if (packed) return mid ? launch_tiles<CfgMid, true, true>(p, st) : launch_tiles<CfgSmall, true, true>(p, st);
+  if (row_info) return mid ? launch_tiles<CfgMid, false, true>(p, st) : launch_tiles<CfgSmall, false, true>(p, st);
+  return mid ? launch_tiles<CfgMid, false, false>(p, st) : launch_tiles<CfgSmall, false, false>(p, st);
 }
 
 }  // namespace milora

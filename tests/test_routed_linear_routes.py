@@ -85,3 +85,60 @@ def test_workspace_for_the_largest_call_serves_every_smaller_one():
                 assert all(x <= y for s in along for x, y in zip(s, s[1:])), (M, a, r)
     for M in rows:
         assert size(M, 4096, 4096, 8) <= size(M, 4096, 4096, 9) <= size(M, 4096, 4096, 64)
+
+
+@gpu
+@pytest.mark.parametrize("packed,M,d1,d2,T", [
+    (False, 45, 192, 272, 5),    # 64 x 64 tiles, one part
+    (False, 63, 4096, 144, 7),   # the reduction in parts
+    (True, 33, 96, 2064, 33),    # a tenant per row, half a stage at the end
+    (True, 100, 2048, 3520, 9),  # 128 x 128 tiles
+])
+def test_one_tenants_infinities_and_nans_reach_its_own_rows_only(packed, M, d1, d2, T):
+    """Rows of many tenants meet in a tile.  Tenant 1's W^B holds Inf and NaN, tenant 2's W^A an Inf (its shrink is Inf): every
+    other row, routed or not, stays bit for bit what it is with clean adapters, and theirs are Inf and NaN where fp64 has them."""
+    site, rank = 2, (12, 16, 5)
+    A, B, ranks = _adapters(T, d1, d2, rank, 0.1, 30 + M)
+    A, B = [[a[0].clone()] * 7 for a in A], [[b[0].clone()] * 7 for b in B]
+    g = torch.Generator(device=DEV).manual_seed(M)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    X, W = rnd(M, d1), rnd(d2, d1) * d1 ** -0.5
+    Wd = mb.milora_pack_weight(W) if packed else W
+    tid = torch.arange(T, dtype=torch.int32)
+    route = torch.tensor([mb.ROUTE_NONE if t == 4 else site for t in range(T)], dtype=torch.uint8)
+    r2r = (torch.arange(M) % T).to(torch.int32)
+    run = lambda: mb.milora_routed_linear(X, Wd, mb.AdapterTable.from_tensors(A, B, ranks), site, tid.to(DEV), route.to(DEV),
+                                          r2r.to(DEV), w_layout=mb.W_PACKED if packed else mb.W_ROWMAJOR, d2=d2)
+    clean = run()
+    assert torch.isfinite(clean).all()
+    for c, n, v in [(3, 7, float("inf")), (0, d2 - 1, float("-inf")), (ranks[1] - 1, 64, float("nan"))]:
+        B[1][site][c, n] = v
+    A[2][site][d1 - 1, 1] = float("inf")
+    Y = run()
+    bad = (r2r == 1) | (r2r == 2)
+    assert torch.equal(Y[~bad], clean[~bad])
+    for m in torch.nonzero(bad).flatten().tolist():
+        t = X[m].double() @ A[r2r[m]][site].double()
+        ref = X[m].double() @ W.double().T + (t[:, None] * B[r2r[m]][site].double()).sum(0)
+        for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+            assert torch.equal(kind(Y[m]), kind(ref)), f"row {m}, tenant {int(r2r[m])}"
+        fine = torch.isfinite(ref)
+        assert (Y[m].double() - ref)[fine].abs().max() <= 2e-2 * ref[fine].abs().max() if fine.any() else True
+
+
+@gpu
+@pytest.mark.parametrize("packed,M", [(False, 1), (False, 63), (True, 1), (True, 33), (True, 200)])
+def test_the_low_rank_intermediate_keeps_all_bits(packed, M):
+    """t = 2^20 + 2^10 + 1, every sum exact in fp32, against a base term of -(2^20 + 2^10): the result is the last of t's 21 bits."""
+    d1, d2, site = 64, 80, 0
+    X, W = torch.zeros(M, d1), torch.zeros(d2, d1)
+    X[:, 5], X[:, 20], X[:, 63] = 2.0 ** 10, 2.0 ** 5, 1.0
+    W[:, 5], W[:, 20] = -2.0 ** 10, -2.0 ** 5
+    A, B = torch.zeros(d1, 8), torch.zeros(8, d2)
+    A[5, 3], A[20, 3], A[63, 3], B[3] = 2.0 ** 10, 2.0 ** 5, 1.0, 1.0
+    X, W, A, B = (v.to(torch.bfloat16).to(DEV) for v in (X, W, A, B))
+    tab = mb.AdapterTable.from_tensors([[A] * 7], [[B] * 7], [8])
+    one = torch.zeros(1, dtype=torch.uint8, device=DEV)
+    Y = mb.milora_routed_linear(X, mb.milora_pack_weight(W) if packed else W, tab, site, one.int(), one,
+                                torch.zeros(M, dtype=torch.int32, device=DEV), w_layout=mb.W_PACKED if packed else mb.W_ROWMAJOR, d2=d2)
+    assert (Y == 1).all()

@@ -28,7 +28,7 @@ int static_scratch_status(int* status, hipStream_t st);
 int decode_workspace_status(const void* workspace, int* status, hipStream_t st);
 bool prefill_supported(int64_t M, int d1, int d2, const void* X, const void* W, const void* Y);
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
-                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, RowLora* row_info, hipStream_t stream);
+                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, hipStream_t stream);
 int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W,
                           const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id,
                           const uint8_t* route, int B, const float* t, bf16_t* Y, hipStream_t st);
@@ -268,7 +268,7 @@ extern "C" size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2
   // Control words, LoRA shrinks, the rows' look-ups, partial tiles.  What a call needs of shrinks and tiles goes up and down with M (fewer rows are cut
   // into more parts); a caller sizes once for the largest call, so each is bounded by something that no size lowers.
   const size_t t_bytes = align_up(shrink_rows_bound(M, d1) * r_max * sizeof(float), 256);
-  const size_t tiles = kStreamCtrlBytes + t_bytes + align_up((size_t)M * sizeof(RowLora), 256) + partial_bytes_bound(M, d1, d2);
+  const size_t tiles = kStreamCtrlBytes + t_bytes + align_up((size_t)M * sizeof(int2), 256) + partial_bytes_bound(M, d1, d2);
   // (the stream kernel's space for swapped tiles belongs to calls of up to 32 rows only)
   size_t packed = 0;
   for (int most : {32, MILORA_MAX_DECODE_BATCH}) {
@@ -329,12 +329,12 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
     if (large || tiles_supported(M, d1, d2, packed, X, W, Y)) {
       const int parts = shrink_parts(M, d1);
       const size_t t_stride = (size_t)M * ad.r_max;
-      RowLora* const info = (RowLora*)((char*)t + align_up(t_stride * sizeof(float) * parts, 256));
-      float* const partial = (float*)((char*)info + align_up((size_t)M * sizeof(RowLora), 256));
+      int2* const looked_up = (int2*)((char*)t + align_up(t_stride * sizeof(float) * parts, 256));
+      float* const partial = (float*)((char*)looked_up + align_up((size_t)M * sizeof(int2), 256));
       // Where the 256 x 256 kernel is no choice, the LoRA term is added in fp32 row by row: few rows and packed weights, where many
       // tenants meet, and weights beyond that kernel's offsets.
-      RowLora* const row_info = large ? nullptr : info;
-      rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, row_info, st);
+      int2* const row_lora = large ? nullptr : looked_up;
+      rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, row_lora, st);
       if (rc) return rc;
       // more rows than a launch of the smaller tiles takes, and no larger ones for this layout: slices of rows
       const int64_t slice = large ? M : kTileMaxRows;
@@ -348,7 +348,7 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
           rc = routed_linear_prefill(x, mc, d1, d2, map, (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
                                      t, y, st);
         else
-          rc = routed_linear_tiles(x, mc, d1, d2, map, (const bf16_t*)W, packed, row_info ? row_info + m0 : nullptr, (const bf16_t*)bias, ad, site, tenant_id,
+          rc = routed_linear_tiles(x, mc, d1, d2, map, (const bf16_t*)W, packed, row_lora ? row_lora + m0 : nullptr, (const bf16_t*)bias, ad, site, tenant_id,
                                    route, B, t + (size_t)m0 * ad.r_max, t_stride, parts, pl, cnt, partial, y, st);
         if (rc) return rc;
       }

@@ -167,13 +167,6 @@ inline size_t shrink_rows_bound(int64_t M, int d1) {
   return (size_t)(parts == 1 || n < M ? M : n);
 }
 
-// What the shrink's look-ups found for a row, for the launch behind it: one load there instead of a chain of five.
-struct RowLora {
-  const void* B;  // W^B of the row's tenant at the call's site
-  int32_t rank;   // 0: no LoRA term
-  int32_t unused;
-};
-
 // ---- internal entry points shared between translation units ------------------------------------
 // LoRA shrink in fp32: for every row m whose request is routed to site `site + i`, i < sites, t[i][m][0..r) = X[m] . A.
 // X has rows of ldx elements, t is [sites][M][r_max] floats; rows that carry no LoRA term are left untouched.

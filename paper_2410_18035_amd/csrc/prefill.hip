@@ -366,11 +366,18 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
   }
 }
 
-template <int RT>
+template <int RT, bool INFO>
 __global__ void __launch_bounds__(512, 4) shrink_tiles_kernel(const ShrinkArgs g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[8 * kShrinkWaveBytes];
-  __shared__ int row_ten[RT * 16];
-  shrink_block<RT, 8>(g, blockIdx.x, blockIdx.y, gridDim.y, blockIdx.z, gridDim.z, smem, row_ten, [](float* p, float v) { *p = v; });
+  __shared__ int row_ten[RT * 16 * (INFO ? 2 : 1)];
+  shrink_block<RT, 8, INFO>(g, blockIdx.x, blockIdx.y, gridDim.y, blockIdx.z, gridDim.z, smem, row_ten,
+                            [](float* p, float v) { *p = v; });
+}
+
+template <int RT>
+void launch_shrink_block(const ShrinkArgs& g, dim3 grid, hipStream_t st) {
+  if (g.row_lora) hipLaunchKernelGGL((shrink_tiles_kernel<RT, true>), grid, dim3(512), 0, st, g);
+  else hipLaunchKernelGGL((shrink_tiles_kernel<RT, false>), grid, dim3(512), 0, st, g);
 }
 
 }  // namespace
@@ -428,24 +435,28 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 }
 
 // LoRA shrink of the rows the tile kernel serves (same conditions as prefill_supported): t receives
-// shrink_parts(M, d1) partial results [part][M][r_max], to be added in part order, row_info (or null) the rows' look-ups.
+// shrink_parts(M, d1) partial results [part][M][r_max], to be added in part order, row_lora (or null) what the look-ups found of
+// each row.
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
-                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, RowLora* row_info, hipStream_t stream) {
+                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, hipStream_t stream) {
   const int parts = shrink_parts(M, d1);
   const int64_t slice = (int64_t)1 << 30;  // rows per launch: the grid index stays well inside 32 bits
   for (int64_t r0 = 0; r0 < M; r0 += slice) {
     ShrinkArgs g{X + (size_t)r0 * d1, M - r0 < slice ? M - r0 : slice, r0, d1, site, B, row_to_req ? row_to_req + r0 : nullptr,
-                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max, row_info ? row_info + r0 : nullptr};
+                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max, row_lora ? row_lora + r0 : nullptr};
     if (M <= kTileMaxRows) {
-      // up to four workgroups share the units of a block while all of them are resident at once (two per compute unit; beams,
-      // 96 rows of 24 requests: 13.6 us a launch with one, 7.4 with four)
+      // Workgroups share the units of a block (32 ranks of a tenant each) while there can be units for them and all are resident
+      // at once, two per compute unit.  64 packed rows of 64 tenants, rank 256, 4096 x 4096, a call: 189 us with four at
+      // most, 87 so; 45 rows of one request have one unit a block, and no workgroup comes for nothing.
       const int64_t blocks = (g.M + 15) / 16;
+      const int tenants = B < ad.n_tenants ? B : ad.n_tenants;
+      const int units = (tenants < 16 ? tenants : 16) * ((ad.r_max + kShrinkC - 1) / kShrinkC);
       int shares = 1;
-      while (shares < 4 && blocks * parts * shares * 2 <= 512) shares *= 2;
-      hipLaunchKernelGGL((shrink_tiles_kernel<1>), dim3((unsigned)blocks, parts, shares), dim3(512), 0, stream, g);
+      while (shares < units && blocks * parts * shares * 2 <= 512) shares *= 2;
+      launch_shrink_block<1>(g, dim3((unsigned)blocks, parts, shares), stream);
     }
     else
-      hipLaunchKernelGGL((shrink_tiles_kernel<4>), dim3((unsigned)((g.M + 63) / 64), parts), dim3(512), 0, stream, g);
+      launch_shrink_block<4>(g, dim3((unsigned)((g.M + 63) / 64), parts), stream);
     const int rc = check_launch();
     if (rc) return rc;
   }

@@ -35,7 +35,7 @@ struct ShrinkArgs {
   AdapterView ad;
   float* t;        // [part][M][r_max]
   size_t t_stride;
-  RowLora* row_info;  // [M] or null
+  int2* row_lora;  // [M] INFO: receives tenant and rank of each row (rank 0: no LoRA term)
 };
 
 // Two by two bf16 of two words a (k) and b (k + 1): the pair of low halves, the pair of high halves.
@@ -66,8 +66,8 @@ __device__ __forceinline__ u32x4 load8(gbf16* p, int left, bool vec) {
   return v;
 }
 
-// STORE(float* p, float v) stores one element of t.  `smem`: NW * kShrinkWaveBytes, `row_ten`: 16 * RT ints.
-template <int RT, int NW, class STORE>
+// STORE(float* p, float v) stores one element of t.  `smem`: NW * kShrinkWaveBytes, `row_ten`: 16 * RT ints (INFO: twice that).
+template <int RT, int NW, bool INFO, class STORE>
 __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block, int part, int parts, int share, int shares,
                                              unsigned char* smem, int* row_ten, STORE store) {
   constexpr int kRows = RT * 16;
@@ -80,11 +80,10 @@ __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block,
     if (m < g.M) {
       const int64_t req = g.row_to_req ? (int64_t)g.row_to_req[m] : g.row_base + m;
       int tenant = 0;
-      if (req >= 0 && req < g.B) r = routed_rank(g.ad, g.tenant_id, g.route, (int)req, g.B, g.site, &tenant);
-      if (r) ten = tenant;
-      if (g.row_info && part == 0 && share == 0) g.row_info[m] = RowLora{r ? g.ad.B[tenant * MILORA_NUM_SITES + g.site] : nullptr, r, 0};
+      if (req >= 0 && req < g.B && (r = routed_rank(g.ad, g.tenant_id, g.route, (int)req, g.B, g.site, &tenant))) ten = tenant;
     }
     row_ten[tid] = ten;
+    if (INFO) row_ten[kRows + tid] = r;
   }
   __syncthreads();
   const int my_ten = lane < kRows ? row_ten[lane] : -1;
@@ -180,6 +179,7 @@ __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block,
     }
     last = cur;
   }
+  if (INFO && part == 0 && share == 0 && tid < kRows && m0 + tid < g.M) g.row_lora[m0 + tid] = int2{row_ten[tid], row_ten[kRows + tid]};
 }
 
 }  // namespace milora

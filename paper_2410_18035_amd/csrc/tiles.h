@@ -27,10 +27,10 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool large);
 // The most partial_bytes over the plans of all calls of up to these sizes; never less for a larger size.
 size_t partial_bytes_bound(int64_t M, int d1, int d2);
 bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y);
-// `row_info` (always there for packed weights): the LoRA term in fp32 row by row.  Null: by the matrix cores, from the look-ups of
+// `row_lora` (always there for packed weights): the LoRA term in fp32 row by row.  Null: by the matrix cores, from the look-ups of
 // the other arguments; the rows are then all of the call's.
 int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
-                        const RowLora* row_info, const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
+                        const int2* row_lora, const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
                         int B, const float* t, size_t t_stride, int parts, const TilePlan& pl, int* cnt, float* partial, bf16_t* Y, hipStream_t st);
 
 }  // namespace milora

@@ -72,7 +72,7 @@ struct TParams {
   const uint8_t* route;
   AdapterView ad;
   int64_t M;
-  const RowLora* row_info;  // [M], ROWS
+  const int2* row_lora;  // [M], ROWS: tenant and rank of each row, from the shrink's look-ups (one load instead of a chain of four)
   int d1, d2, site, B;
   int tilesM, tilesN;
   int S, steps;    // parts of the reduction and stages (64 k) per part
@@ -98,10 +98,8 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   int* const row_group = row_rank + C::BM;            // [BM] first rank group of the row's run
   int2* const groups = reinterpret_cast<int2*>(row_group + C::BM);  // [kMaxGroups] tenant, first rank
   int* const ctl = reinterpret_cast<int*>(groups + kMaxGroups);     // 0: arrivals before this one, 1: rows with a LoRA term
-  // (ROWS: W^B of the row at the first rank of this part and the tile's first column; that rank; ranks in this part)
-  const bf16_t** const row_b = reinterpret_cast<const bf16_t**>(lds);  // [BM]
-  int* const row_c0 = reinterpret_cast<int*>(row_b + C::BM);           // [BM]
-  int* const row_cnt = row_c0 + C::BM;                                 // [BM]
+  int* const row_c0 = row_rank;    // (ROWS) [BM] first rank of the row in this part
+  int* const row_cnt = row_group;  // (ROWS) [BM] ranks of the row in this part
   unsigned char* const ring = lds + kCtlBytes;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -205,13 +203,12 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   const bool with_lora = part == p.S - 1;
   if ((ROWS || with_lora) && tid < C::BM) {
     if constexpr (ROWS) {
-      RowLora info{nullptr, 0, 0};
-      if (tid < rows) info = p.row_info[m0 + tid];
-      const int r = info.rank;
+      const int2 ten_rank = tid < rows ? p.row_lora[m0 + tid] : int2{-1, 0};
+      const int r = ten_rank.y;
       const int ng = (r + 7) >> 3, c0 = part * ng / p.S * 8, c1 = (part + 1) * ng / p.S * 8, cnt = (c1 < r ? c1 : r) - c0;
+      row_ten[tid] = ten_rank.x;
       row_c0[tid] = c0;
       row_cnt[tid] = cnt > 0 ? cnt : 0;
-      if (cnt > 0) row_b[tid] = (const bf16_t*)info.B + (size_t)c0 * p.d2 + n0;
       int most = cnt;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
@@ -441,7 +438,9 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
 #pragma unroll
       for (int it = 0; it < C::Items; ++it) {
         cnt[it] = cg * 8 < cols ? row_cnt[r0 + it * kRowStep] : 0;
-        bp[it] = cnt[it] > 0 ? in_global(row_b[r0 + it * kRowStep]) + cg * 8 : in_global(p.W);  // (no rank: any valid 16 bytes)
+        const int row = r0 + it * kRowStep;
+        bp[it] = in_global(p.W);  // (no rank: any valid 16 bytes)
+        if (cnt[it] > 0) bp[it] = in_global(p.ad.B[row_ten[row] * MILORA_NUM_SITES + p.site]) + (size_t)row_c0[row] * p.d2 + n0 + cg * 8;
         ranks = cnt[it] > ranks ? cnt[it] : ranks;
       }
       __syncthreads();  // the sums are read
@@ -627,16 +626,16 @@ bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, cons
 }
 
 int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W, bool packed,
-                        const RowLora* row_info, const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
+                        const int2* row_lora, const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id, const uint8_t* route,
                         int B, const float* t, size_t t_stride, int parts, const TilePlan& pl, int* cnt, float* partial, bf16_t* Y, hipStream_t st) {
   TParams p;
   p.X = X; p.W = W; p.bias = bias; p.Y = Y; p.t = t; p.t_stride = t_stride; p.parts = parts;
-  p.row_to_req = row_to_req; p.tenant_id = tenant_id; p.route = route; p.ad = ad; p.M = M; p.row_info = row_info; p.d1 = d1; p.d2 = d2;
+  p.row_to_req = row_to_req; p.tenant_id = tenant_id; p.route = route; p.ad = ad; p.M = M; p.row_lora = row_lora; p.d1 = d1; p.d2 = d2;
   p.site = site; p.B = B; p.tilesM = pl.tilesM; p.tilesN = pl.tilesN; p.S = pl.S; p.steps = pl.steps;
   p.partial = partial; p.cnt = cnt;
   const bool mid = pl.shape == kTiles128;
   if (packed) return mid ? launch_tiles<CfgMid, true, true>(p, st) : launch_tiles<CfgSmall, true, true>(p, st);
-  if (row_info) return mid ? launch_tiles<CfgMid, false, true>(p, st) : launch_tiles<CfgSmall, false, true>(p, st);
+  if (row_lora) return mid ? launch_tiles<CfgMid, false, true>(p, st) : launch_tiles<CfgSmall, false, true>(p, st);
   return mid ? launch_tiles<CfgMid, false, false>(p, st) : launch_tiles<CfgSmall, false, false>(p, st);
 }
 

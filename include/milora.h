@@ -15,11 +15,13 @@
  *    and the call returns without synchronising.  Buffers must stay valid until that work is done.
  *  - The library allocates nothing.  Calls that need scratch memory take a device `workspace`
  *    of at least the size the matching *_workspace_bytes() function returns.  A workspace must be
- *    zero-filled once before its first use: the decode kernels keep their cross-workgroup
- *    hand-over flags in it, as values that only grow from launch to launch, so nothing has to be
- *    cleared between calls; apart from that its contents are undefined.  After a call that
- *    returned an error, or when the same memory is to serve another entry point or other sizes,
- *    zero it again.  Two calls that share a workspace must be ordered on one stream.
+ *    zero-filled once before its first use: the decode kernels (milora_layer_decode on packed weights,
+ *    milora_routed_linear on up to 32 rows and packed weights) keep their cross-workgroup hand-over flags in
+ *    it, as values that only grow from launch to launch, so nothing has to be cleared between calls; apart
+ *    from that its contents are undefined.  Calls of the other kernels work whatever it holds.  One
+ *    milora_routed_linear workspace serves calls of any sizes and either layout in turn.  After a call that
+ *    returned an error, or when the same memory is to serve another entry point or milora_layer_decode at
+ *    other sizes, zero it again.  Two calls that share a workspace must be ordered on one stream.
  *  - Return value: MILORA_OK (0) or a negative milora_status.  Arguments are validated on the
  *    host before anything is enqueued; values that live in device arrays (tenant ids, routes,
  *    prompt spans) are checked by the kernels, which then skip the offending request as

@@ -28,7 +28,8 @@ int static_scratch_status(int* status, hipStream_t st);
 int decode_workspace_status(const void* workspace, int* status, hipStream_t st);
 bool prefill_supported(int64_t M, int d1, int d2, const void* X, const void* W, const void* Y);
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
-                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, hipStream_t stream);
+                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, int* clear,
+                        hipStream_t stream);
 int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int32_t* row_to_req, const bf16_t* W,
                           const bf16_t* bias, const AdapterView& ad, int site, const int32_t* tenant_id,
                           const uint8_t* route, int B, const float* t, bf16_t* Y, hipStream_t st);
@@ -334,7 +335,9 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
       // Where the 256 x 256 kernel is no choice, the LoRA term is added in fp32 row by row: few rows and packed weights, where many
       // tenants meet, and weights beyond that kernel's offsets.
       int2* const row_lora = large ? nullptr : looked_up;
-      rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, row_lora, st);
+      // Part counters start from zero in every call: what the workspace held before does not matter here.
+      int* const clear = row_lora || plan_tiles(M, d1, d2, true).S > 1 ? cnt : nullptr;
+      rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, row_lora, clear, st);
       if (rc) return rc;
       // more rows than a launch of the smaller tiles takes, and no larger ones for this layout: slices of rows
       const int64_t slice = large ? M : kTileMaxRows;

@@ -372,11 +372,13 @@ __global__ void __launch_bounds__(512, 4) shrink_tiles_kernel(const ShrinkArgs g
   __shared__ int row_ten[RT * 16 * (INFO ? 2 : 1)];
   shrink_block<RT, 8, INFO>(g, blockIdx.x, blockIdx.y, gridDim.y, blockIdx.z, gridDim.z, smem, row_ten,
                             [](float* p, float v) { *p = v; });
+  static_assert(kShrinkClear == 512, "one word per thread");
+  if (INFO && g.clear && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) g.clear[threadIdx.x] = 0;
 }
 
 template <int RT>
 void launch_shrink_block(const ShrinkArgs& g, dim3 grid, hipStream_t st) {
-  if (g.row_lora) hipLaunchKernelGGL((shrink_tiles_kernel<RT, true>), grid, dim3(512), 0, st, g);
+  if (g.row_lora || g.clear) hipLaunchKernelGGL((shrink_tiles_kernel<RT, true>), grid, dim3(512), 0, st, g);
   else hipLaunchKernelGGL((shrink_tiles_kernel<RT, false>), grid, dim3(512), 0, st, g);
 }
 
@@ -436,14 +438,14 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 
 // LoRA shrink of the rows the tile kernel serves (same conditions as prefill_supported): t receives
 // shrink_parts(M, d1) partial results [part][M][r_max], to be added in part order, row_lora (or null) what the look-ups found of
-// each row.
+// each row; `clear` (or null) is zeroed.
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
-                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, hipStream_t stream) {
+                        const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, int* clear, hipStream_t stream) {
   const int parts = shrink_parts(M, d1);
   const int64_t slice = (int64_t)1 << 30;  // rows per launch: the grid index stays well inside 32 bits
   for (int64_t r0 = 0; r0 < M; r0 += slice) {
     ShrinkArgs g{X + (size_t)r0 * d1, M - r0 < slice ? M - r0 : slice, r0, d1, site, B, row_to_req ? row_to_req + r0 : nullptr,
-                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max, row_lora ? row_lora + r0 : nullptr};
+                 tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max, row_lora ? row_lora + r0 : nullptr, clear};
     if (M <= kTileMaxRows) {
       // Workgroups share the units of a block (32 ranks of a tenant each) while there can be units for them and all are resident
       // at once, two per compute unit.  64 packed rows of 64 tenants, rank 256, 4096 x 4096, a call: 189 us with four at

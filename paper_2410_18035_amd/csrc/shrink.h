@@ -21,6 +21,7 @@ typedef __attribute__((address_space(1))) const bf16_t gbf16;
 typedef __attribute__((address_space(1))) const u32x4 gu32x4;
 __device__ __forceinline__ gbf16* in_global(const void* p) { return (gbf16*)p; }
 
+constexpr int kShrinkClear = 512;
 constexpr int kShrinkC = 32;                                    // ranks at a time
 constexpr int kShrinkLd = kShrinkChunkK + 8;                    // LDS row of a rank, padded: 16 ranks at one k group hit all banks
 constexpr int kShrinkWaveBytes = kShrinkC * kShrinkLd * 2;      // 8.5 KiB: the wave's chunk of W^A, at the end its sums
@@ -35,7 +36,8 @@ struct ShrinkArgs {
   AdapterView ad;
   float* t;        // [part][M][r_max]
   size_t t_stride;
-  int2* row_lora;  // [M] INFO: receives tenant and rank of each row (rank 0: no LoRA term)
+  int2* row_lora;  // INFO: [M] receives tenant and rank of each row (rank 0: no LoRA term), or null
+  int* clear;      // INFO: [kShrinkClear] words of the launch behind this one that have to start from zero, or null
 };
 
 // Two by two bf16 of two words a (k) and b (k + 1): the pair of low halves, the pair of high halves.
@@ -179,7 +181,8 @@ __device__ __forceinline__ void shrink_block(const ShrinkArgs& g, int row_block,
     }
     last = cur;
   }
-  if (INFO && part == 0 && share == 0 && tid < kRows && m0 + tid < g.M) g.row_lora[m0 + tid] = int2{row_ten[tid], row_ten[kRows + tid]};
+  if (INFO && g.row_lora && part == 0 && share == 0 && tid < kRows && m0 + tid < g.M)
+    g.row_lora[m0 + tid] = int2{row_ten[tid], row_ten[kRows + tid]};
 }
 
 }  // namespace milora

@@ -16,8 +16,8 @@ struct TilePlan {
 constexpr int kMaxSplitUnits = 512;  // tiles x parts of a launch that cuts its reduction
 constexpr int kMaxParts = 8;         // of one reduction
 // The first bytes of a routed linear's workspace belong to control words: those of the stream kernels (decode.hip), then the
-// part counters of the tile kernel, zero between launches.  Both keep their data behind them, so calls of any sizes and
-// either layout can follow one another on one workspace, and the status word can be asked for after either.
+// part counters of the tile kernel, zeroed by the shrink launch in front of it.  Both keep their data behind them, so calls of
+// any sizes and either layout can follow one another on one workspace, and the status word can be asked for after either.
 constexpr int kStreamCtrlBytes = 16384;
 constexpr int kTileCtrlBytes = kMaxSplitUnits * (int)sizeof(int);
 constexpr int kTileCtrlOffset = kStreamCtrlBytes - kTileCtrlBytes;

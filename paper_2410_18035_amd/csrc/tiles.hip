@@ -11,7 +11,7 @@
 // Few rows leave few tiles: the reduction is then cut into S parts, one workgroup each, so that every compute unit
 // streams weights.  A workgroup stores its partial tile (written through) and counts itself in; the one that comes last
 // adds the parts in part order and finishes the tile.  Nobody waits for anybody, so any number of workgroups may
-// be resident, and the sums do not depend on timing.  The counters are zero between launches.
+// be resident, and the sums do not depend on timing.  The shrink's launch zeroes the counters.
 //
 // The LoRA term of the routed rows (t = X W^A is computed beforehand, in fp32) enters in one of two ways.  ROWS: after the matrix
 // work every thread adds t W^B of its own outputs in fp32, the ranks dealt to the parts; what one tenant's adapter holds, Inf and NaN
@@ -507,7 +507,7 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
     if (tid == 0) ctl[0] = __hip_atomic_fetch_add(p.cnt + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (ctl[0] != p.S - 1) return;
-    if (tid == 0) __hip_atomic_store(p.cnt + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(p.cnt + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next slice of rows
     const f32x4* const all = reinterpret_cast<const f32x4*>(p.partial) + (size_t)tile * p.S * (C::BM * C::BN / 4);
     if constexpr (C::Items == 1) {
       for (int s0 = 0; s0 < p.S; s0 += 4) {
@@ -634,6 +634,7 @@ int routed_linear_tiles(const bf16_t* X, int64_t M, int d1, int d2, const int32_
   p.site = site; p.B = B; p.tilesM = pl.tilesM; p.tilesN = pl.tilesN; p.S = pl.S; p.steps = pl.steps;
   p.partial = partial; p.cnt = cnt;
   const bool mid = pl.shape == kTiles128;
+  static_assert(kMaxSplitUnits <= kShrinkClear, "counters the shrink zeroes");
   if (packed) return mid ? launch_tiles<CfgMid, true, true>(p, st) : launch_tiles<CfgSmall, true, true>(p, st);
   if (row_lora) return mid ? launch_tiles<CfgMid, false, true>(p, st) : launch_tiles<CfgSmall, false, true>(p, st);
   return mid ? launch_tiles<CfgMid, false, false>(p, st) : launch_tiles<CfgSmall, false, false>(p, st);

@@ -142,3 +142,32 @@ def test_the_low_rank_intermediate_keeps_all_bits(packed, M):
     Y = mb.milora_routed_linear(X, mb.milora_pack_weight(W) if packed else W, tab, site, one.int(), one,
                                 torch.zeros(M, dtype=torch.int32, device=DEV), w_layout=mb.W_PACKED if packed else mb.W_ROWMAJOR, d2=d2)
     assert (Y == 1).all()
+
+
+@gpu
+@pytest.mark.parametrize("packed,M,d1,d2", [
+    (False, 16, 4096, 64),    # few rows, the reduction in parts
+    (False, 300, 2048, 3520),  # 128 x 128 tiles in parts, the LoRA term as matrix stages
+    (False, 40, 130, 70),     # any-shape
+    (True, 70, 4096, 64),     # packed, in parts
+    (True, 4100, 1024, 64),   # packed, a second slice of few rows
+])
+def test_tiles_work_whatever_the_workspace_holds(packed, M, d1, d2):
+    """Parts of a reduction count themselves in words of the workspace: these start from zero in every call."""
+    A, B, rank = _adapters(4, d1, d2, (8, 20), 0.1, 50)
+    tab = mb.AdapterTable.from_tensors(A, B, rank)
+    g = torch.Generator(device=DEV).manual_seed(51)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    X, W = rnd(M, d1), rnd(d2, d1)
+    W = mb.milora_pack_weight(W) if packed else W
+    ids = torch.arange(4, dtype=torch.int32, device=DEV)
+    r2r = torch.arange(M, dtype=torch.int32, device=DEV) * 4 // M
+    nbytes = mb.routed_linear_workspace_bytes(M, d1, d2, tab.r_max)
+    run = lambda ws: mb.milora_routed_linear(X, W, tab, 1, ids, torch.ones_like(ids, dtype=torch.uint8), r2r, d2=d2,
+                                             w_layout=mb.W_PACKED if packed else mb.W_ROWMAJOR, workspace=ws,
+                                             out=torch.full((M, d2), 7.0, dtype=torch.bfloat16, device=DEV))
+    clean = run(torch.zeros(nbytes, dtype=torch.uint8, device=DEV))
+    dirty = torch.full((nbytes,), 255, dtype=torch.uint8, device=DEV)
+    for _ in range(2):
+        assert torch.equal(run(dirty), clean)
+    assert torch.equal(run(torch.randint(0, 256, (nbytes,), dtype=torch.uint8, device=DEV)), clean)

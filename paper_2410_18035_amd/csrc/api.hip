@@ -37,7 +37,6 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kStreamRows = 32;   // rows up to which a packed linear takes the weight-streaming kernel
 
 template <typename T>
 __device__ __forceinline__ float block_sum(float v, float* sh) {
@@ -270,12 +269,7 @@ extern "C" size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2
   // into more parts); a caller sizes once for the largest call, so each is bounded by something that no size lowers.
   const size_t t_bytes = align_up(shrink_rows_bound(M, d1) * r_max * sizeof(float), 256);
   const size_t tiles = kStreamCtrlBytes + t_bytes + align_up((size_t)M * sizeof(int2), 256) + partial_bytes_bound(M, d1, d2);
-  // (the stream kernel's space for swapped tiles belongs to calls of up to 32 rows only)
-  size_t packed = 0;
-  for (int most : {32, MILORA_MAX_DECODE_BATCH}) {
-    const size_t n = routed_linear_packed_workspace_bytes(M <= most ? (int)M : most, d1, d2, r_max);
-    packed = n > packed ? n : packed;
-  }
+  const size_t packed = routed_linear_packed_workspace_bytes(M <= kStreamRows ? (int)M : kStreamRows, d1, d2, r_max);
   return tiles > packed ? tiles : packed;
 }
 
@@ -314,9 +308,9 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
       return MILORA_EUNSUPPORTED;
     if (!row_to_req && M > MILORA_MAX_DECODE_BATCH) return MILORA_ERANGE;
     if (M <= kStreamRows || !tiles_supported(M, d1, d2, true, X, W, Y))
-      // rows are independent: more than 128 of them run as slices (each re-reads W)
-      for (int64_t m0 = 0;; m0 += MILORA_MAX_DECODE_BATCH) {
-        const int mc = (int)(M - m0 < MILORA_MAX_DECODE_BATCH ? M - m0 : MILORA_MAX_DECODE_BATCH);
+      // (more rows on reductions too long for the tiles: rows are independent, slices of them each read W again)
+      for (int64_t m0 = 0;; m0 += kStreamRows) {
+        const int mc = (int)(M - m0 < kStreamRows ? M - m0 : kStreamRows);
         rc = routed_linear_packed((const bf16_t*)X + m0 * d1, mc, d1, d2, row_to_req ? row_to_req + m0 : nullptr,
                                   (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
                                   (bf16_t*)Y + m0 * d2, workspace, st);

@@ -62,8 +62,6 @@ constexpr int kTraceSlots = 16;             // time stamps per (workgroup, stage
 template <int MT> struct Cfg;
 template <> struct Cfg<1> { static constexpr int D = 12, NS = 6, CHAIN = 1, DELTA = 8192; };
 template <> struct Cfg<2> { static constexpr int D = 12, NS = 6, CHAIN = 1, DELTA = 8192; };
-template <> struct Cfg<4> { static constexpr int D = 12, NS = 6, CHAIN = 3, DELTA = 8192; };
-template <> struct Cfg<8> { static constexpr int D = 12, NS = 2, CHAIN = 3, DELTA = 2048; };
 
 // Polls after which a bounded wait inside a launch gives up; the launches that follow a change use the new value.
 std::atomic<int> g_wait_limit{kSpinLimit};
@@ -387,7 +385,7 @@ __global__ void __launch_bounds__(kThreads) decode_stream_kernel(const Params p)
   constexpr int kTileBytes = MT * 1024;                   // fp32 sums of one 16-column tile
   constexpr int kRedBytes = NSMAX * kTileBytes;
   constexpr int kDeltaBytes = Cfg<MT>::DELTA;
-  constexpr int kTBytes = MT == 8 ? 2048 : 4096;                       // summed shrinks t of the rows expanded ahead of the stage end
+  constexpr int kTBytes = 4096;                           // summed shrinks t of the rows expanded ahead of the stage end
   constexpr int kPool0 = kCtrlBytes + kRedBytes + kDeltaBytes + kTBytes;  // input chunks grow up from here, slots lie at the top
   static_assert(kSW % CHAIN == 0, "slots");
   static_assert(kLdsBytes - kSlots * kRedBytes - kPool0 >= 2 * kChunkBytes, "at least two input chunks next to the largest slots");
@@ -601,16 +599,12 @@ __global__ void __launch_bounds__(kThreads) decode_stream_kernel(const Params p)
       for (int a = 0; a < NSMAX; ++a)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[a][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // Sums of squares of the input rows over this wave's k blocks (normalisation).  Up to 32 rows the matrix cores
-      // form them: the product of an operand block with itself has them on its diagonal, one instruction per row
-      // tile and k block where the vector unit needs sixteen (the stream waves are bound by instruction issue).
-      constexpr bool kGramSS = MT <= 2;
-      float ss[MT];
-      f32x4 ssg[kGramSS ? MT : 1];
+      // Sums of squares of the input rows over this wave's k blocks (normalisation), from the matrix cores: the product of an
+      // operand block with itself has them on its diagonal, one instruction per row tile and k block where the vector
+      // unit needs sixteen (the stream waves are bound by instruction issue).
+      f32x4 ssg[MT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) ss[mt] = 0.f;
-#pragma unroll
-      for (int mt = 0; mt < (kGramSS ? MT : 1); ++mt) ssg[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int mt = 0; mt < MT; ++mt) ssg[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
       const int rounds = rounds_of(NS, NCH);
       // Ring rounds.  Slot s of a round holds tile s % NS of the wave's next k block; NS divides NSMAX and the
       // accumulator of slot s is s % NSMAX, so one piece of code serves every NS that divides NSMAX, and
@@ -666,15 +660,10 @@ __global__ void __launch_bounds__(kThreads) decode_stream_kernel(const Params p)
                 for (int mt = 0; mt < MT; ++mt) xb[mt] = u32x4{0u, 0u, 0u, 0u};
               }
               if (norm && cvalid) {
-                if constexpr (kGramSS) {
 #pragma unroll
-                  for (int mt = 0; mt < MT; ++mt)
-                    ssg[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xb[mt]), __builtin_bit_cast(bf16x8, xb[mt]),
-                                                                      ssg[mt], 0, 0, 0);
-                } else {
-#pragma unroll
-                  for (int mt = 0; mt < MT; ++mt) ss[mt] += sumsq8(xb[mt]);
-                }
+                for (int mt = 0; mt < MT; ++mt)
+                  ssg[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xb[mt]), __builtin_bit_cast(bf16x8, xb[mt]),
+                                                                    ssg[mt], 0, 0, 0);
               }
             }
             // Between stage ends only kSteady loads per wave stay in flight (the rest of the ring holds blocks that
@@ -733,7 +722,7 @@ __global__ void __launch_bounds__(kThreads) decode_stream_kernel(const Params p)
                 float* e = sl + ((a * MT + mt) * 4 + q) * 64 + lane;
                 *e = (pos == 0 ? 0.f : *e) + acc[a][mt][q];
               }
-        if constexpr (kGramSS) {
+        {
           // a lane holds rows 4 (lane / 16) .. + 3 of column lane % 16 of the product: the diagonal element of row
           // j = lane % 16 lies in the lane with lane / 16 == j / 4, at index j % 4
           const int j = lane & 15;
@@ -744,14 +733,6 @@ __global__ void __launch_bounds__(kThreads) decode_stream_kernel(const Params p)
               const float lo = (j & 1) ? g[1] : g[0], hi = (j & 1) ? g[3] : g[2];
               c.ss_part[w][mt * 16 + j] = (j & 2) ? hi : lo;
             }
-          }
-        } else {
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            float v = ss[mt];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            if (lane < 16) c.ss_part[w][mt * 16 + lane] = v;
           }
         }
         compiler_fence();
@@ -2072,9 +2053,8 @@ __global__ void __launch_bounds__(kThreads) decode_wide_kernel(const Params p) {
   }
 }
 
+static_assert(Cfg<1>::NS == Cfg<2>::NS, "tiles per workgroup and stage");
 int mt_for(int M) { return M <= 16 ? 1 : (M <= 32 ? 2 : (M <= 64 ? 4 : 8)); }
-int ns_max_for(int MT) { return MT <= 2 ? Cfg<2>::NS : (MT == 4 ? Cfg<4>::NS : Cfg<8>::NS); }
-
 
 // One workgroup per compute unit, all resident at once (the grid barrier relies on that).
 template <int MT>
@@ -2097,23 +2077,12 @@ int stream_grid() {
   return cached;
 }
 
-int grid_for(int MT) {
-  switch (MT) {
-    case 1: return stream_grid<1>();
-    case 2: return stream_grid<2>();
-    case 4: return stream_grid<4>();
-    default: return stream_grid<8>();
-  }
-}
+int grid_for(int MT) { return MT == 1 ? stream_grid<1>() : stream_grid<2>(); }
 
 template <bool TRACE>
 void launch_stream_t(const Params& p, int MT, int G, hipStream_t st) {
-  switch (MT) {
-    case 1: hipLaunchKernelGGL((decode_stream_kernel<1, TRACE>), dim3(G), dim3(kThreads), kLdsBytes, st, p); break;
-    case 2: hipLaunchKernelGGL((decode_stream_kernel<2, TRACE>), dim3(G), dim3(kThreads), kLdsBytes, st, p); break;
-    case 4: hipLaunchKernelGGL((decode_stream_kernel<4, TRACE>), dim3(G), dim3(kThreads), kLdsBytes, st, p); break;
-    default: hipLaunchKernelGGL((decode_stream_kernel<8, TRACE>), dim3(G), dim3(kThreads), kLdsBytes, st, p); break;
-  }
+  if (MT == 1) hipLaunchKernelGGL((decode_stream_kernel<1, TRACE>), dim3(G), dim3(kThreads), kLdsBytes, st, p);
+  else hipLaunchKernelGGL((decode_stream_kernel<2, TRACE>), dim3(G), dim3(kThreads), kLdsBytes, st, p);
 }
 
 int launch_stream(const Params& p, int MT, int G, hipStream_t st) {
@@ -2322,7 +2291,7 @@ int layer_decode_packed(const bf16_t* x, int B, int d, int F, const milora_layer
   const bool wide = MT >= 4;  // more than 32 rows: the kernel that cuts the reduction over the workgroups
   const int G = wide ? (MT == 4 ? wide_grid<4>() : wide_grid<8>()) : grid_for(MT);
   if (G <= 0) return hip_fail(hipGetLastError());
-  const int nsm = ns_max_for(MT);
+  const int nsm = Cfg<2>::NS;
   DecodeWs ws = carve_decode_ws(workspace, B, d, F, ad.r_max, B > 32);
   const int norm = (flags & MILORA_LAYER_RMSNORM) ? 1 : 0;
   Params p;
@@ -2473,7 +2442,7 @@ int static_scratch_status(int* status, hipStream_t st) {
   return decode_workspace_status(ptr, status, st);
 }
 
-// ---- one routed linear of M <= 128 rows on a packed weight ------------------------------------------
+// ---- one routed linear of up to kStreamRows rows on a packed weight -----------------------------------------------
 size_t routed_linear_packed_workspace_bytes(int M, int d1, int d2, int r_max) {
   (void)d2;
   return carve_decode_ws(nullptr, M, 32, d1, r_max, false, true).bytes;
@@ -2493,7 +2462,7 @@ int routed_linear_packed(const bf16_t* X, int M, int d1, int d2, const int32_t* 
   l.X = X; l.ldx = d1; l.K = d1; l.n_seg = 1;
   l.W[0] = W; l.N[0] = d2; l.site[0] = site; l.bias[0] = bias;
   l.out[0] = Y; l.ld_out[0] = d2;
-  if (!push_level(p, l, d2 >> 4, G, ns_max_for(MT))) return MILORA_ERANGE;
+  if (!push_level(p, l, d2 >> 4, G, Cfg<2>::NS)) return MILORA_ERANGE;
   return launch_stream(p, MT, G, st);
 }
 

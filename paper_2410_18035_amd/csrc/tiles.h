@@ -13,6 +13,7 @@ struct TilePlan {
   int S, steps;          // parts of the reduction, stages of 64 k per part
   size_t partial_bytes;  // fp32 partial tiles in the workspace (0 when S == 1)
 };
+constexpr int kStreamRows = 32;      // rows up to which a packed linear takes the weight-streaming kernel (decode.hip)
 constexpr int kMaxSplitUnits = 512;  // tiles x parts of a launch that cuts its reduction
 constexpr int kMaxParts = 8;         // of one reduction
 // The first bytes of a routed linear's workspace belong to control words: those of the stream kernels (decode.hip), then the

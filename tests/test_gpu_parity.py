@@ -253,6 +253,8 @@ def test_routed_linear_generic_ragged_shapes_and_ranks(dtype):
 
 @pytest.mark.parametrize("M", [1, 5, 16, 17, 32, 33, 64, 100, 128])
 def test_routed_linear_packed_batch_sizes(M):
+    """Both sides of the row counts where a packed call changes hands: one and two row tiles of the stream kernel, then the
+    64 x 64 and 128 x 128 tiles."""
     wl = small(dtype="bf16", d=512, F=1056, T=6, B=M, ranks=(8, 32, 64), tenants="uniform", seed=M)
     for site in (1, 5, 6):
         Y, ref = _linear_case(wl, site, w_layout=mb.W_PACKED, with_bias=(site == 5), seed=site)
@@ -261,8 +263,8 @@ def test_routed_linear_packed_batch_sizes(M):
 
 @pytest.mark.parametrize("d,F,site,M", [(4096, 64, 4, 20), (64, 11008, 6, 32), (2560, 96, 5, 70), (4096, 64, 0, 128)])
 def test_routed_linear_packed_sliced_reduction(d, F, site, M):
-    """Few output columns and a long reduction: the reduction is cut into slices handled by different
-    workgroups and summed by the last one to finish (4, 10, 2 and 4 slices here)."""
+    """Few output columns and a long reduction.  Up to 32 rows (the first two) the stream kernel's waves share it; above, it is
+    cut into parts handled by different workgroups and summed in part order by the last one to finish."""
     wl = small(dtype="bf16", d=d, F=F, T=5, B=M, ranks=(8, 32), tenants="uniform", seed=d + F)
     Y, ref = _linear_case(wl, site, w_layout=mb.W_PACKED, with_bias=True, seed=M)
     assert_rows_close(Y, ref, torch.bfloat16, f"d {d} F {F} site {site}")
@@ -273,7 +275,7 @@ def test_routed_linear_packed_sliced_reduction(d, F, site, M):
 def test_routed_linear_packed_unaligned_rank_and_row_map():
     wl = small(dtype="bf16", d=256, F=352, T=3, B=5, ranks=(5, 12, 16), tenants="uniform", seed=8)
     g = torch.Generator().manual_seed(4)
-    r2r = torch.randint(0, wl.B, (150,), generator=g)  # more than one 128-row slice
+    r2r = torch.randint(0, wl.B, (150,), generator=g)  # three row tiles, the last one ragged
     for site in (2, 4):
         Y, ref = _linear_case(wl, site, M=150, row_to_req=r2r, w_layout=mb.W_PACKED, seed=site)
         assert_rows_close(Y, ref, torch.bfloat16, f"site {site}")

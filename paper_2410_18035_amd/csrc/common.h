@@ -205,6 +205,7 @@ struct FewArgs {
   const void* x_res;
   float* h;
   const float* t;  // filled in by the launch
+  int col0;        // first column of the launch, the same
 };
 // t: scratch of [sites][M][r_max] floats
 int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t stream);

@@ -31,6 +31,9 @@ __device__ __forceinline__ f32x4 load4_end(const T* row, int k, int K) {
       if (k + e < K) v[e] = Elem<T>::load(row, k + e);
   return v;
 }
+// Columns of one launch: a grid has to stay below 2^32 threads (512 for 16 columns in the few-row kernel).
+constexpr int kLaunchCols = 1 << 26;
+
 __device__ __forceinline__ int pow2_above(int r) {
   int p = 1;
   while (p < r) p <<= 1;
@@ -109,7 +112,7 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
   __shared__ float ts[NW][16][kFuseRank];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int s0 = MODE == kFewGateUp ? 0 : blockIdx.y, n0 = blockIdx.x * 16;
+  const int s0 = MODE == kFewGateUp ? 0 : blockIdx.y, n0 = g.col0 + blockIdx.x * 16;
   const int d1 = g.d1;
   const bool fused = g.t == nullptr;
 
@@ -292,7 +295,7 @@ typedef GenCfg<64, 64, 32> GenLarge;
 constexpr int kGenLargeTiles = 128;
 
 template <typename T, class C, bool WIDE>
-__global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restrict__ X, int64_t M, int d1, int d2,
+__global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restrict__ X, int64_t M, int d1, int d2, int col0,
                                                            const int32_t* __restrict__ row_to_req, const T* __restrict__ W,
                                                            const T* __restrict__ bias, AdapterView ad, int site,
                                                            const int32_t* __restrict__ tenant_id,
@@ -304,7 +307,7 @@ __global__ void __launch_bounds__(C::T, 4) linear_tile_kernel(const T* __restric
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = w / (C::WM * C::WN), wm = w % (C::WM * C::WN) % C::WM, wn = w % (C::WM * C::WN) / C::WM;
   const int64_t m0 = (int64_t)blockIdx.y * C::BM;
-  const int n0 = blockIdx.x * C::BN;
+  const int n0 = col0 + blockIdx.x * C::BN;
 
   const T* src[C::Items];
   const int kq = tid % (C::SK / 4) * 4;
@@ -460,10 +463,15 @@ int launch_tile(const void* X, int64_t M, int d1, int d2, const int32_t* row_to_
     MILORA_HIP(hipFuncSetAttribute((const void*)linear_tile_kernel<T, C, WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LdsBytes));
     lds_set_for = dev;
   }
-  dim3 grid((unsigned)((d2 + C::BN - 1) / C::BN), (unsigned)((M + C::BM - 1) / C::BM));
-  hipLaunchKernelGGL((linear_tile_kernel<T, C, WIDE>), grid, dim3(C::T), C::LdsBytes, stream, (const T*)X, M, d1, d2, row_to_req,
-                     (const T*)W, (const T*)bias, ad, site, tenant_id, route, B, t, (T*)Y);
-  return check_launch();
+  int rc = MILORA_OK;
+  for (int64_t col0 = 0; col0 < d2 && !rc; col0 += kLaunchCols) {
+    const int cols = d2 - col0 < kLaunchCols ? (int)(d2 - col0) : kLaunchCols;
+    dim3 grid((unsigned)((cols + C::BN - 1) / C::BN), (unsigned)((M + C::BM - 1) / C::BM));
+    hipLaunchKernelGGL((linear_tile_kernel<T, C, WIDE>), grid, dim3(C::T), C::LdsBytes, stream, (const T*)X, M, d1, d2, (int)col0,
+                       row_to_req, (const T*)W, (const T*)bias, ad, site, tenant_id, route, B, t, (T*)Y);
+    rc = check_launch();
+  }
+  return rc;
 }
 
 }  // namespace
@@ -480,15 +488,21 @@ int launch_shrink(const void* X, int64_t ldx, int64_t M, int d1, int dtype, cons
 }
 
 template <typename T>
-static int launch_few_rows_t(const FewArgs& g, int sites, int mode, hipStream_t st) {
-  const dim3 grid((unsigned)((g.d2 + 15) / 16), (unsigned)sites);
-  switch (mode) {
-    case kFewPlain: hipLaunchKernelGGL((few_rows_kernel<T, kFewPlain>), grid, dim3(kFewT), 0, st, g); break;
-    case kFewResid: hipLaunchKernelGGL((few_rows_kernel<T, kFewResid>), grid, dim3(kFewT), 0, st, g); break;
-    case kFewGateUp: hipLaunchKernelGGL((few_rows_kernel<T, kFewGateUp>), dim3(grid.x), dim3(kFewT), 0, st, g); break;
-    default: hipLaunchKernelGGL((few_rows_kernel<T, kFewDown>), grid, dim3(kFewT), 0, st, g); break;
+static int launch_few_rows_t(FewArgs& g, int sites, int mode, hipStream_t st) {
+  int rc = MILORA_OK;
+  for (int64_t col0 = 0; col0 < g.d2 && !rc; col0 += kLaunchCols) {
+    const int cols = g.d2 - col0 < kLaunchCols ? (int)(g.d2 - col0) : kLaunchCols;
+    const dim3 grid((unsigned)((cols + 15) / 16), (unsigned)sites);
+    g.col0 = (int)col0;
+    switch (mode) {
+      case kFewPlain: hipLaunchKernelGGL((few_rows_kernel<T, kFewPlain>), grid, dim3(kFewT), 0, st, g); break;
+      case kFewResid: hipLaunchKernelGGL((few_rows_kernel<T, kFewResid>), grid, dim3(kFewT), 0, st, g); break;
+      case kFewGateUp: hipLaunchKernelGGL((few_rows_kernel<T, kFewGateUp>), dim3(grid.x), dim3(kFewT), 0, st, g); break;
+      default: hipLaunchKernelGGL((few_rows_kernel<T, kFewDown>), grid, dim3(kFewT), 0, st, g); break;
+    }
+    rc = check_launch();
   }
-  return check_launch();
+  return rc;
 }
 
 int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t st) {

@@ -442,7 +442,7 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
 int launch_shrink_tiles(const bf16_t* X, int64_t M, int d1, const int32_t* row_to_req, const AdapterView& ad, int site,
                         const int32_t* tenant_id, const uint8_t* route, int B, float* t, int2* row_lora, int* clear, hipStream_t stream) {
   const int parts = shrink_parts(M, d1);
-  const int64_t slice = (int64_t)1 << 30;  // rows per launch: the grid index stays well inside 32 bits
+  const int64_t slice = (int64_t)1 << 28;  // rows per launch: 512 threads for 64 rows, a grid has to stay below 2^32 threads
   for (int64_t r0 = 0; r0 < M; r0 += slice) {
     ShrinkArgs g{X + (size_t)r0 * d1, M - r0 < slice ? M - r0 : slice, r0, d1, site, B, row_to_req ? row_to_req + r0 : nullptr,
                  tenant_id, route, ad, t + (size_t)r0 * ad.r_max, (size_t)M * ad.r_max, row_lora ? row_lora + r0 : nullptr, clear};

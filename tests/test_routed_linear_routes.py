@@ -171,3 +171,21 @@ def test_tiles_work_whatever_the_workspace_holds(packed, M, d1, d2):
     for _ in range(2):
         assert torch.equal(run(dirty), clean)
     assert torch.equal(run(torch.randint(0, 256, (nbytes,), dtype=torch.uint8, device=DEV)), clean)
+
+
+@gpu
+@pytest.mark.parametrize("M", [1, 17])
+def test_any_shape_linears_wider_than_one_launch(M):
+    """A grid holds fewer than 2^32 threads: beyond 2^26 columns (of 16 each 512 threads) the launch is cut."""
+    d1, d2 = 1, (1 << 27) + 24
+    g = torch.Generator(device=DEV).manual_seed(61)
+    W = torch.empty(d2, d1, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)
+    X = torch.empty(M, d1, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)
+    A, B, rank = _adapters(1, d1, d2, (1,), 1.0, 62)
+    one = torch.zeros(1, dtype=torch.uint8, device=DEV)
+    Y = mb.milora_routed_linear(X, W, mb.AdapterTable.from_tensors(A, B, rank), 0, one.int(), one,
+                                torch.zeros(M, dtype=torch.int32, device=DEV))
+    for n in (0, (1 << 26) - 40, (1 << 27) - 40):
+        cols = slice(n, min(n + 80, d2))
+        ref = X.double() @ W[cols].double().T + (X.double() @ A[0][0].double()) @ B[0][0][:, cols].double()
+        assert (Y[:, cols].double() - ref).abs().max() <= 2e-2 * ref.abs().max()

@@ -311,8 +311,9 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
       // (more rows on reductions too long for the tiles: rows are independent, slices of them each read W again)
       for (int64_t m0 = 0;; m0 += kStreamRows) {
         const int mc = (int)(M - m0 < kStreamRows ? M - m0 : kStreamRows);
+        const int64_t b0 = row_to_req ? 0 : m0;  // (unmapped rows: the slice's requests)
         rc = routed_linear_packed((const bf16_t*)X + m0 * d1, mc, d1, d2, row_to_req ? row_to_req + m0 : nullptr,
-                                  (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
+                                  (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id + b0, route + b0, (int)(B - b0),
                                   (bf16_t*)Y + m0 * d2, workspace, st);
         if (rc || m0 + mc >= M) return rc;
       }

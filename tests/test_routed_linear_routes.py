@@ -189,3 +189,29 @@ def test_any_shape_linears_wider_than_one_launch(M):
         cols = slice(n, min(n + 80, d2))
         ref = X.double() @ W[cols].double().T + (X.double() @ A[0][0].double()) @ B[0][0][:, cols].double()
         assert (Y[:, cols].double() - ref).abs().max() <= 2e-2 * ref.abs().max()
+
+
+@gpu
+def test_slices_of_unmapped_packed_rows_keep_their_requests():
+    """A reduction of 2^23 is beyond the tiles' offsets: packed rows above 32 go through the stream kernel in slices."""
+    d1, d2, M, r = 1 << 23, 16, 36, 8
+    g = torch.Generator(device=DEV).manual_seed(71)
+    rnd = lambda *s, sigma=1.0: torch.empty(*s, dtype=torch.bfloat16, device=DEV).normal_(0, sigma, generator=g)
+    W, X = rnd(d2, d1, sigma=d1 ** -0.5), rnd(M, d1)
+    A, B, rank = _adapters(2, d1, d2, (r,), 0.02, 72)
+    tid = torch.tensor([1 if m >= 32 else 0 for m in range(M)], dtype=torch.int32)
+    route = torch.zeros(M, dtype=torch.uint8)
+    route[:2] = mb.ROUTE_NONE
+    ws = torch.zeros(mb.routed_linear_workspace_bytes(M, d1, d2, r), dtype=torch.uint8, device=DEV)
+    Y = mb.milora_routed_linear(X, mb.milora_pack_weight(W), mb.AdapterTable.from_tensors(A, B, rank), 0, tid.to(DEV),
+                                route.to(DEV), w_layout=mb.W_PACKED, d2=d2, workspace=ws)
+    assert mb.milora_packed_workspace_status(ws) == 0
+    rows = [0, 1, 2, 31, 32, 33, 35]
+    for m in rows:
+        x = X[m].double()
+        ref = torch.stack([x @ W[n].double() for n in range(d2)])
+        if route[m] == 0:
+            delta = torch.stack([x @ A[tid[m]][0][:, c].double() for c in range(r)]) @ B[tid[m]][0].double()
+            assert delta.abs().max() > 0.2 * ref.abs().max()
+            ref = ref + delta
+        assert_rows_close(Y[m:m + 1], ref[None].cpu().numpy(), torch.bfloat16, f"row {m}")

@@ -150,8 +150,10 @@ int milora_route(const void *H, int64_t M_tok, int d, int dtype, const int32_t *
  * Sec. 3.3: a request's LoRA term is present only at the site its route selected):
  *   b = row_to_req ? row_to_req[m] : m,  t = tenant_id[b]
  *   Y[m] = X[m] W + bias + [route[b] selects site] (X[m] W^A_{t,site}) W^B_{t,site}
- * Accumulation is fp32; the low-rank intermediate stays fp32 and is added to the fp32 base result
- * before the single rounding to `dtype`.
+ * Accumulation is fp32; the low-rank intermediate is formed in fp32 and its product added to the fp32 base result
+ * before the single rounding to `dtype`.  It enters that product in fp32, on row-major bf16 weights and 64 rows or
+ * more as the sum of two bf16 values (about 17 bits of it).  A tenant's Inf and NaN reach that tenant's rows only, in
+ * calls of the latter kind all rows of a 64-, 128- or 256-row tile.
  *
  *   X           device [M][d1], `dtype`
  *   row_to_req  device [M] int32 or NULL.  NULL means row m belongs to request m and needs M == B
@@ -168,16 +170,18 @@ int milora_route(const void *H, int64_t M_tok, int d, int dtype, const int32_t *
  * d1 % 32 != 0 or d2 % 16 != 0, or with X, W, bias or Y not 16-byte aligned), EWORKSPACE, EHIP.
  */
 size_t milora_routed_linear_workspace_bytes(int64_t M, int d1, int d2, int r_max);
-/* Which kernel family milora_routed_linear runs for these sizes when its pointers are 16-byte aligned (host
- * logic only, no device work): MILORA_KERNEL_STREAM (packed weights: up to 32 rows the weight-streaming kernel, more rows
- * the matrix-core tiles), MILORA_KERNEL_TILES (row-major bf16 weights, M >= 64, d1 % 64 == 0, d2 % 16 == 0: matrix-core
- * tiles of 64 x 64, 128 x 128 or 256 x 256 by the sizes) or MILORA_KERNEL_GENERIC (everything else: fp32, any shape, and
- * fewer rows than 64, which take the 64 x 64 matrix-core tiles where the widths allow it).  Negative status for
- * arguments milora_routed_linear itself would reject. */
+/* Which family of calls these sizes belong to when the pointers are 16-byte aligned (host logic only, no device work):
+ * MILORA_KERNEL_STREAM (packed weights), MILORA_KERNEL_TILES (row-major bf16 weights, M >= 64, d1 % 64 == 0, d2 % 16 == 0) or
+ * MILORA_KERNEL_GENERIC (everything else).  Which kernel runs, by the same rules the call itself follows, is
+ * milora_routed_linear_tile's answer: the side of the matrix-core tiles (64, 128 or 256), or 0 where there are none (the
+ * weight-streaming kernel: packed, up to 32 rows; the any-shape kernels: fp32 and widths the others do not take).  Packed
+ * weights above 32 rows and row-major bf16 ones below 64 run on tiles of 64 or 128.  Both: negative status for arguments
+ * milora_routed_linear itself would reject. */
 #define MILORA_KERNEL_GENERIC 0
 #define MILORA_KERNEL_STREAM 1
 #define MILORA_KERNEL_TILES 2
 int milora_routed_linear_kernel(int64_t M, int d1, int d2, int dtype, int w_layout);
+int milora_routed_linear_tile(int64_t M, int d1, int d2, int dtype, int w_layout);
 int milora_routed_linear(const void *X, int64_t M, int d1, int d2, int dtype,
                          const int32_t *row_to_req, const void *W, int w_layout, const void *bias,
                          const milora_adapters *adapters, int site, const int32_t *tenant_id,

@@ -31,7 +31,7 @@ MAX_DECODE_BATCH = 128
 EXPORTS = (
     "milora_version", "milora_status_string", "milora_last_hip_error",
     "milora_route_workspace_bytes", "milora_route",
-    "milora_routed_linear_workspace_bytes", "milora_routed_linear_kernel", "milora_routed_linear",
+    "milora_routed_linear_workspace_bytes", "milora_routed_linear_kernel", "milora_routed_linear_tile", "milora_routed_linear",
     "milora_layer_decode_workspace_bytes", "milora_layer_decode", "milora_layer_decode_noalloc",
     "milora_layer_decode_profile", "milora_layer_decode_trace_bytes", "milora_layer_decode_trace",
     "milora_pack_weight", "milora_packed_workspace_status", "milora_set_wait_limit",
@@ -79,6 +79,8 @@ def lib() -> ctypes.CDLL:
         L.milora_routed_linear_workspace_bytes.argtypes = [i64, i32, i32, i32]
         L.milora_routed_linear_kernel.restype = i32
         L.milora_routed_linear_kernel.argtypes = [i64, i32, i32, i32, i32]
+        L.milora_routed_linear_tile.restype = i32
+        L.milora_routed_linear_tile.argtypes = [i64, i32, i32, i32, i32]
         L.milora_routed_linear.restype = i32
         L.milora_routed_linear.argtypes = [vp, i64, i32, i32, i32, vp, vp, i32, vp, ctypes.POINTER(_Adapters), i32,
                                            vp, vp, i32, vp, vp, sz, vp]
@@ -235,6 +237,12 @@ KERNEL_GENERIC, KERNEL_STREAM, KERNEL_TILES = 0, 1, 2
 def milora_routed_linear_kernel(M: int, d1: int, d2: int, dtype: torch.dtype, w_layout: int = W_ROWMAJOR) -> int:
     code = {torch.bfloat16: 0, torch.float32: 1}[dtype] if not isinstance(dtype, int) else dtype
     return int(lib().milora_routed_linear_kernel(M, d1, d2, code, w_layout))
+
+
+def milora_routed_linear_tile(M: int, d1: int, d2: int, dtype: torch.dtype, w_layout: int = W_ROWMAJOR) -> int:
+    """Side of the matrix-core tiles the call runs on (64, 128, 256), 0 where it runs on none."""
+    code = {torch.bfloat16: 0, torch.float32: 1}[dtype] if not isinstance(dtype, int) else dtype
+    return int(lib().milora_routed_linear_tile(M, d1, d2, code, w_layout))
 
 
 def milora_routed_linear(X: torch.Tensor, W: torch.Tensor, adapters: AdapterTable, site: int,

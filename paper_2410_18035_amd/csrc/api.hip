@@ -239,6 +239,30 @@ int check_adapters(const milora_adapters* a) {
   return MILORA_OK;
 }
 
+// How milora_routed_linear serves a call whose arguments it has accepted.
+struct LinearPlan {
+  int kind;        // MILORA_KERNEL_GENERIC, MILORA_KERNEL_STREAM, or MILORA_KERNEL_TILES: matrix-core tiles of any size
+  bool small, large;
+  int64_t slice;   // rows of a launch of the tiles
+  TilePlan tiles;  // of the first slice
+};
+
+LinearPlan plan_linear(int64_t M, int d1, int d2, int dtype, bool packed, const void* X, const void* W, const void* Y) {
+  LinearPlan p{MILORA_KERNEL_GENERIC, false, false, M, TilePlan{}};
+  if (dtype != MILORA_BF16) return p;
+  p.small = tiles_supported(M, d1, d2, packed, X, W, Y);
+  p.large = !packed && prefill_supported(M, d1, d2, X, W, Y);
+  if (packed && (M <= kStreamRows || !p.small)) {
+    p.kind = MILORA_KERNEL_STREAM;
+  } else if (p.small || p.large) {
+    p.kind = MILORA_KERNEL_TILES;
+    // more rows than a launch of the smaller tiles takes, and no larger ones for this weight: slices of rows
+    if (!p.large && M > kTileMaxRows) p.slice = kTileMaxRows;
+    p.tiles = plan_tiles(p.slice, d1, d2, p.small, p.large);
+  }
+  return p;
+}
+
 bool packed_shape_ok(int d1, int d2) { return d1 % 32 == 0 && d2 % 16 == 0; }
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
@@ -285,6 +309,15 @@ extern "C" int milora_routed_linear_kernel(int64_t M, int d1, int d2, int dtype,
   return MILORA_KERNEL_GENERIC;
 }
 
+extern "C" int milora_routed_linear_tile(int64_t M, int d1, int d2, int dtype, int w_layout) {
+  const int kernel = milora_routed_linear_kernel(M, d1, d2, dtype, w_layout);
+  if (kernel < 0) return kernel;
+  const void* aligned = (const void*)(uintptr_t)256;
+  const LinearPlan p = plan_linear(M, d1, d2, dtype, w_layout == MILORA_W_PACKED, aligned, aligned, aligned);
+  if (p.kind != MILORA_KERNEL_TILES) return 0;
+  return p.tiles.shape == kTiles256 ? 256 : p.tiles.shape == kTiles128 ? 128 : 64;
+}
+
 extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, int dtype, const int32_t* row_to_req,
                                     const void* W, int w_layout, const void* bias, const milora_adapters* adapters,
                                     int site, const int32_t* tenant_id, const uint8_t* route, int B, void* Y,
@@ -307,51 +340,45 @@ extern "C" int milora_routed_linear(const void* X, int64_t M, int d1, int d2, in
         (bias && !aligned16(bias)))
       return MILORA_EUNSUPPORTED;
     if (!row_to_req && M > MILORA_MAX_DECODE_BATCH) return MILORA_ERANGE;
-    if (M <= kStreamRows || !tiles_supported(M, d1, d2, true, X, W, Y))
-      // (more rows on reductions too long for the tiles: rows are independent, slices of them each read W again)
-      for (int64_t m0 = 0;; m0 += kStreamRows) {
-        const int mc = (int)(M - m0 < kStreamRows ? M - m0 : kStreamRows);
-        const int64_t b0 = row_to_req ? 0 : m0;  // (unmapped rows: the slice's requests)
-        rc = routed_linear_packed((const bf16_t*)X + m0 * d1, mc, d1, d2, row_to_req ? row_to_req + m0 : nullptr,
-                                  (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id + b0, route + b0, (int)(B - b0),
-                                  (bf16_t*)Y + m0 * d2, workspace, st);
-        if (rc || m0 + mc >= M) return rc;
-      }
   }
+  const LinearPlan pl = plan_linear(M, d1, d2, dtype, packed, X, W, Y);
+  if (pl.kind == MILORA_KERNEL_STREAM)
+    // (more rows on reductions too long for the tiles: rows are independent, slices of them each read W again)
+    for (int64_t m0 = 0;; m0 += kStreamRows) {
+      const int mc = (int)(M - m0 < kStreamRows ? M - m0 : kStreamRows);
+      const int64_t b0 = row_to_req ? 0 : m0;  // (unmapped rows: the slice's requests)
+      rc = routed_linear_packed((const bf16_t*)X + m0 * d1, mc, d1, d2, row_to_req ? row_to_req + m0 : nullptr,
+                                (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id + b0, route + b0, (int)(B - b0),
+                                (bf16_t*)Y + m0 * d2, workspace, st);
+      if (rc || m0 + mc >= M) return rc;
+    }
   int* const cnt = (int*)((char*)workspace + kTileCtrlOffset);
   float* const t = (float*)((char*)workspace + kStreamCtrlBytes);
-  if (dtype == MILORA_BF16) {
-    const bool large = !packed && prefill_supported(M, d1, d2, X, W, Y);
-    if (large || tiles_supported(M, d1, d2, packed, X, W, Y)) {
-      const int parts = shrink_parts(M, d1);
-      const size_t t_stride = (size_t)M * ad.r_max;
-      int2* const looked_up = (int2*)((char*)t + align_up(t_stride * sizeof(float) * parts, 256));
-      float* const partial = (float*)((char*)looked_up + align_up((size_t)M * sizeof(int2), 256));
-      // Where the 256 x 256 kernel is no choice, the LoRA term is added in fp32 row by row: few rows and packed weights, where many
-      // tenants meet, and weights beyond that kernel's offsets.
-      int2* const row_lora = large ? nullptr : looked_up;
-      // Part counters start from zero in every call: what the workspace held before does not matter here.
-      int* const clear = row_lora || plan_tiles(M, d1, d2, true).S > 1 ? cnt : nullptr;
-      rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, row_lora, clear, st);
-      if (rc) return rc;
-      // more rows than a launch of the smaller tiles takes, and no larger ones for this layout: slices of rows
-      const int64_t slice = large ? M : kTileMaxRows;
-      for (int64_t m0 = 0; m0 < M; m0 += slice) {
-        const int64_t mc = M - m0 < slice ? M - m0 : slice;
-        const TilePlan pl = plan_tiles(mc, d1, d2, large);
-        const bf16_t* const x = (const bf16_t*)X + (size_t)m0 * d1;
-        bf16_t* const y = (bf16_t*)Y + (size_t)m0 * d2;
-        const int32_t* const map = row_to_req ? row_to_req + m0 : nullptr;
-        if (pl.shape == kTiles256)
-          rc = routed_linear_prefill(x, mc, d1, d2, map, (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B,
-                                     t, y, st);
-        else
-          rc = routed_linear_tiles(x, mc, d1, d2, map, (const bf16_t*)W, packed, row_lora ? row_lora + m0 : nullptr, (const bf16_t*)bias, ad, site, tenant_id,
-                                   route, B, t + (size_t)m0 * ad.r_max, t_stride, parts, pl, cnt, partial, y, st);
-        if (rc) return rc;
-      }
-      return MILORA_OK;
+  if (pl.kind == MILORA_KERNEL_TILES) {
+    const int parts = shrink_parts(M, d1);
+    const size_t t_stride = (size_t)M * ad.r_max;
+    int2* const looked_up = (int2*)((char*)t + align_up(t_stride * sizeof(float) * parts, 256));
+    float* const partial = (float*)((char*)looked_up + align_up((size_t)M * sizeof(int2), 256));
+    // Where the 256 x 256 kernel is no choice, the LoRA term is added in fp32 row by row: few rows and packed weights, where many
+    // tenants meet, and weights beyond that kernel's offsets.
+    int2* const row_lora = pl.large ? nullptr : looked_up;
+    // Part counters start from zero in every call: what the workspace held before does not matter here.
+    int* const clear = row_lora || pl.tiles.S > 1 ? cnt : nullptr;
+    rc = launch_shrink_tiles((const bf16_t*)X, M, d1, row_to_req, ad, site, tenant_id, route, B, t, row_lora, clear, st);
+    for (int64_t m0 = 0; m0 < M && !rc; m0 += pl.slice) {
+      const int64_t mc = M - m0 < pl.slice ? M - m0 : pl.slice;
+      const TilePlan tiles = mc == pl.slice ? pl.tiles : plan_tiles(mc, d1, d2, pl.small, pl.large);
+      const bf16_t* const x = (const bf16_t*)X + (size_t)m0 * d1;
+      bf16_t* const y = (bf16_t*)Y + (size_t)m0 * d2;
+      const int32_t* const map = row_to_req ? row_to_req + m0 : nullptr;
+      if (tiles.shape == kTiles256)
+        rc = routed_linear_prefill(x, mc, d1, d2, map, (const bf16_t*)W, (const bf16_t*)bias, ad, site, tenant_id, route, B, t, y, st);
+      else
+        rc = routed_linear_tiles(x, mc, d1, d2, map, (const bf16_t*)W, packed, row_lora ? row_lora + m0 : nullptr,
+                                 (const bf16_t*)bias, ad, site, tenant_id, route, B, t + (size_t)m0 * ad.r_max, t_stride, parts,
+                                 tiles, cnt, partial, y, st);
     }
+    return rc;
   }
   return launch_linear_generic(X, M, d1, d2, dtype, row_to_req, W, bias, ad, site, tenant_id, route, B, t, Y, st);
 }

@@ -23,8 +23,9 @@ constexpr int kStreamCtrlBytes = 16384;
 constexpr int kTileCtrlBytes = kMaxSplitUnits * (int)sizeof(int);
 constexpr int kTileCtrlOffset = kStreamCtrlBytes - kTileCtrlBytes;
 
-// `large`: the 256 x 256 kernel is a choice (row-major weights, 64 rows or more); M up to kTileMaxRows, else it is taken.
-TilePlan plan_tiles(int64_t M, int d1, int d2, bool large);
+// `small`: the tiles of tiles.hip are a choice up to kTileMaxRows rows (tiles_supported); `large`: the 256 x 256 kernel is one
+// (row-major weights, 64 rows or more).  At least one of them.
+TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large);
 // The most partial_bytes over the plans of all calls of up to these sizes; never less for a larger size.
 size_t partial_bytes_bound(int64_t M, int d1, int d2);
 bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y);

@@ -578,7 +578,7 @@ int launch_tiles(const TParams& p, hipStream_t st) {
 // (two workgroups share it: half the rate each), 0.58 us for a 128 x 128 one and 1.25 .. 1.75 us (few .. all units busy:
 // the L2 is shared) for a 256 x 256 one; workgroups beyond 256 wait for a second turn; cutting the reduction costs the
 // partial tiles and the last workgroup's sums (M = 64 on 4096 x 4096: one part 25.0 us a call, two 19.8, four 16.4, six 22.2).
-TilePlan plan_tiles(int64_t M, int d1, int d2, bool large) {
+TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large) {
   const int KT = (d1 + 63) / 64;
   TilePlan best{};
   int64_t best_t = INT64_MAX;
@@ -592,12 +592,12 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool large) {
     best = TilePlan{shape, (int)tm, (int)tn, (KT + steps - 1) / steps, steps, 0};  // (no empty part)
     if (best.S > 1) best.partial_bytes = (size_t)(tm * tn) * best.S * side * side * sizeof(float);
   };
-  if (M <= kTileMaxRows)
+  if (small && M <= kTileMaxRows)
     for (int S = 1; S <= kMaxParts; ++S) {
       offer(kTiles64, 64, 26, 200, S, 400 + 70 * S);
       offer(kTiles128, 128, 58, 400, S, 250 + 220 * S);
     }
-  if (large || M > kTileMaxRows) {
+  if (large) {
     const int64_t tiles = ((M + 255) / 256) * ((d2 + 255) / 256);
     offer(kTiles256, 256, 125 + 50 * (tiles < 256 ? tiles : 256) / 256, 800, 1, 0);
   }
@@ -621,6 +621,8 @@ size_t partial_bytes_bound(int64_t M, int d1, int d2) {
 
 bool tiles_supported(int64_t M, int d1, int d2, bool packed, const void* X, const void* W, const void* Y) {
   if (M < 1 || d2 % 16 != 0 || d1 % (packed ? 32 : 64) != 0) return false;
+  const int64_t rows = M < kTileMaxRows ? M : kTileMaxRows;
+  if (((rows + 63) / 64) * (((int64_t)d2 + 63) / 64) >= 1 << 22) return false;  // a grid has to stay below 2^32 threads
   if ((((uintptr_t)X | (uintptr_t)W) & 15) != 0 || ((uintptr_t)Y & 7) != 0) return false;
   return (uint64_t)d1 * 128u * 2u < (1ull << 31);  // byte offsets inside a tile's lines
 }

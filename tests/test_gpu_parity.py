@@ -335,9 +335,8 @@ def _segments(M, B, seed):
 
 @pytest.mark.parametrize("site", [0, 2, 4, 6])
 def test_routed_linear_many_rows_matrix_core_tiles(site):
-    """Row-major bf16 weights with several hundred rows take the matrix-core tile kernel: three row tiles with
-    a ragged last one, one to three column tiles with a ragged last one, prompts of several tenants (ranks
-    5..64) meeting inside a tile, bias on two of the sites."""
+    """Several hundred rows of row-major bf16 weights on the 64 x 64 matrix-core tiles: a ragged last row tile, whole and
+    ragged column tiles, prompts of several tenants (ranks 5..64) meeting inside a tile, bias on two of the sites."""
     wl = small(dtype="bf16", d=192, F=576, T=5, B=9, ranks=(5, 16, 32, 64), tenants="uniform", seed=31)
     M = 700
     d1, d2 = synth.site_dims(site, wl.d, wl.F)

@@ -6,7 +6,7 @@ import torch
 import oracle
 from paper_2410_18035_amd import binding as mb
 from paper_2410_18035_amd import synth
-from tests.util import assert_rows_close, oracle_adapters
+from tests.util import assert_rows_close, oracle_adapters, to_f64
 
 DEV = "cuda:0"
 gpu = pytest.mark.gpu
@@ -215,3 +215,65 @@ def test_slices_of_unmapped_packed_rows_keep_their_requests():
             assert delta.abs().max() > 0.2 * ref.abs().max()
             ref = ref + delta
         assert_rows_close(Y[m:m + 1], ref[None].cpu().numpy(), torch.bfloat16, f"row {m}")
+
+
+def test_tile_query_follows_the_dispatch():
+    """Which matrix-core tiles a call runs on, at the borders of the rules."""
+    k, bf, f32 = mb.milora_routed_linear_tile, torch.bfloat16, torch.float32
+    assert [k(M, 4096, 4096, bf, mb.W_PACKED) for M in (1, 32, 33)] == [0, 0, 64]
+    assert k(96, 4096, 11008, bf, mb.W_PACKED) == 128 and k(32768, 4096, 11008, bf, mb.W_PACKED) == 128
+    assert [k(M, 64, 16, bf) for M in (1, 63, 64, 4096, 4097)] == [64, 64, 64, 64, 256]
+    assert k(777, 4096, 4096, bf) == 128 and k(777, 4096, 11008, bf) == 256 and k(32768, 4096, 4096, bf) == 256
+    assert k(700, 96, 528, bf) == 0 and k(700, 192, 520, bf) == 0 and k(700, 192, 528, f32) == 0
+    assert k(5000, 1 << 18, 1 << 13, bf) in (64, 128)  # a weight of 4 GiB: beyond the 256 x 256 kernel's offsets
+    assert k(40, 1 << 23, 16, bf, mb.W_PACKED) == 0 and k(40, 1 << 23, 16, bf) == 0  # beyond the smaller tiles' offsets
+    assert k(4096, 64, 1 << 23, bf) == 256  # more smaller tiles than a grid of fewer than 2^32 threads holds
+    assert k(32, 4096, 4096, f32, mb.W_PACKED) == -3 and k(0, 8, 8, f32) == -1 and k(8, 8, 8, f32, 5) == -1
+
+
+@gpu
+@pytest.mark.parametrize("M,d1,d2,ranks,T,spread", [
+    (4097, 64, 272, (5, 40), 7, "segments"),     # one row in the last row tile, a second block of 32 ranks, ranks of any size
+    (4400, 192, 528, (16, 64, 33), 5, "segments"),  # a ragged last row tile, three column tiles, a ragged one, r_max % 4 == 0
+    (4400, 128, 352, (8, 24), 20, "scattered"),  # tenants of neighbouring rows differ
+    (4300, 64, 48, (256, 3), 3, "segments"),     # the largest rank, eight blocks of 32, one narrow column tile
+    (8193, 320, 272, (7,), 2, "none"),           # unmapped rows, r_max % 4 != 0
+])
+def test_routed_linear_256_tiles(M, d1, d2, ranks, T, spread):
+    """The 256 x 256 kernel and the 64-row shrink blocks in front of it, with bias, against the fp64 oracle."""
+    assert mb.milora_routed_linear_tile(M, d1, d2, torch.bfloat16) == 256
+    g = torch.Generator().manual_seed(M + d1)
+    rnd = lambda *s, sigma: (torch.randn(*s, generator=g) * sigma).to(torch.bfloat16).to(DEV)
+    X, W, bias = rnd(M, d1, sigma=1.0), rnd(d2, d1, sigma=d1 ** -0.5), rnd(d2, sigma=0.1)
+    A, B, rank = _adapters(T, d1, d2, ranks, 0.12, M)
+    site, nreq = 4, M if spread == "none" else T + 2
+    tid = torch.arange(nreq, dtype=torch.int32) % T
+    route = torch.randint(0, 7, (nreq,), generator=g).to(torch.uint8)
+    route[::2] = site
+    r2r = {"segments": torch.sort(torch.randint(0, nreq, (M,), generator=g))[0], "none": None,
+           "scattered": torch.randint(0, nreq, (M,), generator=g)}[spread]
+    r2r = None if r2r is None else r2r.to(torch.int32)
+    Y = mb.milora_routed_linear(X, W, mb.AdapterTable.from_tensors(A, B, rank), site, tid.to(DEV), route.to(DEV),
+                                None if r2r is None else r2r.to(DEV), bias=bias)
+    ref = oracle.routed_linear(synth.as_numpy(X), synth.as_numpy(W), oracle.Adapters(
+        [[synth.as_numpy(a) for a in row] for row in A], [[synth.as_numpy(b) for b in row] for row in B], rank), site, tid.numpy(),
+        route.numpy(), row_to_req=None if r2r is None else r2r.numpy(), bias=synth.as_numpy(bias))
+    assert_rows_close(Y, ref, torch.bfloat16)
+
+
+@gpu
+def test_routed_linear_256_tiles_small_integers_bit_exact():
+    d1, d2, T, r, M, site = 64, 272, 3, 4, 4200, 1
+    rnd = lambda shape, lo, hi, seed: synth.small_int_tensor(shape, lo, hi, torch.bfloat16, seed, DEV)
+    assert mb.milora_routed_linear_tile(M, d1, d2, torch.bfloat16) == 256
+    X, W = rnd((M, d1), -2, 2, 2), rnd((d2, d1), -1, 1, 1)
+    A, B = [[rnd((d1, r), -1, 1, 300 + t)] * 7 for t in range(T)], [[rnd((r, d2), -1, 1, 400 + t)] * 7 for t in range(T)]
+    tid = torch.tensor([0, 1, 2, 2, 1, 0], dtype=torch.int32)
+    route = torch.tensor([site, 0, site, site, 3, site], dtype=torch.uint8)
+    r2r = (torch.arange(M) * 6 // M).to(torch.int32)
+    Y = mb.milora_routed_linear(X, W, mb.AdapterTable.from_tensors(A, B, [r] * T), site, tid.to(DEV), route.to(DEV), r2r.to(DEV))
+    ref = oracle.routed_linear(synth.as_numpy(X), synth.as_numpy(W), oracle.Adapters(
+        [[synth.as_numpy(a) for a in row] for row in A], [[synth.as_numpy(b) for b in row] for row in B], [r] * T), site,
+        tid.numpy(), route.numpy(), row_to_req=r2r.numpy())
+    assert (abs(ref) <= 256).all()
+    assert (to_f64(Y) == ref).all()

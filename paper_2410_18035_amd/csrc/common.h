@@ -181,7 +181,7 @@ int launch_linear_generic(const void* X, int64_t M, int d1, int d2, int dtype, c
 
 // The same for up to kFewRows rows, with the glue of a layer's decode step in its store.
 constexpr int kFewRows = 16;
-constexpr int kFuseRank = 16;  // ranks up to here are shrunk inside the launch
+constexpr int kFuseRank = 16;  // the largest rank that can be shrunk inside the launch
 enum FewMode {
   kFewPlain,   // Y[i] = the linear at site[i], i < sites
   kFewResid,   // h = x_res + linear (fp32); Y[0] = h rounded, if given

@@ -88,9 +88,9 @@ __global__ void __launch_bounds__(kShrinkT) shrink_rows_kernel(const T* __restri
 
 // ---- few rows: up to 16 --------------------------------------------------------------------------------------------
 // A workgroup takes 16 columns of one linear (gate and up: of both) and the whole reduction, dealt to its eight waves in
-// blocks of 16 k that go straight from global memory into matrix operands; the waves' sums meet in LDS.  Ranks up to
-// kFuseRank are shrunk here too, each wave over its share of k (every workgroup does it again: the sums of a row are
-// 16 times less than the workgroup's share of the linear or about as many), others come from shrink_rows_kernel.
+// blocks of 16 k that go straight from global memory into matrix operands; the waves' sums meet in LDS.  Where rows, ranks
+// and widths are small the shrinks are formed here too (fuse_shrink), each wave over its share of k and one row after
+// the other, again in every workgroup; else they come from shrink_rows_kernel.
 // The layer's glue is part of the store: a decode step of a layer is four launches instead of eighteen.
 // Bound: launches and the chain of dependent loads (route -> adapter tables -> A) of each.  A decode step of 4 rows
 // through the 256 x 688 fp32 layer, rank 8: 284 us with eighteen launches, 24.8 us with these.
@@ -505,10 +505,23 @@ static int launch_few_rows_t(FewArgs& g, int sites, int mode, hipStream_t st) {
   return rc;
 }
 
+// Shrinks inside the launch spare one of its own (3 to 4 us) and cost every wave about 0.7 us per routed row and round trip, a trip
+// taking d1 / 8 x rank in pieces of 64 lanes x 8 loads.  With every row routed the two meet at some 10 trips (fp32, 8 rows, 512 x
+// 1376, rank 8: 11.3 us a call inside, 12.7 apart; 8 rows, 1000 x 2730: 16.6 and 13.2; 16 rows, 4100 x 11010, rank 16: 306 and
+// 59), with one site a request, as in a layer's step, at some 30 (16 rows, d = 512: 40.2 and 45.3 us a step; d = 1000, rank 8:
+// 61.6 and 63.0, rank 16: 80.6 and 70.0): the line lies between.
+static bool fuse_shrink(int M, int d1, int r_max) {
+  if (r_max > kFuseRank) return false;
+  int rpad = 1;
+  while (rpad < r_max) rpad <<= 1;
+  const int64_t trip = 8 * 64 * 8, work = (int64_t)d1 * rpad;
+  return M * (work > trip ? work : trip) <= 16 * trip;
+}
+
 int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t st) {
   FewArgs g = args;
   g.t = nullptr;
-  if (g.ad.r_max > kFuseRank) {
+  if (!fuse_shrink(g.M, g.d1, g.ad.r_max)) {
     const int rc = launch_shrink(g.X, g.ldx, g.M, g.d1, dtype, g.row_to_req, g.ad, g.site[0], sites, g.tenant_id, g.route, g.B, t, st);
     if (rc) return rc;
     g.t = t;

@@ -152,8 +152,8 @@ int milora_route(const void *H, int64_t M_tok, int d, int dtype, const int32_t *
  *   Y[m] = X[m] W + bias + [route[b] selects site] (X[m] W^A_{t,site}) W^B_{t,site}
  * Accumulation is fp32; the low-rank intermediate is formed in fp32 and its product added to the fp32 base result
  * before the single rounding to `dtype`.  It enters that product in fp32, on row-major bf16 weights and 64 rows or
- * more as the sum of two bf16 values (about 17 bits of it).  A tenant's Inf and NaN reach that tenant's rows only, in
- * calls of the latter kind all rows of a 64-, 128- or 256-row tile.
+ * more as the sum of two bf16 values (about 17 bits of it).  Inf and NaN in a tenant's matrices reach that
+ * tenant's rows only.
  *
  *   X           device [M][d1], `dtype`
  *   row_to_req  device [M] int32 or NULL.  NULL means row m belongs to request m and needs M == B

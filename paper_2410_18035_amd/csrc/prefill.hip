@@ -11,7 +11,7 @@
 // refilled from there on, so that nearly the whole LDS is data on its way (the copies are bound by latency:
 // bytes in flight over about two microseconds).
 // The LoRA term enters as extra k steps: t = X W^A (fp32, computed beforehand) split into two bf16 halves
-// (hi + lo, so nothing of t's precision is lost) against W^B of the tenant, masked to that tenant's rows.
+// (hi + lo, about 17 of its 24 bits) against W^B of the tenant, masked to that tenant's rows.
 // Bias is added and the result rounded once at the store.
 #include "shrink.h"
 
@@ -237,6 +237,7 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
       if (r) my_ten = tenant;
     }
   }
+  if (tid == 0) ctl[1] = 0;  // set: W^B of some tenant of the tile holds Inf or NaN
   int last = -1;
   for (;;) {
     if (tid == 0) ctl[0] = 0x7fffffff;
@@ -264,6 +265,14 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
       uint16_t bv[32];
 #pragma unroll
       for (int c = 0; c < 32; ++c) bv[c] = Bm[(size_t)(c0 + c < r ? c0 + c : r - 1) * p.d2 + (n < p.d2 ? n : p.d2 - 1)];
+      uint32_t worst = 0;
+#pragma unroll
+      for (int c = 0; c < 32; ++c) worst = (bv[c] & 0x7fffu) > worst ? (bv[c] & 0x7fffu) : worst;
+      if (worst >= 0x7f80u) {
+#pragma unroll
+        for (int c = 0; c < 32; ++c) bv[c] = (uint16_t)finite2(bv[c]);
+        ctl[1] = 1;
+      }
       // t of the tile's 256 rows for these 32 ranks, the shrink's parts added in part order, through LDS: eight
       // lanes read the 128 bytes of a row (whole lines), then every thread picks up its own row
       float* const ts = reinterpret_cast<float*>(lds + 2 * kHalfBytes + 1024);  // [256][33]
@@ -323,7 +332,7 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
           }
           const bf16_t h0b = f32_to_bf16(tv[0]), h1b = f32_to_bf16(tv[1]);
           hi[e] = (uint32_t)h0b | ((uint32_t)h1b << 16);
-          lo[e] = pack_bf16x2(tv[0] - bf16_to_f32(h0b), tv[1] - bf16_to_f32(h1b));
+          lo[e] = (uint32_t)split_lo(tv[0], h0b) | ((uint32_t)split_lo(tv[1], h1b) << 16);
           wb[e] = bw[0] | (bw[1] << 16);
         }
         const uint32_t o_hi = blk + (((uint32_t)g ^ (uint32_t)swz(rb)) << 4);
@@ -361,6 +370,29 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
         v[0] = pack_bf16x2(acc[i][j][4 * g] + bv[0], acc[i][j][4 * g + 1] + bv[1]);
         v[1] = pack_bf16x2(acc[i][j][4 * g + 2] + bv[2], acc[i][j][4 * g + 3] + bv[3]);
         *(u32x2*)(p.Y + (size_t)m * p.d2 + n) = v;
+      }
+    }
+  }
+
+  // ---- what the stages could not take: products with the tenant's own Inf and NaN, onto the stored results (no finite part of
+  // them matters any more)
+  if (ctl[1]) {
+    for (int i = 0; i < 4; ++i) {
+      const int64_t m = m0 + wm * 128 + i * 32 + (lane & 31);
+      if (m >= p.M) continue;
+      const int64_t req = p.row_to_req ? (int64_t)p.row_to_req[m] : p.row_base + m;
+      int tenant = 0;
+      const int r = (req >= 0 && req < p.B) ? routed_rank(p.ad, p.tenant_id, p.route, (int)req, p.B, p.site, &tenant) : 0;
+      for (int c = 0; c < r; ++c) {
+        gbf16* b = in_global(p.ad.B[tenant * MILORA_NUM_SITES + p.site]) + (size_t)c * p.d2;
+        float t = 0.f;
+        for (int k = 0; k < p.parts; ++k) t += p.t[k * p.t_stride + (size_t)m * p.ad.r_max + c];
+        for (int q = 0; q < 64; ++q) {  // this lane's columns
+          const int n = n0 + wn * 128 + (q >> 4) * 32 + ((q >> 2) & 3) * 8 + (lane >> 5) * 4 + (q & 3);
+          if (n >= p.d2 || (b[n] & 0x7f80u) != 0x7f80u) continue;
+          bf16_t* const y = p.Y + (size_t)m * p.d2 + n;
+          *y = f32_to_bf16(bf16_to_f32(*y) + t * bf16_to_f32(b[n]));
+        }
       }
     }
   }

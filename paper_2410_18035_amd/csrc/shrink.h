@@ -55,6 +55,22 @@ __device__ __forceinline__ void transpose8(const u32x4 (&a)[8], u32x4 (&out)[8])
     }
 }
 
+// Tenants whose rows share a matrix stage see each other's W^B times zero, and zero times Inf is NaN.  Inf and NaN therefore never
+// enter a stage: a 1 of their sign goes in (for the tenant's own rows it stands beside the true product, which is not finite and
+// is added behind the stages), and the workgroup remembers that it has to add.
+// Bits 15 and 31: whether the low or high bf16 of the word is Inf or NaN.
+__device__ __forceinline__ uint32_t nonfinite2(uint32_t w) { return ((w & 0x7f807f80u) + 0x00800080u) & 0x80008000u; }
+__device__ __forceinline__ uint32_t finite2(uint32_t w) {
+  const uint32_t bad = nonfinite2(w);
+  if (bad & 0x8000u) w = (w & 0xffff8000u) | 0x3f80u;
+  if (bad & 0x80000000u) w = (w & 0x8000ffffu) | 0x3f800000u;
+  return w;
+}
+// t as a sum of two bf16 (an infinite one stands alone: Inf - Inf is NaN).
+__device__ __forceinline__ bf16_t split_lo(float t, bf16_t hi) {
+  return (hi & 0x7f80u) == 0x7f80u ? (bf16_t)0 : f32_to_bf16(t - bf16_to_f32(hi));
+}
+
 // Eight bf16 of a row that ends after `left` elements (zero past the end); 16-byte load where `vec` allows it.
 __device__ __forceinline__ u32x4 load8(gbf16* p, int left, bool vec) {
   if (vec) return *(gu32x4*)p;

@@ -17,7 +17,8 @@
 // work every thread adds t W^B of its own outputs in fp32, the ranks dealt to the parts; what one tenant's adapter holds, Inf and NaN
 // too, reaches that tenant's rows only.  This serves packed weights and calls of fewer than 64 rows, where rows of many tenants
 // meet.  Else as more stages of the matrix work: t split into two bf16 halves (hi + lo, about 17 bits of it) against
-// W^B, the rows of other tenants entering as zeros.  Then bias, one rounding, 16-byte stores.
+// W^B, the rows of other tenants entering as zeros (Inf and NaN of W^B are kept out and added for their own rows behind
+// the stages).  Then bias, one rounding, 16-byte stores.
 //
 // Bound: few rows, the stream of the weights (a 4096 x 11008 linear at 45 rows: 23 us = 3.9 TB/s); from some hundred rows on
 // the copies through the L2 (0.58 us per 128 x 128 x 64 stage and compute unit, 56 GB/s each).  The seven linears of the 7B
@@ -38,6 +39,7 @@ constexpr int kT = 512;        // threads: eight waves
 constexpr int kCtlBytes = 4096;
 constexpr int kMaxGroups = 256;  // groups of 8 ranks of the LoRA phase listed at a time
 constexpr int kGroupM = 6;
+constexpr int kCtlBad = 4;  // control word: W^B holds Inf or NaN
 constexpr int kTs = MILORA_MAX_RANK + 4;  // t of a row in LDS
 
 template <int BM_, int BN_, int KQ_, int WMC_, int WNC_, int NS_, int OCC_>
@@ -97,7 +99,7 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
   int* const row_rank = row_ten + C::BM;              // [BM]
   int* const row_group = row_rank + C::BM;            // [BM] first rank group of the row's run
   int2* const groups = reinterpret_cast<int2*>(row_group + C::BM);  // [kMaxGroups] tenant, first rank
-  int* const ctl = reinterpret_cast<int*>(groups + kMaxGroups);     // 0: arrivals before this one, 1: rows with a LoRA term
+  int* const ctl = reinterpret_cast<int*>(groups + kMaxGroups);     // 0: arrivals before this one, 1, 2: rows with a LoRA term, kCtlBad
   int* const row_c0 = row_rank;    // (ROWS) [BM] first rank of the row in this part
   int* const row_cnt = row_group;  // (ROWS) [BM] ranks of the row in this part
   unsigned char* const ring = lds + kCtlBytes;
@@ -227,6 +229,7 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
       row_rank[tid] = r;
       const unsigned long long any = __ballot(r > 0);
       if (lane == 0) ctl[1 + w] = any != 0;
+      if (tid == 0) ctl[kCtlBad] = 0;
     }
   }
   int slot = 0;
@@ -331,7 +334,7 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
           for (int e = 0; e < 4; ++e) {
             const bf16_t h0 = f32_to_bf16(tv[2 * e]), h1 = f32_to_bf16(tv[2 * e + 1]);
             hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            lo[e] = pack_bf16x2(tv[2 * e] - bf16_to_f32(h0), tv[2 * e + 1] - bf16_to_f32(h1));
+            lo[e] = (uint32_t)split_lo(tv[2 * e], h0) | ((uint32_t)split_lo(tv[2 * e + 1], h1) << 16);
           }
           unsigned char* const row = ring + (group >> 2) * C::StageBytes + xr * 128;
           *reinterpret_cast<u32x4*>(row + (((group & 3) ^ swz(xr & 15)) << 4)) = hi;
@@ -356,6 +359,18 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
 #pragma unroll
           for (int i = 0; i < 8; ++i)
             if (gr.y + i < r) a[i] = *(gu32x4_a2*)(b + (size_t)(gr.y + i) * p.d2);
+          uint32_t bad = 0;
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bad |= nonfinite2(a[i][e]);
+          if (bad) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) a[i][e] = finite2(a[i][e]);
+            ctl[kCtlBad] = 1;
+          }
         }
         auto put_w = [&]() __attribute__((always_inline)) {
           u32x4 at[8];
@@ -492,6 +507,26 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
               val[it][e >> 1][2 * (e & 1) + 1] += t * __uint_as_float(x & 0xffff0000u);
             }
           }
+      }
+    }
+  }
+
+  // ---- what the stages could not take: products with the tenant's own Inf and NaN ----
+  if (!ROWS && lora && ctl[kCtlBad] && cg * 8 < cols) {
+#pragma unroll
+    for (int it = 0; it < C::Items; ++it) {
+      const int row = r0 + it * kRowStep, ten = row_ten[row], r = ten >= 0 ? row_rank[row] : 0;
+      for (int c = 0; c < r; ++c) {
+        const u32x4 b = *(gu32x4_a2*)(in_global(p.ad.B[ten * MILORA_NUM_SITES + p.site]) + (size_t)c * p.d2 + n0 + cg * 8);
+        if (!(nonfinite2(b[0]) | nonfinite2(b[1]) | nonfinite2(b[2]) | nonfinite2(b[3]))) continue;
+        float t = 0.f;
+        for (int k = 0; k < p.parts; ++k) t += p.t[k * p.t_stride + (size_t)(m0 + row) * p.ad.r_max + c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t bad = nonfinite2(b[e]);
+          if (bad & 0x8000u) val[it][e >> 1][2 * (e & 1)] += t * __uint_as_float(b[e] << 16);
+          if (bad & 0x80000000u) val[it][e >> 1][2 * (e & 1) + 1] += t * __uint_as_float(b[e] & 0xffff0000u);
+        }
       }
     }
   }

@@ -93,6 +93,9 @@ def test_workspace_for_the_largest_call_serves_every_smaller_one():
     (False, 63, 4096, 144, 7),   # the reduction in parts
     (True, 33, 96, 2064, 33),    # a tenant per row, half a stage at the end
     (True, 100, 2048, 3520, 9),  # 128 x 128 tiles
+    (False, 130, 192, 272, 6),   # the LoRA term as matrix stages, 64 x 64 tiles
+    (False, 300, 2048, 3520, 9),  # 128 x 128 tiles, in parts
+    (False, 4097, 192, 272, 40),  # 256 x 256 tiles
 ])
 def test_one_tenants_infinities_and_nans_reach_its_own_rows_only(packed, M, d1, d2, T):
     """Rows of many tenants meet in a tile.  Tenant 1's W^B holds Inf and NaN, tenant 2's W^A an Inf (its shrink is Inf): every
@@ -117,13 +120,14 @@ def test_one_tenants_infinities_and_nans_reach_its_own_rows_only(packed, M, d1, 
     Y = run()
     bad = (r2r == 1) | (r2r == 2)
     assert torch.equal(Y[~bad], clean[~bad])
-    for m in torch.nonzero(bad).flatten().tolist():
+    for m in torch.nonzero(bad).flatten().tolist()[:60]:
         t = X[m].double() @ A[r2r[m]][site].double()
         ref = X[m].double() @ W.double().T + (t[:, None] * B[r2r[m]][site].double()).sum(0)
         for kind in (torch.isnan, torch.isposinf, torch.isneginf):
             assert torch.equal(kind(Y[m]), kind(ref)), f"row {m}, tenant {int(r2r[m])}"
         fine = torch.isfinite(ref)
-        assert (Y[m].double() - ref)[fine].abs().max() <= 2e-2 * ref[fine].abs().max() if fine.any() else True
+        if fine.any():
+            assert (Y[m].double() - ref)[fine].abs().max() <= 2e-2 * ref[fine].abs().max()
 
 
 @gpu

@@ -265,14 +265,6 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
       uint16_t bv[32];
 #pragma unroll
       for (int c = 0; c < 32; ++c) bv[c] = Bm[(size_t)(c0 + c < r ? c0 + c : r - 1) * p.d2 + (n < p.d2 ? n : p.d2 - 1)];
-      uint32_t worst = 0;
-#pragma unroll
-      for (int c = 0; c < 32; ++c) worst = (bv[c] & 0x7fffu) > worst ? (bv[c] & 0x7fffu) : worst;
-      if (worst >= 0x7f80u) {
-#pragma unroll
-        for (int c = 0; c < 32; ++c) bv[c] = (uint16_t)finite2(bv[c]);
-        ctl[1] = 1;
-      }
       // t of the tile's 256 rows for these 32 ranks, the shrink's parts added in part order, through LDS: eight
       // lanes read the 128 bytes of a row (whole lines), then every thread picks up its own row
       float* const ts = reinterpret_cast<float*>(lds + 2 * kHalfBytes + 1024);  // [256][33]
@@ -332,8 +324,13 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
           }
           const bf16_t h0b = f32_to_bf16(tv[0]), h1b = f32_to_bf16(tv[1]);
           hi[e] = (uint32_t)h0b | ((uint32_t)h1b << 16);
-          lo[e] = (uint32_t)split_lo(tv[0], h0b) | ((uint32_t)split_lo(tv[1], h1b) << 16);
+          lo[e] = pack_bf16x2(tv[0] - bf16_to_f32(h0b), tv[1] - bf16_to_f32(h1b));
           wb[e] = bw[0] | (bw[1] << 16);
+        }
+        if (taint(taint(taint(taint(0.f, wb[0]), wb[1]), wb[2]), wb[3]) != 0.f) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) wb[e] = finite2(wb[e]);
+          ctl[1] = 1;
         }
         const uint32_t o_hi = blk + (((uint32_t)g ^ (uint32_t)swz(rb)) << 4);
         const uint32_t o_lo = blk + (((uint32_t)(g + 4) ^ (uint32_t)swz(rb)) << 4);

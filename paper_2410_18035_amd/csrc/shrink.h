@@ -66,11 +66,12 @@ __device__ __forceinline__ uint32_t finite2(uint32_t w) {
   if (bad & 0x80000000u) w = (w & 0x8000ffffu) | 0x3f800000u;
   return w;
 }
-// t as a sum of two bf16 (an infinite one stands alone: Inf - Inf is NaN).
-__device__ __forceinline__ bf16_t split_lo(float t, bf16_t hi) {
-  return (hi & 0x7f80u) == 0x7f80u ? (bf16_t)0 : f32_to_bf16(t - bf16_to_f32(hi));
+// `sum` plus zero times both bf16 of the word: NaN from the first Inf or NaN on, else as it was (one instruction per word; by bit
+// tests, three: 4096 scattered rows of 64 tenants, rank 256, 4096 x 4096: 5.22 ms a call, 5.10 so).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float taint(float sum, uint32_t w) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0u), sum, false);
 }
-
 // Eight bf16 of a row that ends after `left` elements (zero past the end); 16-byte load where `vec` allows it.
 __device__ __forceinline__ u32x4 load8(gbf16* p, int left, bool vec) {
   if (vec) return *(gu32x4*)p;

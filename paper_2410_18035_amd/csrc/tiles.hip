@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
           for (int e = 0; e < 4; ++e) {
             const bf16_t h0 = f32_to_bf16(tv[2 * e]), h1 = f32_to_bf16(tv[2 * e + 1]);
             hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            lo[e] = (uint32_t)split_lo(tv[2 * e], h0) | ((uint32_t)split_lo(tv[2 * e + 1], h1) << 16);
+            lo[e] = pack_bf16x2(tv[2 * e] - bf16_to_f32(h0), tv[2 * e + 1] - bf16_to_f32(h1));
           }
           unsigned char* const row = ring + (group >> 2) * C::StageBytes + xr * 128;
           *reinterpret_cast<u32x4*>(row + (((group & 3) ^ swz(xr & 15)) << 4)) = hi;
@@ -359,12 +359,12 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
 #pragma unroll
           for (int i = 0; i < 8; ++i)
             if (gr.y + i < r) a[i] = *(gu32x4_a2*)(b + (size_t)(gr.y + i) * p.d2);
-          uint32_t bad = 0;
+          float bad[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bad |= nonfinite2(a[i][e]);
-          if (bad) {
+            for (int e = 0; e < 4; ++e) bad[e] = taint(bad[e], a[i][e]);
+          if ((bad[0] + bad[1]) + (bad[2] + bad[3]) != 0.f) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll

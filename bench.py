@@ -130,7 +130,7 @@ def prefill_leg(torch, mb, synth, dev, reps=5):
     route_ms = timed(lambda: mb.milora_route(H, ss, sl, tid, Wr, wl.pool, wl.act, route_out=route, want_logits=False,
                                              workspace=ws_route))
     Xm = torch.empty(M, wl.F, dtype=torch.float32, device=dev).normal_(0, 1).to(torch.bfloat16)
-    ws = torch.empty(mb.routed_linear_workspace_bytes(M, wl.F, wl.F, tab.r_max), dtype=torch.uint8, device=dev)
+    ws = torch.zeros(mb.routed_linear_workspace_bytes(M, wl.F, wl.F, tab.r_max), dtype=torch.uint8, device=dev)
     site_ms, flops = [], 0.0
     for site in range(7):
         d1, d2 = synth.site_dims(site, wl.d, wl.F)

@@ -11,7 +11,8 @@
 // refilled from there on, so that nearly the whole LDS is data on its way (the copies are bound by latency:
 // bytes in flight over about two microseconds).
 // The LoRA term enters as extra k steps: t = X W^A (fp32, computed beforehand) split into two bf16 halves
-// (hi + lo, about 17 of its 24 bits) against W^B of the tenant, masked to that tenant's rows.
+// (hi + lo, about 17 of its 24 bits) against W^B of the tenant, masked to that tenant's rows; Inf and NaN of W^B are kept
+// out of the stages and added to those rows at the end.
 // Bias is added and the result rounded once at the store.
 #include "shrink.h"
 

@@ -440,8 +440,9 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
 
   // ---- ROWS: LoRA term of this part's ranks: t of the tile's rows through LDS (the shrink's parts added in part order), then
   // kU rows of W^B for all of a thread's rows on their way together.  Bound by the reads of W^B where every row has a tenant of
-  // its own: 64 packed rows, rank 64, 4096 x 4096: 143 us a call with the term as matrix stages, 56 us so.  A tile of one tenant
-  // reads its W^B again for each row: 300 rows of 4 tenants, rank 64, 4096 x 11008: 77 -> 89 us.
+  // its own: 64 packed rows, rank 64, 4096 x 4096: 143 us a call with the term as matrix stages, 56 us so (37 since the shrink in
+  // front has more workgroups).  A tile of one tenant reads its W^B again for each row: 300 rows of 4 tenants, rank 64, 4096 x
+  // 11008: 77 -> 90 us.
   if constexpr (ROWS) {
     int most = ctl[1];
     if (C::BM > 64) most = ctl[2] > most ? ctl[2] : most;

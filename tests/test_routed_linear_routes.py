@@ -283,3 +283,39 @@ def test_routed_linear_256_tiles_small_integers_bit_exact():
         tid.numpy(), route.numpy(), row_to_req=r2r.numpy())
     assert (abs(ref) <= 256).all()
     assert (to_f64(Y) == ref).all()
+
+
+@gpu
+@pytest.mark.parametrize("packed,M,d1,d2", [(False, 16, 4096, 64), (False, 300, 2048, 3520), (True, 70, 4096, 64)])
+def test_tiles_in_parts_replay_in_a_graph(packed, M, d1, d2):
+    """Shrink, counters and parts recorded once and replayed on new rows, with eager calls on the same workspace between."""
+    A, B, rank = _adapters(4, d1, d2, (8, 20), 0.1, 80)
+    tab = mb.AdapterTable.from_tensors(A, B, rank)
+    g = torch.Generator(device=DEV).manual_seed(81)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    X, W = rnd(M, d1), rnd(d2, d1)
+    W = mb.milora_pack_weight(W) if packed else W
+    ids = torch.arange(4, dtype=torch.int32, device=DEV)
+    r2r, route = torch.arange(M, dtype=torch.int32, device=DEV) * 4 // M, torch.ones(4, dtype=torch.uint8, device=DEV)
+    ws = torch.zeros(mb.routed_linear_workspace_bytes(M, d1, d2, tab.r_max), dtype=torch.uint8, device=DEV)
+    out = torch.empty(M, d2, dtype=torch.bfloat16, device=DEV)
+    run = lambda x, y: mb.milora_routed_linear(x, W, tab, 1, ids, route, r2r, d2=d2, w_layout=mb.W_PACKED if packed else mb.W_ROWMAJOR,
+                                               workspace=ws, out=y)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        run(X, out)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(X, out)
+    for rep in range(5):
+        x = rnd(M, d1)
+        eager = run(x, torch.empty_like(out)).clone()
+        torch.cuda.synchronize()
+        X.copy_(x)
+        out.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager), f"replay {rep}"

@@ -508,20 +508,21 @@ static int launch_few_rows_t(FewArgs& g, int sites, int mode, hipStream_t st) {
 // Shrinks inside the launch spare one of its own (3 to 4 us) and cost every wave about 0.7 us per routed row and round trip, a trip
 // taking d1 / 8 x rank in pieces of 64 lanes x 8 loads.  With every row routed the two meet at some 10 trips (fp32, 8 rows, 512 x
 // 1376, rank 8: 11.3 us a call inside, 12.7 apart; 8 rows, 1000 x 2730: 16.6 and 13.2; 16 rows, 4100 x 11010, rank 16: 306 and
-// 59), with one site a request, as in a layer's step, at some 30 (16 rows, d = 512: 40.2 and 45.3 us a step; d = 1000, rank 8:
-// 61.6 and 63.0, rank 16: 80.6 and 70.0): the line lies between.
-static bool fuse_shrink(int M, int d1, int r_max) {
+// 59).  In a layer's step a request has one of the seven sites, or a few: there it is some 45 trips of all rows (16 rows, d = 512,
+// rank 8, 16 trips and 42 of the down projection: 40.2 and 45.3 us a step; d = 1000, rank 8, 31 and 85: 61.6 and 63.0; rank 16, 62 and
+// 171: 80.6 and 70.0).
+static bool fuse_shrink(int M, int d1, int r_max, bool layer) {
   if (r_max > kFuseRank) return false;
   int rpad = 1;
   while (rpad < r_max) rpad <<= 1;
   const int64_t trip = 8 * 64 * 8, work = (int64_t)d1 * rpad;
-  return M * (work > trip ? work : trip) <= 16 * trip;
+  return M * (work > trip ? work : trip) <= (layer ? 48 : 16) * trip;
 }
 
 int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t st) {
   FewArgs g = args;
   g.t = nullptr;
-  if (!fuse_shrink(g.M, g.d1, g.ad.r_max)) {
+  if (!fuse_shrink(g.M, g.d1, g.ad.r_max, sites > 1 || mode != kFewPlain)) {
     const int rc = launch_shrink(g.X, g.ldx, g.M, g.d1, dtype, g.row_to_req, g.ad, g.site[0], sites, g.tenant_id, g.route, g.B, t, st);
     if (rc) return rc;
     g.t = t;

@@ -1,8 +1,8 @@
 // Prompt-aware LoRA router of one layer (paper Sec. 3.3): pooler (Eq. 2 and the pooler list of Sec. 3.3:
 // last token, average, max, self-attention of App. C), activation g (fixed functions or the rational form of
 // Sec. 3.4), router linear and top-k selection (Eq. 3).  Last-token, average and max pooling run with the router
-// in one kernel (one HBM pass over H, the finish inside the same launch); the self-attention pooler keeps a
-// token-split partial reduction followed by one workgroup per request.
+// in one kernel (one HBM pass over H, the finish inside the same launch); the self-attention pooler is one pass that leaves
+// partial rows, and a launch that merges them and finishes the same way.
 // Pooled state, activation and logits stay in fp32; every sum runs in a fixed order, so the
 // same prompt always yields the same route.
 #include <atomic>
@@ -13,7 +13,6 @@ namespace milora {
 
 namespace {
 
-constexpr int kThreads = 256;
 constexpr int kMaxSplits = 128;  // token slices per request at most
 
 typedef uint32_t raw_u32x4 __attribute__((ext_vector_type(4)));
@@ -179,6 +178,107 @@ struct PoolRouteArgs {
   RationalCoef coef;
 };
 
+// A request without a valid span or tenant.
+template <typename T>
+__device__ __forceinline__ void no_route(const PoolRouteArgs<T>& p, int b) {
+  if (threadIdx.x == 0) p.route_out[b] = MILORA_ROUTE_NONE;
+  if (p.logits_out && threadIdx.x < MILORA_NUM_SITES) p.logits_out[b * MILORA_NUM_SITES + threadIdx.x] = __uint_as_float(0x7fc00000u);
+}
+
+// Router weights of the four columns that lane f < FT finishes.
+template <typename T, int FT>
+__device__ __forceinline__ void load_router_weights(const PoolRouteArgs<T>& p, int ten, int f, int fcol, float (&wr)[MILORA_NUM_SITES][4]) {
+#pragma unroll
+  for (int j = 0; j < MILORA_NUM_SITES; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) wr[j][v] = 0.f;
+  if (f >= FT) return;
+  const T* wt = p.Wr + (size_t)ten * MILORA_NUM_SITES * p.d;
+#pragma unroll
+  for (int j = 0; j < MILORA_NUM_SITES; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (fcol + v < p.d) wr[j][v] = Elem<T>::load(wt, (size_t)j * p.d + fcol + v);
+}
+
+// Columns 4 f .. + 3 of the sixteen token lanes, added in a fixed tree.
+template <int SW>
+__device__ __forceinline__ f32x4 add_token_lanes(const float (&red)[kTokenLanes][SW], int f) {
+  f32x4 r[kTokenLanes];
+#pragma unroll
+  for (int i = 0; i < kTokenLanes; ++i) r[i] = *reinterpret_cast<const f32x4*>(&red[i][4 * f]);
+  return (((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]))) +
+         (((r[8] + r[9]) + (r[10] + r[11])) + ((r[12] + r[13]) + (r[14] + r[15])));
+}
+
+// z = g(scale * h) of a lane's columns fcol .. fcol + 3 (where `on`) and what they add to the seven logits, summed over the wave (every
+// lane ends with the sums).
+template <typename T>
+__device__ __forceinline__ void wave_logits(const PoolRouteArgs<T>& p, bool on, int fcol, f32x4 h, float scale,
+                                            const float (&wr)[MILORA_NUM_SITES][4], float (&lg)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) lg[j] = 0.f;
+  if (on) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (fcol + v < p.d) {
+        const float z = activate(h[v] * scale, p.act, p.coef);
+#pragma unroll
+        for (int j = 0; j < MILORA_NUM_SITES; ++j) lg[j] += z * wr[j][v];
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < MILORA_NUM_SITES; ++j)
+    for (int off = 32; off > 0; off >>= 1) lg[j] += __shfl_xor(lg[j], off, 64);
+}
+
+// A slab's share of the seven logits is known: hand it over and, by the wave that finds every slab's share, select.  Called by one
+// wave.
+template <typename T>
+__device__ __forceinline__ void finish_request(const PoolRouteArgs<T>& p, int b, int c, int lane, float (&lg)[8]) {
+  if (p.C > 1) {
+    // unit u of the slab: logits 2u and 2u + 1 with the tag.  Lane i takes units i, i + 64, ...: always unit i % 4,
+    // of slabs i / 4, i / 4 + 16, ...; the sixteen running sums of a unit are then added across the lanes.
+    u32x4* units = p.share + (size_t)b * p.C * 4;
+    if (lane < 4) {
+      float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (lane == u) { e0 = lg[2 * u]; e1 = lg[2 * u + 1]; }
+      st_through(units + c * 4 + lane, u32x4{__float_as_uint(e0), __float_as_uint(e1), p.tag_lo, p.tag_hi});
+    }
+    wait_all_mem();
+    bool all = true;
+    float a0 = 0.f, a1 = 0.f;
+    for (int i = lane; i < 4 * p.C; i += 64) {
+      const u32x4 g = ld_through(units + i);
+      all = all && g[2] == p.tag_lo && g[3] == p.tag_hi;
+      a0 += __uint_as_float(g[0]);
+      a1 += __uint_as_float(g[1]);
+    }
+    if (__builtin_amdgcn_readfirstlane(__ballot(all) != ~0ull)) return;
+    for (int i = lane; i < 4 * p.C; i += 64) st_through(units + i, u32x4{0u, 0u, 0u, 0u});
+    for (int off = 4; off < 64; off <<= 1) {
+      a0 += __shfl_xor(a0, off, 64);
+      a1 += __shfl_xor(a1, off, 64);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      lg[2 * u] = __shfl(a0, u, 64);
+      lg[2 * u + 1] = __shfl(a1, u, 64);
+    }
+  }
+  float logit[MILORA_NUM_SITES];
+#pragma unroll
+  for (int j = 0; j < MILORA_NUM_SITES; ++j) logit[j] = lg[j];
+  if (lane == 0) {
+    if (p.logits_out)
+      for (int j = 0; j < MILORA_NUM_SITES; ++j) p.logits_out[b * MILORA_NUM_SITES + j] = logit[j];
+    p.route_out[b] = select_route(logit, p.top_k);
+  }
+}
+
 template <typename T, int VEC>
 __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<T> p) {
   constexpr int SW = kColLanes * VEC;  // columns of a slab
@@ -192,11 +292,7 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
   int64_t start = p.seq_start[b], n = p.seq_len[b];
   const int ten = p.tenant_id[b];
   if (!span_ok(start, n, p.M_tok) || ten < 0 || ten >= p.T_tenants) {
-    if (blockIdx.x == 0) {
-      if (threadIdx.x == 0) p.route_out[b] = MILORA_ROUTE_NONE;
-      if (p.logits_out && threadIdx.x < MILORA_NUM_SITES)
-        p.logits_out[b * MILORA_NUM_SITES + threadIdx.x] = __uint_as_float(0x7fc00000u);
-    }
+    if (blockIdx.x == 0) no_route(p, b);
     return;
   }
   const bool is_max = p.pool == MILORA_POOL_MAX;
@@ -215,18 +311,7 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
   const int f = threadIdx.x;
   const int fcol = c * SW + 4 * f;
   float wr[MILORA_NUM_SITES][4];
-#pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) wr[j][v] = 0.f;
-  if (f < FT) {
-    const T* wt = p.Wr + (size_t)ten * MILORA_NUM_SITES * d;
-#pragma unroll
-    for (int j = 0; j < MILORA_NUM_SITES; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (fcol + v < d) wr[j][v] = Elem<T>::load(wt, (size_t)j * d + fcol + v);
-  }
+  load_router_weights<T, FT>(p, ten, f, fcol, wr);
 
   // ---- pool the slice: token lane tl takes rows t0 + tl, t0 + tl + 16, ...
   const int col = c * SW + cl * VEC;
@@ -265,19 +350,18 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
 
   f32x4 h = {ident, ident, ident, ident};
   if (f < FT) {
-    f32x4 r[TL];
+    if (is_max) {
+      f32x4 r[TL];
 #pragma unroll
-    for (int i = 0; i < TL; ++i) r[i] = *reinterpret_cast<const f32x4*>(&red[i][4 * f]);
+      for (int i = 0; i < TL; ++i) r[i] = *reinterpret_cast<const f32x4*>(&red[i][4 * f]);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (is_max)
+      for (int v = 0; v < 4; ++v)
         h[v] = fmaxf(fmaxf(fmaxf(fmaxf(r[0][v], r[1][v]), fmaxf(r[2][v], r[3][v])),
                            fmaxf(fmaxf(r[4][v], r[5][v]), fmaxf(r[6][v], r[7][v]))),
                      fmaxf(fmaxf(fmaxf(r[8][v], r[9][v]), fmaxf(r[10][v], r[11][v])),
                            fmaxf(fmaxf(r[12][v], r[13][v]), fmaxf(r[14][v], r[15][v]))));
-      else
-        h[v] = (((r[0][v] + r[1][v]) + (r[2][v] + r[3][v])) + ((r[4][v] + r[5][v]) + (r[6][v] + r[7][v]))) +
-               (((r[8][v] + r[9][v]) + (r[10][v] + r[11][v])) + ((r[12][v] + r[13][v]) + (r[14][v] + r[15][v])));
+    } else {
+      h = add_token_lanes<SW>(red, f);
     }
   }
   if (p.S > 1) {
@@ -331,293 +415,332 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
     }
   }
 
-  // ---- z = g(h); the slab's share of the seven logits, summed over the lanes (every lane ends with the sums)
   float lg[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) lg[j] = 0.f;
-  if (f < FT) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (fcol + v < d) {
-        const float z = activate(h[v] * scale, p.act, p.coef);
-#pragma unroll
-        for (int j = 0; j < MILORA_NUM_SITES; ++j) lg[j] += z * wr[j][v];
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j)
-    for (int off = 32; off > 0; off >>= 1) lg[j] += __shfl_xor(lg[j], off, 64);
-
-  if (p.C > 1) {
-    // unit u of the slab: logits 2u and 2u + 1 with the tag.  Lane i takes units i, i + 64, ...: always unit i % 4,
-    // of slabs i / 4, i / 4 + 16, ...; the sixteen running sums of a unit are then added across the lanes.
-    u32x4* units = p.share + (size_t)b * p.C * 4;
-    if (lane < 4) {
-      float e0 = 0.f, e1 = 0.f;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (lane == u) { e0 = lg[2 * u]; e1 = lg[2 * u + 1]; }
-      st_through(units + c * 4 + lane, u32x4{__float_as_uint(e0), __float_as_uint(e1), p.tag_lo, p.tag_hi});
-    }
-    wait_all_mem();
-    bool all = true;
-    float a0 = 0.f, a1 = 0.f;
-    for (int i = lane; i < 4 * p.C; i += 64) {
-      const u32x4 g = ld_through(units + i);
-      all = all && g[2] == p.tag_lo && g[3] == p.tag_hi;
-      a0 += __uint_as_float(g[0]);
-      a1 += __uint_as_float(g[1]);
-    }
-    if (__builtin_amdgcn_readfirstlane(__ballot(all) != ~0ull)) return;
-    for (int i = lane; i < 4 * p.C; i += 64) st_through(units + i, u32x4{0u, 0u, 0u, 0u});
-    for (int off = 4; off < 64; off <<= 1) {
-      a0 += __shfl_xor(a0, off, 64);
-      a1 += __shfl_xor(a1, off, 64);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      lg[2 * u] = __shfl(a0, u, 64);
-      lg[2 * u + 1] = __shfl(a1, u, 64);
-    }
-  }
-  float logit[MILORA_NUM_SITES];
-#pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j) logit[j] = lg[j];
-  if (lane == 0) {
-    if (p.logits_out)
-      for (int j = 0; j < MILORA_NUM_SITES; ++j) p.logits_out[b * MILORA_NUM_SITES + j] = logit[j];
-    p.route_out[b] = select_route(logit, p.top_k);
-  }
+  wave_logits(p, f < FT, fcol, h, scale, wr, lg);
+  finish_request(p, b, c, lane, lg);
 }
 
-// Self-attention pooling (App. C): u_t = H[t] . w_sa, a = softmax over the request's tokens, p = sum_t a_t H[t].
-// A workgroup takes one token slice of one request in blocks of 256 tokens: scores (one wave per token), the
-// block's maximum, then the weighted sum with the running maximum as reference (a block that raises the
-// maximum rescales what was gathered before it).  Out: the unnormalised weighted sum, and (max, sum of
-// weights) per slice; the finishing kernel merges the slices.  d <= 8192.
+// ---- self-attention pooling (App. C): u_t = H[t] . w_sa, a = softmax over the request's tokens, p = sum_t a_t H[t] ----
+// One pass over H.  The valid tokens of all requests, one request after the other, are a line that is cut into equal
+// pieces, one per workgroup, whatever the lengths.  A workgroup holds a row across its threads (16 bytes each, kPieces of them) and
+// takes R rows at a time: R scores (in-wave sums, then over the waves through LDS, one barrier), weights relative to the
+// running maximum (a batch that raises it rescales what was gathered before), weighted sum out of the same registers,
+// while the next R rows are on their way.  The part of a piece that lies in one request leaves a row of unnormalised sums
+// and (maximum, sum of weights) in the workspace, at index piece + request; the finishing launch merges a request's rows.
+// Bound: the read of H.  16 prompts of 1024 to 2048 tokens, d = 4096 (201 MB): 41 us = 4.9 TB/s and 10.6 us
+// for the finishing launch, six dependent round trips (with slices of 16 tokens, each read twice, and one finishing workgroup
+// per request: 65 and 72 us).
 constexpr int kSelfAttnMaxD = 8192;
+constexpr int kAttnMaxWaves = 16;
 
-template <typename T, int VEC>
-__global__ void __launch_bounds__(kThreads) pool_selfattn_kernel(const T* __restrict__ H, int64_t M_tok, int d,
-                                                                 const int32_t* __restrict__ seq_start,
-                                                                 const int32_t* __restrict__ seq_len,
-                                                                 const int32_t* __restrict__ tenant_id, int T_tenants,
-                                                                 const T* __restrict__ w_sa, int S, int cgw,
-                                                                 float* __restrict__ partial, float* __restrict__ ml) {
-  constexpr int MAXP = 32 / VEC;  // column passes of a thread: d / VEC / 256 at most
-  __shared__ float sc[kThreads];
-  __shared__ float red[kThreads * VEC];
-  __shared__ float wred[kThreads / 64];
-  const int b = blockIdx.y, s = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int64_t start = seq_start[b], n = seq_len[b];
+// VEC neighbouring elements as they lie in memory; read once.
+template <typename T, int VEC> struct Piece;
+template <> struct Piece<bf16_t, 8> {
+  raw_u32x4 v;
+  __device__ __forceinline__ void load(const bf16_t* p) { v = __builtin_nontemporal_load(reinterpret_cast<const raw_u32x4*>(p)); }
+  __device__ __forceinline__ float get(int i) const { return __uint_as_float((i & 1) ? v[i >> 1] & 0xffff0000u : v[i >> 1] << 16); }
+};
+template <> struct Piece<float, 4> {
+  raw_u32x4 v;
+  __device__ __forceinline__ void load(const float* p) { v = __builtin_nontemporal_load(reinterpret_cast<const raw_u32x4*>(p)); }
+  __device__ __forceinline__ float get(int i) const { return __uint_as_float(v[i]); }
+};
+template <typename T> struct Piece<T, 1> {
+  T v;
+  __device__ __forceinline__ void load(const T* p) { v = *p; }
+  __device__ __forceinline__ float get(int) const { return Elem<T>::load(&v, 0); }
+};
+
+struct AttnParts {
+  float* partial;  // [pieces + B][pitch]
+  float2* ml;      // [pieces + B] maximum, sum of weights
+  int2* span;      // [B] first row of the request in `partial`, rows
+  int pitch;
+};
+
+__device__ __forceinline__ int64_t attn_tokens(const int32_t* seq_start, const int32_t* seq_len, const int32_t* tenant_id, int b,
+                                               int64_t M_tok, int T_tenants) {
+  const int64_t start = seq_start[b], n = seq_len[b];
   const int ten = tenant_id[b];
-  if (!span_ok(start, n, M_tok) || ten < 0 || ten >= T_tenants) return;  // the finishing kernel skips it too
-  const int64_t per = (n + S - 1) / S;
-  const int64_t t0 = start + (int64_t)s * per;
-  int64_t t1 = t0 + per;
-  if (t1 > start + n) t1 = start + n;
-  const int ncg = d / VEC;
-  const int cg = threadIdx.x % cgw, tr = threadIdx.x / cgw, TR = kThreads / cgw;
-  const T* q = w_sa + (size_t)ten * d;
-  float acc[MAXP][VEC];
+  return span_ok(start, n, M_tok) && ten >= 0 && ten < T_tenants ? n : 0;
+}
+
+template <typename T, int VEC, int P>
+__global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const T* __restrict__ H, int64_t M_tok, int d, int B,
+                                                                          const int32_t* __restrict__ seq_start,
+                                                                          const int32_t* __restrict__ seq_len,
+                                                                          const int32_t* __restrict__ tenant_id, int T_tenants,
+                                                                          const T* __restrict__ w_sa, AttnParts out) {
+  constexpr int R = P == 1 ? 8 : P == 2 ? 4 : 2;  // rows of a batch: two batches of P * R pieces are in registers
+  constexpr int Lanes = 64 / R;      // lanes that share a row's sum
+  __shared__ float red[2][kAttnMaxWaves][R];
+  __shared__ int64_t wave_sum[kAttnMaxWaves];
+  __shared__ int s_req, s_off;
+  const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x, nw = n_threads >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // ---- this workgroup's piece of the line ----
+  const int chunk = (B + n_threads - 1) / n_threads, b0 = tid * chunk, b1 = b0 + chunk < B ? b0 + chunk : B;
+  int64_t mine = 0;
+  for (int b = b0; b < b1; ++b) mine += attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
+  int64_t incl = mine;
 #pragma unroll
-  for (int pss = 0; pss < MAXP; ++pss)
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) acc[pss][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int64_t tb = t0; tb < t1; tb += kThreads) {
-    const int nb = (int)(t1 - tb < kThreads ? t1 - tb : kThreads);
-    for (int tt = wave; tt < nb; tt += kThreads / 64) {
-      const T* row = H + (size_t)(tb + tt) * d;
-      float u = 0.f;
-      for (int c = lane; c < ncg; c += 64) {
-        float x[VEC], w[VEC];
-        VecLoad<T, VEC>::load(row + (size_t)c * VEC, x);
-        VecLoad<T, VEC>::load(q + (size_t)c * VEC, w);
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) u += x[v] * w[v];
-      }
-      for (int off = 32; off > 0; off >>= 1) u += __shfl_xor(u, off, 64);
-      if (lane == 0) sc[tt] = u;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t o = __shfl_up(incl, off, 64);
+    incl += lane >= off ? o : 0;
+  }
+  if (lane == 63) wave_sum[wave] = incl;
+  __syncthreads();
+  int64_t before = 0, total = 0;
+  for (int i = 0; i < nw; ++i) {
+    before += i < wave ? wave_sum[i] : 0;
+    total += wave_sum[i];
+  }
+  incl += before;
+  const int64_t per = ((total + gridDim.x - 1) / gridDim.x + R - 1) / R * R;
+  const int g = blockIdx.x;
+  int64_t pos = (int64_t)g * per;
+  if (pos >= total) return;
+  if (pos >= incl - mine && pos < incl) {
+    int64_t first = incl - mine;
+    int b = b0;
+    for (;; ++b) {
+      const int64_t n = attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
+      if (pos < first + n) break;
+      first += n;
     }
-    __syncthreads();
-    float mx = threadIdx.x < nb ? sc[threadIdx.x] : -INFINITY;
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) wred[wave] = mx;
-    __syncthreads();
-    float m_new = m_run;
-    for (int w = 0; w < kThreads / 64; ++w) m_new = fmaxf(m_new, wred[w]);
-    const float scale = expf(m_run - m_new);  // 0 for the first block (m_run = -inf)
-    const float pw = threadIdx.x < nb ? expf(sc[threadIdx.x] - m_new) : 0.f;
-    __syncthreads();
-    if (threadIdx.x < nb) sc[threadIdx.x] = pw;
-    float ps = pw;
-    for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off, 64);
-    if (lane == 0) wred[wave] = ps;
-    __syncthreads();
-    float lsum = 0.f;
-    for (int w = 0; w < kThreads / 64; ++w) lsum += wred[w];
-    l_run = l_run * scale + lsum;
-    m_run = m_new;
+    s_req = b;
+    s_off = (int)(pos - first);
+  }
+  __syncthreads();
+  int b = __builtin_amdgcn_readfirstlane(s_req);
+  int off = __builtin_amdgcn_readfirstlane(s_off);  // of the piece's first token in its request
+  int64_t left = total - pos < per ? total - pos : per;
+
+  const int ncg = d / VEC;
+  for (; left > 0; ++b, off = 0) {
+    const int64_t n = attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
+    if (n == 0) continue;
+    const int rows_n = __builtin_amdgcn_readfirstlane((int)(n - off < left ? n - off : left));
+    const T* rows = H + (size_t)(seq_start[b] + off) * d;
+    const T* q = w_sa + (size_t)tenant_id[b] * d;
+    int col[P];
 #pragma unroll
-    for (int pss = 0; pss < MAXP; ++pss) {
-      const int c = cg + pss * cgw;
-      if (c < ncg) {
-        float a[VEC];
+    for (int p = 0; p < P; ++p) {
+      const int c = p * n_threads + tid;
+      col[p] = (c < ncg ? c : ncg - 1) * VEC;  // past the row's end: its last piece, against zeros of w
+    }
+    Piece<T, VEC> x[2][R][P];
+    auto ask = [&](int t, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) a[v] = 0.f;
-        const T* col = H + (size_t)tb * d + (size_t)c * VEC;
-        for (int tt = tr; tt < nb; tt += TR) {
-          float x[VEC];
-          VecLoad<T, VEC>::load(col + (size_t)tt * d, x);
-          const float p = sc[tt];
+      for (int r = 0; r < R; ++r) {
+        const int row = t + r < rows_n ? t + r : rows_n - 1;  // past the end: the last row, with no weight
+        const T* src = rows + (size_t)row * d;
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) a[v] += p * x[v];
+        for (int p = 0; p < P; ++p) v[r][p].load(src + col[p]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    ask(0, x[0]);
+    float w[P][VEC], acc[P][VEC];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      float v[VEC];
+      VecLoad<T, VEC>::load(q + col[p], v);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        w[p][e] = p * n_threads + tid < ncg ? v[e] : 0.f;
+        acc[p][e] = 0.f;
+      }
+    }
+    float m_run = -INFINITY, l_run = 0.f;  // (l_run: of row lane % R of every batch)
+    auto batch = [&](int t, int buf, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
+      float u[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        u[r] = 0.f;
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) u[r] += v[r][p].get(e) * w[p][e];
+      }
+      // sums over the lanes: every step halves the rows a lane holds, row lane / Lanes is left
+#pragma unroll
+      for (int h = R / 2, o = 32; h >= 1; h >>= 1, o >>= 1)
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+          const bool up = (lane & o) != 0;
+          const float give = up ? u[i] : u[i + h], keep = up ? u[i + h] : u[i];
+          u[i] = keep + __shfl_xor(give, o, 64);
         }
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[pss][v] = acc[pss][v] * scale + a[v];
+      for (int o = Lanes / 2; o >= 1; o >>= 1) u[0] += __shfl_xor(u[0], o, 64);
+      if (lane % Lanes == 0) red[buf][wave][lane / Lanes] = u[0];
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // LDS only: the next rows stay on their way
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      float s = 0.f;
+      for (int i = lane / R; i < nw; i += Lanes) s += red[buf][i][lane % R];
+#pragma unroll
+      for (int o = R; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
+      if (t + lane % R >= rows_n) s = -INFINITY;
+      float m_new = s;
+#pragma unroll
+      for (int o = 1; o < R; o <<= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, o, 64));
+      m_new = fmaxf(m_run, m_new);
+      const float ref = m_new == -INFINITY ? 0.f : m_new;
+      const float scale = expf(m_run - ref), pw = expf(s - ref);  // (first batch: scale 0)
+      l_run = l_run * scale + pw;
+      m_run = m_new;
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[p][e] *= scale;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        // (opaque: the floats of the scores are formed again rather than kept)
+        if constexpr (VEC * sizeof(T) == 16)
+#pragma unroll
+          for (int p = 0; p < P; ++p) asm volatile("" : "+v"(v[r][p].v));
+        const float a = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pw), r));
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc[p][e] += a * v[r][p].get(e);
       }
+    };
+    for (int t = 0; t < rows_n; t += 2 * R) {
+      ask(t + R, x[1]);
+      batch(t, 0, x[0]);
+      if (t + R >= rows_n) break;
+      ask(t + 2 * R, x[0]);
+      batch(t + R, 1, x[1]);
     }
-    __syncthreads();
-  }
-  float* out = partial + ((size_t)b * S + s) * d;
-  if (TR == 1) {
 #pragma unroll
-    for (int pss = 0; pss < MAXP; ++pss) {
-      const int c = cg + pss * cgw;
-      if (c < ncg) {
+    for (int o = 1; o < R; o <<= 1) l_run += __shfl_xor(l_run, o, 64);
+    const size_t idx = (size_t)g + b;
+    float* const o = out.partial + idx * out.pitch;
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) out[(size_t)c * VEC + v] = acc[pss][v];
-      }
+    for (int p = 0; p < P; ++p)
+      if (p * n_threads + tid < ncg)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o[col[p] + e] = acc[p][e];
+    if (tid == 0) {
+      out.ml[idx] = float2{m_run, l_run};
+      if (off == 0) out.span[b] = int2{(int)idx, (int)((pos + n - 1) / per) - g + 1};
     }
-  } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) red[threadIdx.x * VEC + v] = acc[0][v];
-    __syncthreads();
-    if (tr == 0 && cg < ncg) {
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        float a = 0.f;
-        for (int r = 0; r < TR; ++r) a += red[(r * cgw + cg) * VEC + v];
-        out[(size_t)cg * VEC + v] = a;
-      }
-    }
-  }
-  if (threadIdx.x == 0) {
-    ml[((size_t)b * S + s) * 2] = m_run;
-    ml[((size_t)b * S + s) * 2 + 1] = l_run;
+    pos += rows_n;
+    left -= rows_n;
+    __syncthreads();  // (the next request's first batch writes the buffer that the last one's may still be read from)
   }
 }
 
-// Finish of the self-attention pooler: one workgroup of 1024 threads per request merges the slices (each holds a
-// sum weighted by exp(u - m_s): brought to the common maximum and normalised), then z = g(h), the seven logits and
-// the selection.  A thread owns four neighbouring columns; the S slice sums of a column are added as eight
-// interleaved running sums (slice s goes to sum s % 8) that are combined pairwise at the end, so eight loads are
-// in flight and the order is fixed.
-constexpr int kFinishThreads = 1024;
-constexpr int kFinishWays = 8;
-
-template <typename T>
-__global__ void __launch_bounds__(kFinishThreads) selfattn_finish_kernel(int64_t M_tok, int d,
-                                                                         const int32_t* __restrict__ seq_start,
-                                                                         const int32_t* __restrict__ seq_len,
-                                                                         const int32_t* __restrict__ tenant_id,
-                                                                         int T_tenants, const T* __restrict__ Wr,
-                                                                         int act, RationalCoef coef, int top_k, int S,
-                                                                         const float* __restrict__ partial,
-                                                                         const float* __restrict__ ml,
-                                                                         uint8_t* __restrict__ route_out,
-                                                                         float* __restrict__ logits_out) {
-  __shared__ float wsum[kFinishThreads / 64][MILORA_NUM_SITES];
-  __shared__ float wts[kMaxSplits];  // weight of each slice's partial result in the pooled state
-  const int b = blockIdx.x;
-  const int64_t start = seq_start[b], n = seq_len[b];
-  const int t = tenant_id[b];
-  if (!span_ok(start, n, M_tok) || t < 0 || t >= T_tenants) {
-    if (threadIdx.x == 0) route_out[b] = MILORA_ROUTE_NONE;
-    if (logits_out && threadIdx.x < MILORA_NUM_SITES)
-      logits_out[b * MILORA_NUM_SITES + threadIdx.x] = __uint_as_float(0x7fc00000u);
+// Finish of the self-attention pooler: a workgroup of 512 threads merges CL * 4 columns of a request's rows (each holds a
+// sum weighted by exp(u - m_s): brought to the common maximum and normalised), 512 / CL rows side by side, eight of each on
+// their way, and goes on as pool_route_kernel does.
+template <typename T, int CL>
+__global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRouteArgs<T> p, AttnParts in) {
+  constexpr int SW = CL * 4, TL = kPoolThreads / CL, kWaves = (CL + 63) / 64;  // waves that finish
+  __shared__ __align__(16) float red[TL][SW];
+  __shared__ float wave_lg[kWaves][8];
+  const int c = blockIdx.x, b = blockIdx.y;
+  const int cl = threadIdx.x % CL, tl = threadIdx.x / CL, lane = threadIdx.x & 63;
+  const int2 sp = in.span[b];  // (asked for with the facts that say whether it means anything)
+  const int64_t start = p.seq_start[b], n = p.seq_len[b];
+  const int ten = p.tenant_id[b];
+  if (!span_ok(start, n, p.M_tok) || ten < 0 || ten >= p.T_tenants) {
+    if (c == 0) no_route(p, b);
     return;
   }
-  float acc[MILORA_NUM_SITES];
+  // the first 8 TL rows and their maxima before anything waits, the router weights behind them
+  const float2* ml = in.ml + sp.x;
+  const int col = c * SW + cl * 4 < in.pitch ? c * SW + cl * 4 : 0;  // (past the end: never used)
+  const f32x4* rows = reinterpret_cast<const f32x4*>(in.partial + (size_t)sp.x * in.pitch + col);
+  f32x4 x[8];
+  float m[8];
+  auto ask = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j) acc[j] = 0.f;
-  const T* w = Wr + (size_t)t * MILORA_NUM_SITES * d;
-  const bool vec = (d % 4) == 0;  // rows of `partial` are then 16-byte aligned
-  const float* pb = partial + (size_t)b * S * d;
-  {
-    const float* mlb = ml + (size_t)b * S * 2;
-    float mx = -INFINITY, z = 0.f;
-    for (int s = 0; s < S; ++s) mx = fmaxf(mx, mlb[2 * s]);
-    for (int s = 0; s < S; ++s) z += mlb[2 * s + 1] * expf(mlb[2 * s] - mx);
-    if (threadIdx.x < S) wts[threadIdx.x] = mlb[2 * threadIdx.x + 1] > 0.f ? expf(mlb[2 * threadIdx.x] - mx) / z : 0.f;
-  }
-  __syncthreads();
-  for (int i0 = threadIdx.x * 4; i0 < d; i0 += kFinishThreads * 4) {
-    const int nv = d - i0 < 4 ? d - i0 : 4;
-    float h[4];
-    float run[kFinishWays][4];
-#pragma unroll
-    for (int u = 0; u < kFinishWays; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) run[u][v] = 0.f;
-    for (int s0 = 0; s0 < S; s0 += kFinishWays) {
-#pragma unroll
-      for (int u = 0; u < kFinishWays; ++u) {
-        if (s0 + u < S) {
-          const float* q = pb + (size_t)(s0 + u) * d + i0;
-          float x[4] = {0.f, 0.f, 0.f, 0.f};
-          if (vec) {
-            const float4 x4 = *reinterpret_cast<const float4*>(q);
-            x[0] = x4.x; x[1] = x4.y; x[2] = x4.z; x[3] = x4.w;
-          } else {
-            for (int v = 0; v < nv; ++v) x[v] = q[v];
-          }
-          const float wgt = wts[s0 + u];
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (wgt != 0.f) run[u][v] += wgt * x[v];  // a slice without tokens holds nothing to read
-        }
-      }
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u * TL < sp.y ? i0 + u * TL : sp.y - 1;
+      m[u] = ml[i].x;
+      x[u] = rows[(size_t)i * (in.pitch / 4)];
     }
+  };
+  float2 own = float2{-INFINITY, 0.f};
+  if (lane < sp.y) own = ml[lane];
+  ask(tl);
+  float wr[MILORA_NUM_SITES][4];
+  load_router_weights<T, CL>(p, ten, threadIdx.x, c * SW + 4 * (int)threadIdx.x, wr);
+  __builtin_amdgcn_sched_barrier(0);
+  float mx = own.x;
+  for (int i = lane + 64; i < sp.y; i += 64) mx = fmaxf(mx, ml[i].x);
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-      h[v] = ((run[0][v] + run[1][v]) + (run[2][v] + run[3][v])) + ((run[4][v] + run[5][v]) + (run[6][v] + run[7][v]));
-    for (int v = 0; v < nv; ++v) {
-      const float z = activate(h[v], act, coef);
+  for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  const float ref = mx == -INFINITY ? 0.f : mx;
+  float z = own.y * expf(own.x - ref);
+  for (int i = lane + 64; i < sp.y; i += 64) z += ml[i].y * expf(ml[i].x - ref);
 #pragma unroll
-      for (int j = 0; j < MILORA_NUM_SITES; ++j) acc[j] += z * Elem<T>::load(w, (size_t)j * d + i0 + v);
+  for (int o = 1; o < 64; o <<= 1) z += __shfl_xor(z, o, 64);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = tl; i0 < sp.y; i0 += 8 * TL) {
+    if (i0 != tl) ask(i0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + u * TL < sp.y) acc += expf(m[u] - ref) / z * x[u];
+  }
+  if constexpr (TL > 1) {
+    *reinterpret_cast<f32x4*>(&red[tl][cl * 4]) = acc;
+    __syncthreads();
+    if (threadIdx.x < CL) {
+      acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < TL; ++i) acc += *reinterpret_cast<const f32x4*>(&red[i][cl * 4]);
     }
   }
+  float lg[8];
+  if (threadIdx.x < kWaves * 64) wave_logits(p, threadIdx.x < CL, c * SW + 4 * (int)threadIdx.x, acc, 1.0f, wr, lg);
+  if constexpr (kWaves > 1) {
+    if (threadIdx.x < kWaves * 64 && lane == 0)
 #pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j) {
-    float v = acc[j];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6][j] = v;
+      for (int j = 0; j < 8; ++j) wave_lg[threadIdx.x >> 6][j] = lg[j];
+    __syncthreads();
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float logit[MILORA_NUM_SITES];
-    for (int j = 0; j < MILORA_NUM_SITES; ++j) {
-      float v = 0.f;
-      for (int wv = 0; wv < kFinishThreads / 64; ++wv) v += wsum[wv][j];
-      logit[j] = v;
-      if (logits_out) logits_out[b * MILORA_NUM_SITES + j] = v;
+  if (threadIdx.x >= 64) return;
+  if constexpr (kWaves > 1)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      lg[j] = wave_lg[0][j];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) lg[j] += wave_lg[w][j];
     }
-    route_out[b] = select_route(logit, top_k);
-  }
+  finish_request(p, b, c, lane, lg);
 }
 
-// Token slices per request of the self-attention pooler.
-int pick_splits(int B, int64_t M_tok) {
-  int64_t avg = (M_tok + B - 1) / B;
-  int64_t s = (4096 + B - 1) / B;  // aim at a few thousand workgroups
-  if (s > (avg + 15) / 16) s = (avg + 15) / 16;
-  if (s > kMaxSplits) s = kMaxSplits;
-  if (s < 1) s = 1;
-  return (int)s;
+// Workspace of the self-attention pooler.  Pieces of the line: two workgroups of up to eight waves per compute unit, one of
+// more, four of up to four; none shorter than eight tokens.
+// Column lanes of a finishing workgroup: few rows to merge, wide slabs (many requests are then few workgroups, and a row that fits
+// one of them needs no hand-over); more, narrow ones, so that all rows are on their way together.  Calls of 200 prompts of 16
+// to 128 tokens, d = 4096 (4 rows each): 133 us with 32 lanes, 53 with
+// 512; 32 of 256 (17 rows): 36 us with 32, 29 with 128; 16 of 1024 to 2048 (33 rows): the finishing launch 10.6 us with 32, 11.6 with 128.
+struct AttnCarve {
+  int pieces, lanes, C, pitch;
+  size_t ml, span, share, total;  // byte offsets, and the size
+};
+AttnCarve carve_attn(int B, int d, int64_t M_tok, int waves) {
+  AttnCarve a;
+  const int64_t most = (M_tok + 7) / 8;
+  a.pieces = waves <= 4 ? 1024 : waves <= 8 ? 512 : 256;
+  if (a.pieces > most) a.pieces = (int)most;
+  const int to_merge = a.pieces / B + 1;
+  a.lanes = to_merge <= 8 ? 512 : to_merge <= 20 ? 128 : 32;
+  a.C = (d + a.lanes * 4 - 1) / (a.lanes * 4);
+  a.pitch = (d + 3) / 4 * 4;
+  const size_t rows = (size_t)a.pieces + B;
+  a.ml = align_up(rows * a.pitch * sizeof(float), 256);
+  a.span = a.ml + align_up(rows * sizeof(float2), 256);
+  a.share = a.span + align_up((size_t)B * sizeof(int2), 256);
+  a.total = a.share + align_up((size_t)B * ((d + 127) / 128) * 4 * 16, 256);
+  return a;
 }
 
 // Token slices per request of pool_route_kernel with C column slabs: one, unless the requests are so few that
@@ -650,6 +773,12 @@ PoolRouteCarve carve_pool_route(int B, int d, int64_t M_tok, int slab_cols, bool
 
 std::atomic<uint32_t> g_route_calls{0};
 
+template <typename T>
+void new_tag(PoolRouteArgs<T>& a) {
+  a.tag_hi = ++g_route_calls;
+  a.tag_lo = (a.tag_hi * 2654435761u ^ 0x9e3779b9u) | 1u;
+}
+
 template <typename T, int VEC>
 int launch_pool_route(PoolRouteArgs<T> a, int B, int64_t M_tok, void* workspace, size_t workspace_bytes,
                       hipStream_t st) {
@@ -658,8 +787,7 @@ int launch_pool_route(PoolRouteArgs<T> a, int B, int64_t M_tok, void* workspace,
   if ((size_t)cv.C * cv.S > 65535u * 32u) return MILORA_ERANGE;
   a.S = cv.S;
   a.C = cv.C;
-  a.tag_hi = ++g_route_calls;
-  a.tag_lo = (a.tag_hi * 2654435761u ^ 0x9e3779b9u) | 1u;
+  new_tag(a);
   a.partial = (float*)((char*)workspace + cv.partial);
   a.arrived = (u32x2*)((char*)workspace + cv.arrived);
   a.share = (u32x4*)((char*)workspace + cv.share);
@@ -667,16 +795,25 @@ int launch_pool_route(PoolRouteArgs<T> a, int B, int64_t M_tok, void* workspace,
   return check_launch();
 }
 
-template <typename T, int VEC>
-void launch_selfattn(const void* H, int64_t M_tok, int d, const int32_t* ss, const int32_t* sl, const int32_t* tenant_id,
-                     int T_tenants, const void* w_sa, int B, int S, float* partial, float* ml, hipStream_t st) {
-  int ncg = d / VEC, cgw = 1;
-  while (cgw < ncg && cgw < kThreads) cgw <<= 1;
-  hipLaunchKernelGGL((pool_selfattn_kernel<T, VEC>), dim3(S, B), dim3(kThreads), 0, st, (const T*)H, M_tok, d, ss, sl,
-                     tenant_id, T_tenants, (const T*)w_sa, S, cgw, partial, ml);
+template <typename T, int VEC, int P>
+int launch_attn(PoolRouteArgs<T> a, const T* w_sa, int B, void* workspace, hipStream_t st) {
+  const int pieces_of_row = a.d / VEC, waves = (pieces_of_row + 64 * P - 1) / (64 * P);
+  const AttnCarve cv = carve_attn(B, a.d, a.M_tok, waves);
+  char* const ws = (char*)workspace;
+  AttnParts parts{(float*)ws, (float2*)(ws + cv.ml), (int2*)(ws + cv.span), cv.pitch};
+  hipLaunchKernelGGL((pool_selfattn_kernel<T, VEC, P>), dim3(cv.pieces), dim3(waves * 64), 0, st, a.H, a.M_tok, a.d, B, a.seq_start,
+                     a.seq_len, a.tenant_id, a.T_tenants, w_sa, parts);
+  int rc = check_launch();
+  if (rc) return rc;
+  a.C = cv.C;
+  new_tag(a);
+  a.share = (u32x4*)(ws + cv.share);
+  const dim3 grid(cv.C, B);
+  if (cv.lanes == 512) hipLaunchKernelGGL((selfattn_finish_kernel<T, 512>), grid, dim3(kPoolThreads), 0, st, a, parts);
+  else if (cv.lanes == 128) hipLaunchKernelGGL((selfattn_finish_kernel<T, 128>), grid, dim3(kPoolThreads), 0, st, a, parts);
+  else hipLaunchKernelGGL((selfattn_finish_kernel<T, 32>), grid, dim3(kPoolThreads), 0, st, a, parts);
+  return check_launch();
 }
-
-size_t partial_bytes(int B, int S, int d) { return align_up((size_t)B * S * d * sizeof(float), 256); }
 
 }  // namespace
 
@@ -686,8 +823,12 @@ using namespace milora;
 
 extern "C" size_t milora_route_workspace_bytes(int B, int d, int64_t M_tok) {
   if (B < 1 || d < 1 || M_tok < 1) return 0;
-  const int S = pick_splits(B, M_tok);
-  size_t need = partial_bytes(B, S, d) + align_up((size_t)B * S * 2 * sizeof(float), 256);  // self-attention pooler
+  size_t need = 0;
+  for (int waves : {4, 8, kAttnMaxWaves}) {  // of the self-attention pooler: a wave of it holds at most 512 columns, 1024 if there are 16
+    const int most = waves < kAttnMaxWaves ? waves * 512 : d;
+    const size_t n = carve_attn(B, d < most ? d : most, M_tok, waves).total;
+    if (n > need) need = n;
+  }
   for (int slab_cols : {32, 128, 256}) {  // the slab widths pool_route_kernel is built for
     const size_t n = carve_pool_route(B, d, M_tok, slab_cols, false).total;
     if (n > need) need = n;
@@ -704,21 +845,6 @@ int route_typed(const void* H, int64_t M_tok, int d, const int32_t* seq_start, c
                 size_t workspace_bytes, hipStream_t st) {
   constexpr int VEC = 16 / (int)sizeof(T);  // elements of a 16-byte load
   const bool vec = ((uintptr_t)H % 16) == 0 && d % VEC == 0;
-  if (pool == MILORA_POOL_SELFATTN) {
-    if (workspace_bytes < milora_route_workspace_bytes(B, d, M_tok)) return MILORA_EWORKSPACE;
-    const int S = pick_splits(B, M_tok);
-    float* partial = (float*)workspace;
-    float* ml = (float*)((char*)workspace + partial_bytes(B, S, d));
-    if (vec && ((uintptr_t)w_sa % 16) == 0)
-      launch_selfattn<T, VEC>(H, M_tok, d, seq_start, seq_len, tenant_id, n_tenants, w_sa, B, S, partial, ml, st);
-    else
-      launch_selfattn<T, 1>(H, M_tok, d, seq_start, seq_len, tenant_id, n_tenants, w_sa, B, S, partial, ml, st);
-    int rc = check_launch();
-    if (rc != MILORA_OK) return rc;
-    hipLaunchKernelGGL((selfattn_finish_kernel<T>), dim3(B), dim3(kFinishThreads), 0, st, M_tok, d, seq_start, seq_len,
-                       tenant_id, n_tenants, (const T*)Wr, act, coef, top_k, S, partial, ml, route_out, logits_out);
-    return check_launch();
-  }
   PoolRouteArgs<T> a;
   a.H = (const T*)H;
   a.M_tok = M_tok;
@@ -734,6 +860,16 @@ int route_typed(const void* H, int64_t M_tok, int d, const int32_t* seq_start, c
   a.route_out = route_out;
   a.logits_out = logits_out;
   a.coef = coef;
+  if (pool == MILORA_POOL_SELFATTN) {
+    if (workspace_bytes < milora_route_workspace_bytes(B, d, M_tok)) return MILORA_EWORKSPACE;
+    const T* const w = (const T*)w_sa;
+    if (vec && ((uintptr_t)w_sa % 16) == 0) {
+      if constexpr (kSelfAttnMaxD > kAttnMaxWaves * 64 * VEC)  // more than one piece of a row per thread of the largest workgroup
+        if (d > kAttnMaxWaves * 64 * VEC) return launch_attn<T, VEC, 2>(a, w, B, workspace, st);
+      return launch_attn<T, VEC, 1>(a, w, B, workspace, st);
+    }
+    return d <= kAttnMaxWaves * 64 ? launch_attn<T, 1, 1>(a, w, B, workspace, st) : launch_attn<T, 1, 8>(a, w, B, workspace, st);
+  }
   if (vec) return launch_pool_route<T, VEC>(a, B, M_tok, workspace, workspace_bytes, st);
   return launch_pool_route<T, 1>(a, B, M_tok, workspace, workspace_bytes, st);
 }

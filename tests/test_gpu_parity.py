@@ -187,6 +187,48 @@ def test_route_self_attention_long_prompts_full_width():
         np.testing.assert_allclose(to_f64(logits), ref.logits, atol=1e-4 * max(1.0, np.abs(ref.logits).max()))
 
 
+@pytest.mark.parametrize("dtype,d,B,plen,shift", [("bf16", 64, 300, (1, 9), 0), ("bf16", 2048, 40, (1, 50), 0), ("bf16", 4096, 1, (1, 1), 0),
+                                                  ("bf16", 5120, 4, (1, 700), 0), ("bf16", 8192, 3, (100, 900), 0), ("f32", 2052, 30, (1, 40), 0),
+                                                  ("f32", 8192, 3, (1, 300), 0), ("bf16", 1000, 7, (1, 90), 1), ("f32", 1500, 5, (1, 60), 1),
+                                                  ("bf16", 8192, 2, (1, 60), 1)])
+def test_route_self_attention_pieces_of_the_token_line(dtype, d, B, plen, shift):
+    """The line of all valid tokens is cut without regard to requests: many short requests in a piece, one request in many,
+    requests that take no part in between, every register shape of the kernel (row widths, `shift`: rows that allow no 16-byte
+    loads), and replays of a recorded call on new states.  Logit bound: 5e-5 of the largest one (fp32 sums of up to 8192
+    products of scores of a few units; the exponentials add 2^-24 times the largest score, about 10)."""
+    wl = small(dtype=dtype, d=d, T=5, B=B, prompt_len=plen, tenants="uniform", seed=d + B)
+    H0, ss, sl = synth.prompts(wl, 0, DEV)
+    H = torch.empty(H0.numel() + shift, dtype=H0.dtype, device=DEV)[shift:].view_as(H0).copy_(H0)
+    tid = synth.tenant_ids(wl)
+    skipped = []
+    if B > 3:
+        skipped = [0, B // 2, B - 1]
+        tid[0], sl[B // 2], ss[B - 1] = wl.T, 0, H.shape[0]
+    Wr = synth.router_weights(wl, 0, DEV)
+    w_sa = synth.selfattn_query(wl, 0, DEV) * 2
+    keep = np.array([b for b in range(B) if b not in skipped])
+    args = ss.to(DEV), sl.to(DEV), tid.to(DEV)
+    route_g = torch.empty(B, dtype=torch.uint8, device=DEV)
+    ws = torch.full((mb.route_workspace_bytes(B, d, H.shape[0]),), 255, dtype=torch.uint8, device=DEV)
+    mb.milora_route(H, *args, Wr, "selfattn", "gelu", w_sa=w_sa, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mb.milora_route(H, *args, Wr, "selfattn", "gelu", w_sa=w_sa, route_out=route_g, want_logits=False, workspace=ws)
+    for rep in range(3):
+        H.copy_(torch.roll(H0, shifts=5 * rep, dims=1))
+        route, logits = mb.milora_route(H, *args, Wr, "selfattn", "gelu", w_sa=w_sa)
+        ref = oracle.route(np_of(H), ss.numpy()[keep], sl.numpy()[keep], tid.numpy()[keep], np_of(Wr), mb.POOL["selfattn"], oracle.ACT_GELU,
+                           w_sa=np_of(w_sa))
+        assert_routes_match(route[keep], ref, wl.torch_dtype, f"rep {rep}")
+        np.testing.assert_allclose(to_f64(logits)[keep], ref.logits, atol=5e-5 * max(1.0, np.abs(ref.logits).max()))
+        assert (route.cpu().numpy()[skipped] == mb.ROUTE_NONE).all() and torch.isnan(logits[skipped]).all()
+        route_g.fill_(77)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(route_g, route), f"replay {rep}"
+
+
 def test_route_padded_prompts_and_bad_requests():
     wl = small(dtype="bf16", d=512, T=4, B=6, prompt_len=(5, 64), pad_to=64, seed=5)
     H, ss, sl = synth.prompts(wl, 0, DEV)

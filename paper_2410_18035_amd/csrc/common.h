@@ -39,17 +39,15 @@ typedef uint16_t bf16_t;  // raw bits
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
-// Round-to-nearest-even; NaN stays NaN.
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x0040u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
-
+// Round-to-nearest-even; NaN stays NaN: the chip's conversion of two values, whose bits are those of the rounding by integer
+// arithmetic for all 2^32 inputs, in one instruction instead of fourteen (a wave issues one every four cycles or more, and a
+// wave of the 256 x 256 tiles rounds 256 values per lane: seven linears of 32768 rows 11.68 -> 11.42 ms, of 777 rows 504 -> 488 us).
+typedef __bf16 cvt_bf16x2 __attribute__((ext_vector_type(2)));
+typedef float cvt_f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(cvt_f32x2{lo, hi}, cvt_bf16x2));
 }
+__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 

@@ -20,6 +20,8 @@ namespace milora {
 namespace {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef __attribute__((address_space(1))) const u32x4_a2 gu32x4_a2;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kTM = 256, kTN = 256, kTK = 64;
 constexpr int kThreadsP = 256;
@@ -224,10 +226,14 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
   wait_vm<0>();
   __syncthreads();
 
-  // ---- LoRA term of the routed rows as one more k step per 32 ranks ----------------------------------------
+  // ---- LoRA term of the routed rows as one more k step per 32 ranks, two of them filled together ------------
   // t = X W^A (fp32) goes in as bf16 hi + lo: hi in the first k half of a block, lo in the second, against the
-  // same 32 rows of the tenant's W^B in both halves; rows of other tenants and unrouted rows enter as zeros.
-  int* ctl = (int*)(lds + 2 * kHalfBytes);  // ring slots 0 and 1 hold the operand blocks
+  // same 32 rows of the tenant's W^B in both halves; rows of other tenants and unrouted rows enter as zeros.  Bound by the
+  // instructions of filling a step: W^B in pieces of 8 ranks x 8 columns, 16-byte loads turned with byte permutes, t four ranks of
+  // a row at a time straight into its two halves; and by the round trips to t, about 3 us each (32 loads of two bytes a thread,
+  // t by way of LDS, one step at a time: a call of 777 rows on 4096 x 11008 with a tenant of rank 64 131 us, 120 so, 97 without).
+  int* ctl = (int*)(lds + 4 * kHalfBytes);  // ring slots 0 .. 3 hold the operand blocks
+  int* const row_ten = ctl + 16;            // tenant of each row of the tile, -1: no LoRA term
   int my_ten = -1;
   {
     const int64_t m = m0 + tid;
@@ -238,6 +244,7 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
       if (r) my_ten = tenant;
     }
   }
+  row_ten[tid] = my_ten;
   if (tid == 0) ctl[1] = 0;  // set: W^B of some tenant of the tile holds Inf or NaN
   int last = -1;
   for (;;) {
@@ -255,93 +262,104 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
     if (cur == 0x7fffffff) break;
     const int r = p.ad.rank[cur];
     gbf16* Bm = in_global(p.ad.B[cur * MILORA_NUM_SITES + p.site]);
-    for (int c0 = 0; c0 < r; c0 += 32) {
+    for (int c0 = 0; c0 < r; c0 += 64) {
       int tb = tid;  // opaque: addresses formed from it stay inside the loop instead of being spilled in front of it
       asm volatile("" : "+v"(tb));
-      const int n = n0 + tb;
-      // thread tid fills row tid of the X side and row tb of the W side
-      const uint32_t rb = (uint32_t)(tb & 15);
-      const uint32_t blk = (uint32_t)(tb >> 7) * kHalfBytes + (uint32_t)((tb >> 4) & 7) * kBlockBytes + rb * 128;
-      // this column's 32 values of W^B: asked for first, used last
-      uint16_t bv[32];
+      const int steps = r - c0 > 32 ? 2 : 1;
+      // W side: ranks c0 + 8 gq .. + 7 of columns 8 pc .. + 7, asked for first, used last
+      const int pc = tb & 31, gq = tb >> 5, cw = c0 + gq * 8;
+      const bool wput = gq < steps * 4;
+      u32x4 a[8];
 #pragma unroll
-      for (int c = 0; c < 32; ++c) bv[c] = Bm[(size_t)(c0 + c < r ? c0 + c : r - 1) * p.d2 + (n < p.d2 ? n : p.d2 - 1)];
-      // t of the tile's 256 rows for these 32 ranks, the shrink's parts added in part order, through LDS: eight
-      // lanes read the 128 bytes of a row (whole lines), then every thread picks up its own row
-      float* const ts = reinterpret_cast<float*>(lds + 2 * kHalfBytes + 1024);  // [256][33]
-      const int cq = c0 + (tb & 7) * 4;
-      const bool vec = (p.ad.r_max & 3) == 0 && cq + 3 < p.ad.r_max;
+      for (int i = 0; i < 8; ++i) a[i] = u32x4{0u, 0u, 0u, 0u};
+      if (wput && n0 + pc * 8 < p.d2) {
+        gbf16* b = Bm + (size_t)cw * p.d2 + n0 + pc * 8;
 #pragma unroll
-      for (int i0 = 0; i0 < 8; i0 += 4) {
-        f32x4 v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const float* q[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t mr = m0 + (tb >> 3) + 32 * (i0 + i);
-          q[i] = p.t + (size_t)(mr < p.M ? mr : p.M - 1) * p.ad.r_max + cq;
-        }
-        if (vec) {
-          for (int k0 = 0; k0 < p.parts; k0 += 4) {  // four rows and four parts in flight
-            f32x4 x[4][4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-              for (int i = 0; i < 4; ++i)
-                x[k][i] = *reinterpret_cast<const f32x4*>(q[i] + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              if (k0 + k < p.parts)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] += x[k][i];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (cq + e < p.ad.r_max)
-                for (int part = 0; part < p.parts; ++part) v[i][e] += q[i][part * p.t_stride + e];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ts[((tb >> 3) + 32 * (i0 + i)) * 33 + (tb & 7) * 4 + e] = v[i][e];
+        for (int i = 0; i < 8; ++i)
+          if (cw + i < r) a[i] = *(gu32x4_a2*)(b + (size_t)i * p.d2);  // (whole pieces of 8 columns, d2 % 16 == 0, at any alignment)
       }
-      __syncthreads();
+      // X side: eight lanes take 32 ranks of a row, the shrink's parts added in part order
+      const int rq = tb & 7;
+      for (int st = 0; st < steps; ++st) {
+        const int cq = c0 + st * 32 + rq * 4;
+        const bool vec = (p.ad.r_max & 3) == 0 && cq + 3 < p.ad.r_max;
+#pragma unroll 1
+        for (int i0 = 0; i0 < 8; i0 += 4) {
+          f32x4 v[4];
+          const float* q[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        u32x4 hi, lo, wb;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float tv[2];
-          uint32_t bw[2];
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int c = c0 + g * 8 + e * 2 + h;
-            tv[h] = (my_ten == cur && c < r) ? ts[tb * 33 + (c - c0)] : 0.f;
-            bw[h] = (c < r && n < p.d2) ? (uint32_t)bv[g * 8 + e * 2 + h] : 0u;
+          for (int i = 0; i < 4; ++i) {
+            v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int64_t mr = m0 + (tb >> 3) + 32 * (i0 + i);
+            q[i] = p.t + (size_t)(mr < p.M ? mr : p.M - 1) * p.ad.r_max + cq;
           }
-          const bf16_t h0b = f32_to_bf16(tv[0]), h1b = f32_to_bf16(tv[1]);
-          hi[e] = (uint32_t)h0b | ((uint32_t)h1b << 16);
-          lo[e] = pack_bf16x2(tv[0] - bf16_to_f32(h0b), tv[1] - bf16_to_f32(h1b));
-          wb[e] = bw[0] | (bw[1] << 16);
-        }
-        if (taint(taint(taint(taint(0.f, wb[0]), wb[1]), wb[2]), wb[3]) != 0.f) {
+          if (vec) {
+            for (int k0 = 0; k0 < p.parts; k0 += 4) {  // four rows and four parts in flight
+              f32x4 x[4][4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) wb[e] = finite2(wb[e]);
+              for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                  x[k][i] = *reinterpret_cast<const f32x4*>(q[i] + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride);
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                if (k0 + k < p.parts)
+#pragma unroll
+                  for (int i = 0; i < 4; ++i) v[i] += x[k][i];
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (cq + e < p.ad.r_max)
+                  for (int part = 0; part < p.parts; ++part) v[i][e] += q[i][part * p.t_stride + e];
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = (tb >> 3) + 32 * (i0 + i);
+            const bool ours = row_ten[row] == cur;
+            float tv[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tv[e] = ours && cq + e < r ? v[i][e] : 0.f;
+            u32x2 hi, lo;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              hi[h] = pack_bf16x2(tv[2 * h], tv[2 * h + 1]);
+              lo[h] = pack_bf16x2(tv[2 * h] - __uint_as_float(hi[h] << 16), tv[2 * h + 1] - __uint_as_float(hi[h] & 0xffff0000u));
+            }
+            unsigned char* const x = lds + (2 * st + (row >> 7)) * kHalfBytes + ((row >> 4) & 7) * kBlockBytes + (row & 15) * 128 + (rq & 1) * 8;
+            *(u32x2*)(x + (((rq >> 1) ^ swz(row & 15)) << 4)) = hi;
+            *(u32x2*)(x + ((((rq >> 1) + 4) ^ swz(row & 15)) << 4)) = lo;
+          }
+        }
+      }
+      if (wput) {
+        float bad[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bad[e] = taint(bad[e], a[i][e]);
+        if ((bad[0] + bad[1]) + (bad[2] + bad[3]) != 0.f) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[i][e] = finite2(a[i][e]);
           ctl[1] = 1;
         }
-        const uint32_t o_hi = blk + (((uint32_t)g ^ (uint32_t)swz(rb)) << 4);
-        const uint32_t o_lo = blk + (((uint32_t)(g + 4) ^ (uint32_t)swz(rb)) << 4);
-        *(u32x4*)(lds + o_hi) = hi;
-        *(u32x4*)(lds + o_lo) = lo;
-        *(u32x4*)(lds + (kBlocksM / 2) * kBlockBytes + o_hi) = wb;
-        *(u32x4*)(lds + (kBlocksM / 2) * kBlockBytes + o_lo) = wb;
+        u32x4 at[8];
+        transpose8(a, at);
+        // (columns 8 pc .. + 7: one half of a block of 16)
+        unsigned char* const wst = lds + (2 * (gq >> 2) + (pc >> 4)) * kHalfBytes + (kBlocksM / 2 + ((pc >> 1) & 7)) * kBlockBytes;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int n = (pc & 1) * 8 + j;
+          *(u32x4*)(wst + n * 128 + (((gq & 3) ^ swz(n)) << 4)) = at[j];
+          *(u32x4*)(wst + n * 128 + ((((gq & 3) + 4) ^ swz(n)) << 4)) = at[j];
+        }
       }
       __syncthreads();
-      mma64(wm, wn, []() {}, [](int) {});
+      for (int st = 0; st < steps; ++st) mma64(2 * st + wm, 2 * st + wn, []() {}, [](int) {});
       __syncthreads();
     }
     last = cur;

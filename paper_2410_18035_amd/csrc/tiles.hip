@@ -303,26 +303,31 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
         const int my_first = row_group[xr], my_rank = row_ten[xr] >= 0 ? row_rank[xr] : 0;
         const int wc = tb % kPieces * 8, wg = tb / kPieces;
         const bool tvec = (p.ad.r_max & 3) == 0;
-        auto load_t = [&](int c0, float (&tv)[8]) __attribute__((always_inline)) {  // ranks c0 .. c0 + 7 of row xr
+        constexpr int kFly = C::OCC == 1 ? 4 : 2;  // parts in flight: registers of half a compute unit allow two
+        auto ask_t = [&](int c0, int k0, f32x4 (&v)[2][kFly]) __attribute__((always_inline)) {  // parts k0 .. of ranks c0 .. c0 + 7 of row xr
           const float* tp = p.t + (size_t)(m0 + xr) * p.ad.r_max + c0;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) tv[e] = 0.f;
+          for (int k = 0; k < kFly; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              v[h][k] = *reinterpret_cast<const f32x4*>(tp + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride + h * 4);
+        };
+        auto add_t = [&](int k0, const f32x4 (&v)[2][kFly], float (&tv)[8]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int k = 0; k < kFly; ++k)
+            if (k0 + k < p.parts)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) tv[e] += v[e >> 2][k][e & 3];
+        };
+        auto load_t = [&](int c0, int k0, float (&tv)[8]) __attribute__((always_inline)) {  // the parts from k0 on
           if (tvec && c0 + 8 <= my_rank) {
-            constexpr int kFly = C::OCC == 1 ? 4 : 2;  // parts in flight: registers of half a compute unit allow two
-            for (int k0 = 0; k0 < p.parts; k0 += kFly) {
+            for (; k0 < p.parts; k0 += kFly) {
               f32x4 v[2][kFly];
-#pragma unroll
-              for (int k = 0; k < kFly; ++k)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                  v[h][k] = *reinterpret_cast<const f32x4*>(tp + (k0 + k < p.parts ? k0 + k : p.parts - 1) * p.t_stride + h * 4);
-#pragma unroll
-              for (int k = 0; k < kFly; ++k)
-                if (k0 + k < p.parts)
-#pragma unroll
-                  for (int e = 0; e < 8; ++e) tv[e] += v[e >> 2][k][e & 3];
+              ask_t(c0, k0, v);
+              add_t(k0, v, tv);
             }
           } else {
+            const float* tp = p.t + (size_t)(m0 + xr) * p.ad.r_max + c0;
             for (int e = 0; e < 8; ++e)
               if (c0 + e < my_rank)
                 for (int k = 0; k < p.parts; ++k) tv[e] += tp[k * p.t_stride + e];
@@ -345,20 +350,20 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
         const int off = s0 - my_first, end = g1 - my_first < off + kBatch ? g1 - my_first : off + kBatch;
         const int ng = (my_rank + 7) >> 3, k_end = end < ng ? end : ng;
         int k = (off > 0 ? off : 0) + tb % kRowT;
-        float tv[8];
         const bool has = k < k_end;
+        // One workgroup per compute unit: the first two groups of t and W^B on their way together, a round trip takes about 3 us
+        // (777 rows on 4096 x 4096: 52.8 us a call one after the other, 51.9 so).  Two share its registers: W^B and t one after the other.
+        float tv[C::OCC == 1 ? 2 : 1][8];
+        f32x4 raw[2][2][kFly];
+        bool whole[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          whole[j] = C::OCC == 1 && tvec && k + j * kRowT < k_end && (k + j * kRowT) * 8 + 8 <= my_rank;
+          if (whole[j]) ask_t((k + j * kRowT) * 8, 0, raw[j]);
+        }
         u32x4 a[8];
         const bool wput = wg < stages * 4;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = u32x4{0u, 0u, 0u, 0u};
-        if (wput && s0 + wg < g1 && wc < cols) {
-          const int2 gr = groups[s0 + wg - g0];
-          const int r = p.ad.rank[gr.x];
-          gbf16* b = in_global(p.ad.B[gr.x * MILORA_NUM_SITES + p.site]) + n0 + wc;
-          // (whole pieces of 8 columns, d2 % 16 == 0, at whatever alignment the adapter has: one load each)
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
-            if (gr.y + i < r) a[i] = *(gu32x4_a2*)(b + (size_t)(gr.y + i) * p.d2);
+        auto guard_w = [&]() __attribute__((always_inline)) {
           float bad[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int i = 0; i < 8; ++i)
@@ -371,8 +376,21 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
               for (int e = 0; e < 4; ++e) a[i][e] = finite2(a[i][e]);
             ctl[kCtlBad] = 1;
           }
+        };
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = u32x4{0u, 0u, 0u, 0u};
+        if (wput && s0 + wg < g1 && wc < cols) {
+          const int2 gr = groups[s0 + wg - g0];
+          const int r = p.ad.rank[gr.x];
+          gbf16* b = in_global(p.ad.B[gr.x * MILORA_NUM_SITES + p.site]) + n0 + wc;
+          // (whole pieces of 8 columns, d2 % 16 == 0, at whatever alignment the adapter has: one load each)
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (gr.y + i < r) a[i] = *(gu32x4_a2*)(b + (size_t)(gr.y + i) * p.d2);
+          if (C::OCC > 1) guard_w();
         }
         auto put_w = [&]() __attribute__((always_inline)) {
+          if (C::OCC == 1) guard_w();
           u32x4 at[8];
           transpose8(a, at);
           unsigned char* const wst = ring + (wg >> 2) * C::StageBytes + C::BM * 128;
@@ -383,17 +401,25 @@ __global__ void __launch_bounds__(kT, 2 * C::OCC) tile_kernel(const TParams p) {
             *reinterpret_cast<u32x4*>(wst + n * 128 + ((((wg & 3) + 4) ^ swz(n & 15)) << 4)) = at[j];
           }
         };
-        // (two workgroups share a compute unit's registers: W^B and t one after the other)
         if (C::OCC > 1 && wput) put_w();
         if (C::OCC > 1) __builtin_amdgcn_sched_barrier(0);
-        if (has) load_t(k * 8, tv);
+#pragma unroll
+        for (int j = 0; j < (C::OCC == 1 ? 2 : 1); ++j) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) tv[j][e] = 0.f;
+          if (whole[j]) add_t(0, raw[j], tv[j]);
+          if (k + j * kRowT < k_end) load_t((k + j * kRowT) * 8, whole[j] ? kFly : 0, tv[j]);
+        }
         for (int e = tb; e < stages * C::BM * 8; e += kT)
           *reinterpret_cast<u32x4*>(ring + e / (C::BM * 8) * C::StageBytes + e % (C::BM * 8) * 16) = u32x4{0u, 0u, 0u, 0u};
         __syncthreads();
-        if (has) put_t(k - off, tv);
-        for (k += kRowT; k < k_end; k += kRowT) {
-          load_t(k * 8, tv);
-          put_t(k - off, tv);
+        if (has) put_t(k - off, tv[0]);
+        if (C::OCC == 1 && k + kRowT < k_end) put_t(k + kRowT - off, tv[C::OCC == 1 ? 1 : 0]);
+        for (k += kRowT * (C::OCC == 1 ? 2 : 1); k < k_end; k += kRowT) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) tv[0][e] = 0.f;
+          load_t(k * 8, 0, tv[0]);
+          put_t(k - off, tv[0]);
         }
         if (C::OCC == 1 && wput) put_w();
         __syncthreads();

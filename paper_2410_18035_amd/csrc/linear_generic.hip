@@ -87,15 +87,20 @@ __global__ void __launch_bounds__(kShrinkT) shrink_rows_kernel(const T* __restri
 }
 
 // ---- few rows: up to 16 --------------------------------------------------------------------------------------------
-// A workgroup takes 16 columns of one linear (gate and up: of both) and the whole reduction, dealt to its eight waves in
+// A workgroup takes 16 columns of one linear (gate and up: of both) and the whole reduction, dealt to its waves in
 // blocks of 16 k that go straight from global memory into matrix operands; the waves' sums meet in LDS.  Where rows, ranks
-// and widths are small the shrinks are formed here too (fuse_shrink), each wave over its share of k and one row after
+// and widths are small the shrinks are formed here too (FUSED, fuse_shrink), each wave over its share of k and one row after
 // the other, again in every workgroup; else they come from shrink_rows_kernel.
 // The layer's glue is part of the store: a decode step of a layer is four launches instead of eighteen.
-// Bound: launches and the chain of dependent loads (route -> adapter tables -> A) of each.  A decode step of 4 rows
-// through the 256 x 688 fp32 layer, rank 8: 284 us with eighteen launches, 24.8 us with these.
-constexpr int kFewT = 512, kFewW = kFewT / 64;
+// Bound: launches (about 2.4 us each with nothing in them), and the code a launch runs through, whose time goes with its
+// bytes (4.6 KB 4.8 us, 7.7 KB 8.0 us): what a call does not need is compiled out, the shrinks of two sites are one loop, and
+// four waves run through it where eight would each find two blocks of 16 k or fewer (d = 256 22.3 -> 19.6 us, 360: 26.5 and
+// 26.7, 504: 34.8 and 38.9).  A decode step of 4 rows through the 256 x 688 fp32 layer, rank 8: 284 us with eighteen launches,
+// 22.3 us with four of eight waves and both expands in them, 19.6 us so.  Tried: base and adapter pointers asked for ahead of the
+// look-ups (fewer dependent loads, more code: 26.9 against 24.3 us), 32-bit offsets with a path for whole trips (41.1 against 35.6 us at
+// 16 rows, d = 504).
 constexpr int kFewBlocks = 4;  // blocks of 16 k per wave on their way
+constexpr int kFewNarrow = 320;  // reductions up to here: four waves
 
 template <typename T>
 __device__ __forceinline__ float round_to(float v) {
@@ -104,20 +109,20 @@ __device__ __forceinline__ float round_to(float v) {
   return Elem<T>::load(&q, 0);
 }
 
-template <typename T, int MODE>
-__global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
+template <typename T, int MODE, int kFewW, bool FUSED>
+__global__ void __launch_bounds__(kFewW * 64, 4) few_rows_kernel(const FewArgs g) {
   constexpr int NW = MODE == kFewGateUp ? 2 : 1;
   __shared__ float red[NW][kFewW][16][17];
-  __shared__ float tpart[NW][kFewW][16][kFuseRank];
-  __shared__ float ts[NW][16][kFuseRank];
+  __shared__ float tpart[FUSED ? NW : 1][FUSED ? kFewW : 1][16][kFuseRank];
+  __shared__ float ts[FUSED ? NW : 1][16][kFuseRank];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s0 = MODE == kFewGateUp ? 0 : blockIdx.y, n0 = g.col0 + blockIdx.x * 16;
   const int d1 = g.d1;
-  const bool fused = g.t == nullptr;
 
-  // rank and tenant of row li at the workgroup's sites (route byte and tenant id are asked for together)
-  int rank[NW], ten[NW];
+  // rank and tenant of row li at the workgroup's site, of its two sites in lanes 0 .. 15 and 16 .. 31 (route byte and tenant id are
+  // asked for together)
+  int rank = 0, ten = 0;
   {
     const int64_t req = li < g.M ? (g.row_to_req ? (int64_t)g.row_to_req[li] : li) : -1;
     const bool in = req >= 0 && req < g.B;
@@ -125,11 +130,9 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
     const int tn = in ? g.tenant_id[req] : -1;
     const bool known = tn >= 0 && tn < g.ad.n_tenants;
     const int r = known ? g.ad.rank[tn] : 0;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const bool has = known && route_has(rt, g.site[s0 + j]) && r >= 1 && r <= g.ad.r_max;
-      rank[j] = has ? r : 0;
-      ten[j] = has ? tn : 0;
+    if (known && lq < NW && route_has(rt, g.site[s0] + lq) && r >= 1 && r <= g.ad.r_max) {  // (sites of a workgroup are consecutive)
+      rank = r;
+      ten = tn;
     }
   }
 
@@ -161,7 +164,7 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[j][u][e], xv[u][e], acc[j], 0, 0, 0);
   }
-  if (full * 16 < d1 && w == full % kFewW) {
+  if (__builtin_expect(full * 16 < d1 && w == full % kFewW, 0)) {
     const f32x4 x = load4_end(xr, full * 16 + lq * 4, d1);
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
@@ -177,41 +180,39 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
     for (int e = 0; e < 4; ++e) red[j][w][li][lq * 4 + e] = acc[j][e];
 
   // ---- shrinks of the routed rows over this wave's share of k ----
-  if (fused) {
+  if constexpr (FUSED) {
     const int share = (d1 + kFewW - 1) / kFewW, k0 = w * share, k1 = k0 + share < d1 ? k0 + share : d1;
+    for (unsigned long long left = __ballot(rank > 0); left; left &= left - 1) {
+      const int at = __builtin_ctzll(left), m = at & 15, j = NW > 1 ? at >> 4 : 0;
+      const int r = __builtin_amdgcn_readlane(rank, at), tn = __builtin_amdgcn_readlane(ten, at);
+      const T* const A = (const T*)g.ad.A[tn * MILORA_NUM_SITES + g.site[s0] + j];
+      const T* const x = (const T*)g.X + (size_t)m * g.ldx;
+      const int rpad = pow2_above(r), c = lane & (rpad - 1), kpl = 64 / rpad;
+      float sum = 0.f;
+      for (int k = k0 + lane / rpad; __any(k < k1); k += 8 * kpl) {
+        float xv[8], av[8];
 #pragma unroll
-    for (int j = 0; j < NW; ++j)
-      for (unsigned long long left = __ballot(lane < 16 && rank[j] > 0); left; left &= left - 1) {
-        const int m = __builtin_ctzll(left);
-        const int r = __builtin_amdgcn_readlane(rank[j], m), tn = __builtin_amdgcn_readlane(ten[j], m);
-        const T* const A = (const T*)g.ad.A[tn * MILORA_NUM_SITES + g.site[s0 + j]];
-        const T* const x = (const T*)g.X + (size_t)m * g.ldx;
-        const int rpad = pow2_above(r), c = lane & (rpad - 1), kpl = 64 / rpad;
-        float sum = 0.f;
-        for (int k = k0 + lane / rpad; __any(k < k1); k += 8 * kpl) {
-          float xv[8], av[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int kk = k + u * kpl < k1 ? k + u * kpl : d1 - 1;
-            xv[u] = Elem<T>::load(x, kk);
-            av[u] = Elem<T>::load(A, (size_t)kk * r + (c < r ? c : 0));
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) sum += k + u * kpl < k1 ? xv[u] * av[u] : 0.f;
+        for (int u = 0; u < 8; ++u) {
+          const int kk = k + u * kpl < k1 ? k + u * kpl : d1 - 1;
+          xv[u] = Elem<T>::load(x, kk);
+          av[u] = Elem<T>::load(A, (size_t)kk * r + (c < r ? c : 0));
         }
-        for (int off = rpad; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
-        if (lane < r) tpart[j][w][m][lane] = sum;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += k + u * kpl < k1 ? xv[u] * av[u] : 0.f;
       }
+      for (int off = rpad; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+      if (lane < r) tpart[j][w][m][lane] = sum;
+    }
   }
   __syncthreads();
   const int m = tid >> 4, n = n0 + (tid & 15);  // threads 0 .. 255: one output each; their lanes' rows are 4 (tid / 64) ..
   int rm[NW], tm[NW];
 #pragma unroll
   for (int j = 0; j < NW; ++j) {
-    rm[j] = __shfl(rank[j], m & 15, 64);
-    tm[j] = __shfl(ten[j], m & 15, 64);
+    rm[j] = __shfl(rank, (m & 15) + 16 * j, 64);
+    tm[j] = __shfl(ten, (m & 15) + 16 * j, 64);
   }
-  if (fused && tid < 256) {
+  if (FUSED && tid < 256) {
     const int c = tid & 15;
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
@@ -234,7 +235,7 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
     if (g.bias) v += Elem<T>::load((const T*)g.bias, n);
     if (rm[j] > 0) {
       const T* const Bm = (const T*)g.ad.B[tm[j] * MILORA_NUM_SITES + g.site[s0 + j]] + n;
-      const float* const tg = fused ? nullptr : g.t + ((size_t)(s0 + j) * g.M + m) * g.ad.r_max;
+      const float* const tg = FUSED ? nullptr : g.t + ((size_t)(s0 + j) * g.M + m) * g.ad.r_max;
       float delta = 0.f;
       for (int c0 = 0; c0 < rm[j]; c0 += 8) {
         float bv[8], tv[8];
@@ -242,7 +243,7 @@ __global__ void __launch_bounds__(kFewT, 4) few_rows_kernel(const FewArgs g) {
         for (int u = 0; u < 8; ++u) {
           const int c = c0 + u < rm[j] ? c0 + u : rm[j] - 1;
           bv[u] = Elem<T>::load(Bm, (size_t)c * g.d2);
-          tv[u] = fused ? ts[j][m][c & (kFuseRank - 1)] : tg[c];
+          tv[u] = FUSED ? ts[j][m][c & (kFuseRank - 1)] : tg[c];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) delta += c0 + u < rm[j] ? tv[u] * bv[u] : 0.f;
@@ -487,7 +488,7 @@ int launch_shrink(const void* X, int64_t ldx, int64_t M, int d1, int dtype, cons
   return check_launch();
 }
 
-template <typename T>
+template <typename T, int W, bool FUSED>
 static int launch_few_rows_t(FewArgs& g, int sites, int mode, hipStream_t st) {
   int rc = MILORA_OK;
   for (int64_t col0 = 0; col0 < g.d2 && !rc; col0 += kLaunchCols) {
@@ -495,10 +496,10 @@ static int launch_few_rows_t(FewArgs& g, int sites, int mode, hipStream_t st) {
     const dim3 grid((unsigned)((cols + 15) / 16), (unsigned)sites);
     g.col0 = (int)col0;
     switch (mode) {
-      case kFewPlain: hipLaunchKernelGGL((few_rows_kernel<T, kFewPlain>), grid, dim3(kFewT), 0, st, g); break;
-      case kFewResid: hipLaunchKernelGGL((few_rows_kernel<T, kFewResid>), grid, dim3(kFewT), 0, st, g); break;
-      case kFewGateUp: hipLaunchKernelGGL((few_rows_kernel<T, kFewGateUp>), dim3(grid.x), dim3(kFewT), 0, st, g); break;
-      default: hipLaunchKernelGGL((few_rows_kernel<T, kFewDown>), grid, dim3(kFewT), 0, st, g); break;
+      case kFewPlain: hipLaunchKernelGGL((few_rows_kernel<T, kFewPlain, W, FUSED>), grid, dim3(W * 64), 0, st, g); break;
+      case kFewResid: hipLaunchKernelGGL((few_rows_kernel<T, kFewResid, W, FUSED>), grid, dim3(W * 64), 0, st, g); break;
+      case kFewGateUp: hipLaunchKernelGGL((few_rows_kernel<T, kFewGateUp, W, FUSED>), dim3(grid.x), dim3(W * 64), 0, st, g); break;
+      default: hipLaunchKernelGGL((few_rows_kernel<T, kFewDown, W, FUSED>), grid, dim3(W * 64), 0, st, g); break;
     }
     rc = check_launch();
   }
@@ -527,7 +528,10 @@ int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* 
     if (rc) return rc;
     g.t = t;
   }
-  return dtype == MILORA_BF16 ? launch_few_rows_t<bf16_t>(g, sites, mode, st) : launch_few_rows_t<float>(g, sites, mode, st);
+  const bool bf = dtype == MILORA_BF16;
+  if (g.t) return bf ? launch_few_rows_t<bf16_t, 8, false>(g, sites, mode, st) : launch_few_rows_t<float, 8, false>(g, sites, mode, st);
+  if (g.d1 <= kFewNarrow) return bf ? launch_few_rows_t<bf16_t, 4, true>(g, sites, mode, st) : launch_few_rows_t<float, 4, true>(g, sites, mode, st);
+  return bf ? launch_few_rows_t<bf16_t, 8, true>(g, sites, mode, st) : launch_few_rows_t<float, 8, true>(g, sites, mode, st);
 }
 
 int launch_linear_generic(const void* X, int64_t M, int d1, int d2, int dtype, const int32_t* row_to_req,

@@ -599,6 +599,16 @@ def test_layer_decode_rowmajor_few_rows(dtype, B, ranks, top_k, rmsnorm, with_at
     _layer_case(wl, rmsnorm, mb.W_ROWMAJOR, with_attn=with_attn, route=route)
 
 
+@pytest.mark.parametrize("dtype,d,F,B,ranks", [("f32", 320, 321, 16, (3, 16)), ("f32", 321, 320, 2, (16,)), ("f32", 16, 15, 5, (1, 8)),
+                                              ("f32", 17, 20, 3, (2,)), ("bf16", 72, 400, 16, (9, 24))])
+def test_layer_decode_rowmajor_narrow_reductions(dtype, d, F, B, ranks):
+    """Launches of four and of eight waves, around the width between them, at one block of 16 k and less, with requests that have a
+    term at both gate and up; shrinks inside the launch and (rank 24) apart."""
+    wl = small(dtype=dtype, d=d, F=F, T=3, B=B, ranks=ranks, tenants="uniform", seed=700 + d, sigma_lora=0.15 if dtype == "f32" else 0.4)
+    route = torch.tensor([0x80 | (1 << 4) | (1 << 5) | (1 << (b % 4)) for b in range(B)], dtype=torch.uint8)
+    _layer_case(wl, False, mb.W_ROWMAJOR, route=route)
+
+
 @pytest.mark.parametrize("B", [4, 16, 32, 48, 64, 128])
 @pytest.mark.parametrize("rmsnorm", [False, True])
 def test_layer_decode_packed_bf16(B, rmsnorm):

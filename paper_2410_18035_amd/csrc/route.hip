@@ -66,20 +66,39 @@ struct RationalCoef {
   float b[5];
 };
 
-__device__ __forceinline__ float activate(float x, int act, const RationalCoef& rc) {
+// g of four columns.  One function at a time for all four: a wave jumps once to the code it needs and runs straight through it.
+__device__ __forceinline__ void activate4(float (&x)[4], int act, const RationalCoef& rc) {
   switch (act) {
-    case MILORA_ACT_TANH: return tanhf(x);
-    case MILORA_ACT_RELU: return x > 0.f ? x : 0.f;
-    case MILORA_ACT_GELU: return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f));
-    case MILORA_ACT_RATIONAL: {
-      float num = rc.a[6], den = rc.b[4];
+    case MILORA_ACT_TANH:
+#pragma unroll 1
+      for (int i = 0; i < 4; ++i) {  // (one copy of the code: the values go round)
+        const float t = tanhf(x[0]);
+        x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; x[3] = t;
+      }
+      break;
+    case MILORA_ACT_RELU:
 #pragma unroll
-      for (int j = 5; j >= 0; --j) num = num * x + rc.a[j];
+      for (int v = 0; v < 4; ++v) x[v] = x[v] > 0.f ? x[v] : 0.f;
+      break;
+    case MILORA_ACT_GELU:
+#pragma unroll 1
+      for (int i = 0; i < 4; ++i) {
+        const float t = 0.5f * x[0] * (1.0f + erff(x[0] * 0.70710678118654752440f));
+        x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; x[3] = t;
+      }
+      break;
+    case MILORA_ACT_RATIONAL:
 #pragma unroll
-      for (int j = 3; j >= 0; --j) den = den * x + rc.b[j];
-      return num / (1.0f + fabsf(den * x));
-    }
-    default: return x;
+      for (int v = 0; v < 4; ++v) {
+        float num = rc.a[6], den = rc.b[4];
+#pragma unroll
+        for (int j = 5; j >= 0; --j) num = num * x[v] + rc.a[j];
+#pragma unroll
+        for (int j = 3; j >= 0; --j) den = den * x[v] + rc.b[j];
+        x[v] = num / (1.0f + fabsf(den * x[v]));
+      }
+      break;
+    default: break;
   }
 }
 
@@ -87,10 +106,16 @@ __device__ __forceinline__ float activate(float x, int act, const RationalCoef& 
 __device__ __forceinline__ uint8_t select_route(const float (&logit)[MILORA_NUM_SITES], int top_k) {
   unsigned mask = 0;
   int last = 0;
+#pragma unroll 1
   for (int q = 0; q < top_k; ++q) {
     int best = -1;
+    float most = 0.f;
+#pragma unroll
     for (int j = 0; j < MILORA_NUM_SITES; ++j)
-      if (!((mask >> j) & 1) && (best < 0 || logit[j] > logit[best])) best = j;
+      if (!((mask >> j) & 1) && (best < 0 || logit[j] > most)) {
+        best = j;
+        most = logit[j];
+      }
     mask |= 1u << best;
     last = best;
   }
@@ -157,6 +182,8 @@ constexpr int kPoolThreads = 512;
 constexpr int kColLanes = 32;
 constexpr int kTokenLanes = kPoolThreads / kColLanes;
 
+template <typename T> struct alignas(4 * sizeof(T)) Four { T v[4]; };
+
 template <typename T>
 struct PoolRouteArgs {
   const T* H;
@@ -168,6 +195,7 @@ struct PoolRouteArgs {
   int T_tenants;
   const T* Wr;
   int pool, act, top_k;
+  bool wr4;            // rows of Wr in aligned fours
   int S, C;            // token slices per request, column slabs
   uint32_t tag_lo, tag_hi;  // this call's tag, tag_lo != 0
   float* partial;      // [B][C][S][32 * VEC]
@@ -185,20 +213,31 @@ __device__ __forceinline__ void no_route(const PoolRouteArgs<T>& p, int b) {
   if (p.logits_out && threadIdx.x < MILORA_NUM_SITES) p.logits_out[b * MILORA_NUM_SITES + threadIdx.x] = __uint_as_float(0x7fc00000u);
 }
 
-// Router weights of the four columns that lane f < FT finishes.
+// Router weights of the four columns that lane f < FT finishes, zero past the row's end.
 template <typename T, int FT>
 __device__ __forceinline__ void load_router_weights(const PoolRouteArgs<T>& p, int ten, int f, int fcol, float (&wr)[MILORA_NUM_SITES][4]) {
 #pragma unroll
   for (int j = 0; j < MILORA_NUM_SITES; ++j)
 #pragma unroll
     for (int v = 0; v < 4; ++v) wr[j][v] = 0.f;
-  if (f >= FT) return;
-  const T* wt = p.Wr + (size_t)ten * MILORA_NUM_SITES * p.d;
+  if (f >= FT || fcol >= p.d) return;
+  const T* wt = p.Wr + (size_t)ten * MILORA_NUM_SITES * p.d + fcol;
+  if (p.wr4) {  // rows of whole, aligned fours
+#pragma unroll
+    for (int j = 0; j < MILORA_NUM_SITES; ++j) {
+      const Four<T> q = *reinterpret_cast<const Four<T>*>(wt + (size_t)j * p.d);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) wr[j][v] = Elem<T>::load(q.v, v);
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < MILORA_NUM_SITES; ++j)
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (fcol + v < p.d) wr[j][v] = Elem<T>::load(wt, (size_t)j * p.d + fcol + v);
+    for (int v = 0; v < 4; ++v) {
+      const float w = Elem<T>::load(wt + (size_t)j * p.d, fcol + v < p.d ? v : 0);
+      wr[j][v] = fcol + v < p.d ? w : 0.f;
+    }
 }
 
 // Columns 4 f .. + 3 of the sixteen token lanes, added in a fixed tree.
@@ -211,46 +250,53 @@ __device__ __forceinline__ f32x4 add_token_lanes(const float (&red)[kTokenLanes]
          (((r[8] + r[9]) + (r[10] + r[11])) + ((r[12] + r[13]) + (r[14] + r[15])));
 }
 
-// z = g(scale * h) of a lane's columns fcol .. fcol + 3 (where `on`) and what they add to the seven logits, summed over the wave (every
-// lane ends with the sums).
+// z = g(scale * h) of a lane's columns fcol .. fcol + 3 (where `on`) and what they add to the seven logits, summed over the wave: lane
+// 8 j .. 8 j + 7 end with logit j.  Each of the first three steps halves what a lane holds: ten exchanges, not forty-two.
+// (The end of a router's launch is a chain of round trips and of the code between them: with these ten, the activation as one jump for
+// four columns, router weights in one load per row and the maximum apart from the sums, the whole launch on 32 prompts of 256 tokens,
+// d = 4096, went from 18.0 to 14.8 us, 4.5 TB/s.)
 template <typename T>
-__device__ __forceinline__ void wave_logits(const PoolRouteArgs<T>& p, bool on, int fcol, f32x4 h, float scale,
-                                            const float (&wr)[MILORA_NUM_SITES][4], float (&lg)[8]) {
+__device__ __forceinline__ float wave_logits(const PoolRouteArgs<T>& p, bool on, int fcol, int lane, f32x4 h, float scale,
+                                             const float (&wr)[MILORA_NUM_SITES][4]) {
+  float z[4], lg[8];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) z[v] = h[v] * scale;
+  activate4(z, p.act, p.coef);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) z[v] = on && fcol + v < p.d ? z[v] : 0.f;  // (nothing of what lies past the end, its weights are zeros)
 #pragma unroll
   for (int j = 0; j < 8; ++j) lg[j] = 0.f;
-  if (on) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      if (fcol + v < p.d) {
-        const float z = activate(h[v] * scale, p.act, p.coef);
+  for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int j = 0; j < MILORA_NUM_SITES; ++j) lg[j] += z * wr[j][v];
-      }
+    for (int j = 0; j < MILORA_NUM_SITES; ++j) lg[j] += z[v] * wr[j][v];
+#pragma unroll
+  for (int half = 4, off = 32; half >= 1; half >>= 1, off >>= 1)
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const bool up = (lane & off) != 0;
+      const float give = up ? lg[i] : lg[i + half], keep = up ? lg[i + half] : lg[i];
+      lg[i] = keep + __shfl_xor(give, off, 64);
     }
-  }
 #pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j)
-    for (int off = 32; off > 0; off >>= 1) lg[j] += __shfl_xor(lg[j], off, 64);
+  for (int off = 4; off >= 1; off >>= 1) lg[0] += __shfl_xor(lg[0], off, 64);
+  return lg[0];
 }
 
-// A slab's share of the seven logits is known: hand it over and, by the wave that finds every slab's share, select.  Called by one
-// wave.
+// A slab's share of the seven logits is known (lanes 8 j ..: logit j): hand it over and, by the wave that finds every slab's share,
+// select.  Called by one wave.
 template <typename T>
-__device__ __forceinline__ void finish_request(const PoolRouteArgs<T>& p, int b, int c, int lane, float (&lg)[8]) {
+__device__ __forceinline__ void finish_request(const PoolRouteArgs<T>& p, int b, int c, int lane, float share) {
+  // (lane u: logits 2 u and 2 u + 1)
+  float a0 = __shfl(share, (16 * lane) & 63, 64), a1 = __shfl(share, (16 * lane + 8) & 63, 64);
   if (p.C > 1) {
     // unit u of the slab: logits 2u and 2u + 1 with the tag.  Lane i takes units i, i + 64, ...: always unit i % 4,
     // of slabs i / 4, i / 4 + 16, ...; the sixteen running sums of a unit are then added across the lanes.
     u32x4* units = p.share + (size_t)b * p.C * 4;
-    if (lane < 4) {
-      float e0 = 0.f, e1 = 0.f;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (lane == u) { e0 = lg[2 * u]; e1 = lg[2 * u + 1]; }
-      st_through(units + c * 4 + lane, u32x4{__float_as_uint(e0), __float_as_uint(e1), p.tag_lo, p.tag_hi});
-    }
+    if (lane < 4) st_through(units + c * 4 + lane, u32x4{__float_as_uint(a0), __float_as_uint(a1), p.tag_lo, p.tag_hi});
     wait_all_mem();
     bool all = true;
-    float a0 = 0.f, a1 = 0.f;
+    a0 = a1 = 0.f;
     for (int i = lane; i < 4 * p.C; i += 64) {
       const u32x4 g = ld_through(units + i);
       all = all && g[2] == p.tag_lo && g[3] == p.tag_hi;
@@ -263,23 +309,17 @@ __device__ __forceinline__ void finish_request(const PoolRouteArgs<T>& p, int b,
       a0 += __shfl_xor(a0, off, 64);
       a1 += __shfl_xor(a1, off, 64);
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      lg[2 * u] = __shfl(a0, u, 64);
-      lg[2 * u + 1] = __shfl(a1, u, 64);
-    }
   }
   float logit[MILORA_NUM_SITES];
 #pragma unroll
-  for (int j = 0; j < MILORA_NUM_SITES; ++j) logit[j] = lg[j];
-  if (lane == 0) {
-    if (p.logits_out)
-      for (int j = 0; j < MILORA_NUM_SITES; ++j) p.logits_out[b * MILORA_NUM_SITES + j] = logit[j];
-    p.route_out[b] = select_route(logit, p.top_k);
-  }
+  for (int j = 0; j < MILORA_NUM_SITES; ++j) logit[j] = __shfl(j & 1 ? a1 : a0, j >> 1, 64);
+  const float mine0 = __shfl(a0, lane >> 1, 64), mine1 = __shfl(a1, lane >> 1, 64);
+  if (p.logits_out && lane < MILORA_NUM_SITES) p.logits_out[b * MILORA_NUM_SITES + lane] = lane & 1 ? mine1 : mine0;
+  const uint8_t route = select_route(logit, p.top_k);
+  if (lane == 0) p.route_out[b] = route;
 }
 
-template <typename T, int VEC>
+template <typename T, int VEC, bool is_max>
 __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<T> p) {
   constexpr int SW = kColLanes * VEC;  // columns of a slab
   constexpr int FT = SW / 4;           // lanes of the first wave that finish the slab, four columns each
@@ -295,7 +335,6 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
     if (blockIdx.x == 0) no_route(p, b);
     return;
   }
-  const bool is_max = p.pool == MILORA_POOL_MAX;
   float scale = is_max ? 1.0f : 1.0f / (float)n;
   if (p.pool == MILORA_POOL_LAST) {  // the average over the last valid row alone
     start += n - 1;
@@ -415,9 +454,7 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
     }
   }
 
-  float lg[8];
-  wave_logits(p, f < FT, fcol, h, scale, wr, lg);
-  finish_request(p, b, c, lane, lg);
+  finish_request(p, b, c, lane, wave_logits(p, f < FT, fcol, lane, h, scale, wr));
 }
 
 // ---- self-attention pooling (App. C): u_t = H[t] . w_sa, a = softmax over the request's tokens, p = sum_t a_t H[t] ----
@@ -427,7 +464,7 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
 // running maximum (a batch that raises it rescales what was gathered before), weighted sum out of the same registers,
 // while the next R rows are on their way.  The part of a piece that lies in one request leaves a row of unnormalised sums
 // and (maximum, sum of weights) in the workspace, at index piece + request; the finishing launch merges a request's rows.
-// Bound: the read of H.  16 prompts of 1024 to 2048 tokens, d = 4096 (201 MB): 41 us = 4.9 TB/s and 10.6 us
+// Bound: the read of H.  16 prompts of 1024 to 2048 tokens, d = 4096 (201 MB): 41 us = 4.9 TB/s and 8.7 us
 // for the finishing launch, six dependent round trips (with slices of 16 tokens, each read twice, and one finishing workgroup
 // per request: 65 and 72 us).
 constexpr int kSelfAttnMaxD = 8192;
@@ -642,7 +679,7 @@ template <typename T, int CL>
 __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRouteArgs<T> p, AttnParts in) {
   constexpr int SW = CL * 4, TL = kPoolThreads / CL, kWaves = (CL + 63) / 64;  // waves that finish
   __shared__ __align__(16) float red[TL][SW];
-  __shared__ float wave_lg[kWaves][8];
+  __shared__ float wave_lg[kWaves][64];
   const int c = blockIdx.x, b = blockIdx.y;
   const int cl = threadIdx.x % CL, tl = threadIdx.x / CL, lane = threadIdx.x & 63;
   const int2 sp = in.span[b];  // (asked for with the facts that say whether it means anything)
@@ -686,8 +723,9 @@ __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRoute
     if (i0 != tl) ask(i0);
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (i0 + u * TL < sp.y) acc += expf(m[u] - ref) / z * x[u];
+      if (i0 + u * TL < sp.y) acc += expf(m[u] - ref) * x[u];
   }
+  acc *= 1.0f / z;
   if constexpr (TL > 1) {
     *reinterpret_cast<f32x4*>(&red[tl][cl * 4]) = acc;
     __syncthreads();
@@ -697,23 +735,19 @@ __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRoute
       for (int i = 0; i < TL; ++i) acc += *reinterpret_cast<const f32x4*>(&red[i][cl * 4]);
     }
   }
-  float lg[8];
-  if (threadIdx.x < kWaves * 64) wave_logits(p, threadIdx.x < CL, c * SW + 4 * (int)threadIdx.x, acc, 1.0f, wr, lg);
+  float share = 0.f;
+  if (threadIdx.x < kWaves * 64) share = wave_logits(p, threadIdx.x < CL, c * SW + 4 * (int)threadIdx.x, lane, acc, 1.0f, wr);
   if constexpr (kWaves > 1) {
-    if (threadIdx.x < kWaves * 64 && lane == 0)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) wave_lg[threadIdx.x >> 6][j] = lg[j];
+    if (threadIdx.x < kWaves * 64) wave_lg[threadIdx.x >> 6][lane] = share;
     __syncthreads();
   }
   if (threadIdx.x >= 64) return;
-  if constexpr (kWaves > 1)
+  if constexpr (kWaves > 1) {
+    share = wave_lg[0][lane];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      lg[j] = wave_lg[0][j];
-#pragma unroll
-      for (int w = 1; w < kWaves; ++w) lg[j] += wave_lg[w][j];
-    }
-  finish_request(p, b, c, lane, lg);
+    for (int w = 1; w < kWaves; ++w) share += wave_lg[w][lane];
+  }
+  finish_request(p, b, c, lane, share);
 }
 
 // Workspace of the self-attention pooler.  Pieces of the line: two workgroups of up to eight waves per compute unit, one of
@@ -791,7 +825,9 @@ int launch_pool_route(PoolRouteArgs<T> a, int B, int64_t M_tok, void* workspace,
   a.partial = (float*)((char*)workspace + cv.partial);
   a.arrived = (u32x2*)((char*)workspace + cv.arrived);
   a.share = (u32x4*)((char*)workspace + cv.share);
-  hipLaunchKernelGGL((pool_route_kernel<T, VEC>), dim3(cv.C * cv.S, B), dim3(kPoolThreads), 0, st, a);
+  const dim3 grid(cv.C * cv.S, B);
+  if (a.pool == MILORA_POOL_MAX) hipLaunchKernelGGL((pool_route_kernel<T, VEC, true>), grid, dim3(kPoolThreads), 0, st, a);
+  else hipLaunchKernelGGL((pool_route_kernel<T, VEC, false>), grid, dim3(kPoolThreads), 0, st, a);
   return check_launch();
 }
 
@@ -854,6 +890,7 @@ int route_typed(const void* H, int64_t M_tok, int d, const int32_t* seq_start, c
   a.tenant_id = tenant_id;
   a.T_tenants = n_tenants;
   a.Wr = (const T*)Wr;
+  a.wr4 = d % 4 == 0 && (uintptr_t)Wr % (4 * sizeof(T)) == 0;
   a.pool = pool;
   a.act = act;
   a.top_k = top_k;

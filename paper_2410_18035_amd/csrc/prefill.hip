@@ -370,7 +370,8 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
 
   // ---- bias, one rounding, store: of a 32 x 32 tile a lane holds row l % 32 and, in registers 4 g .. 4 g + 3, the
   // columns 8 g + 4 (l / 32) .. + 3.  By way of the wave's own LDS, so that a store writes whole lines (256 bytes of four rows instead
-  // of 16 bytes of 32 rows, lines that had to be read before they could be written: seven linears of 32768 rows 11.43 -> 10.79 ms).
+  // of 16 bytes of 32 rows, lines that had to be read before they could be written: seven linears of 32768 rows 11.43 -> 10.79 ms), and
+  // past the L2's lines of X and W (10.80 -> 10.57 ms)
   const bool bad = ctl[1] != 0;
   __syncthreads();
   unsigned char* const mine = lds + wave * (128 * kOutPitch);
@@ -403,7 +404,10 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
     if (n < p.d2)
 #pragma unroll 4
       for (int it = 0; it < 32; ++it) {
-        if (mw + it * 4 < p.M) *(u32x4_a8*)(y + (size_t)(it * 4) * p.d2) = *(const u32x4*)(q + it * 4 * kOutPitch);
+        if (mw + it * 4 < p.M) {
+          const u32x4_a8 v = *(const u32x4*)(q + it * 4 * kOutPitch);
+          __builtin_nontemporal_store(v, (u32x4_a8*)(y + (size_t)(it * 4) * p.d2));
+        }
       }
   }
 

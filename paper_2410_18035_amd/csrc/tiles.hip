@@ -637,8 +637,11 @@ int launch_tiles(const TParams& p, hipStream_t st) {
 
 // Which tiles, and how many parts: the estimated time in 10 ns, fitted to launches of 16 .. 4096 rows on the seven linears
 // of the 7B and 13B layers and a 1088 x 2624 one.  A compute unit takes 0.26 us per stage of 64 k for a 64 x 64 tile
-// (two workgroups share it: half the rate each), 0.58 us for a 128 x 128 one and 1.25 .. 1.75 us (few .. all units busy:
-// the L2 is shared) for a 256 x 256 one; workgroups beyond 256 wait for a second turn; cutting the reduction costs the
+// (two workgroups share it: half the rate each), 0.58 us for a 128 x 128 one and 1.2 .. 1.6 us (few .. all units busy:
+// the L2 is shared) for a 256 x 256 one (600 rows on 5120 x 13824: 110 us a call, 133 with 128 x 128; 2048 on 4096 x 4096: 86 and 79);
+// workgroups beyond 256 wait for a second turn; a last turn of few is shorter than a whole one (256 x 256, 1700 rows on 4096 x 11008: 301
+// workgroups, 2.6 us a step for both turns, 3.2 for two whole ones; of more than two turns of 128 x 128, 600 rows on 5120 x 13824: 540,
+// 2.7 turns; below that, 300 rows on 4096 x 11008: 258, 70.2 us against 66.5 with 64 x 64); cutting the reduction costs the
 // partial tiles and the last workgroup's sums (M = 64 on 4096 x 4096: one part 25.0 us a call, two 19.8, four 16.4, six 22.2).
 TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large) {
   const int KT = (d1 + 63) / 64;
@@ -648,7 +651,10 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large) {
     const int64_t tm = (M + side - 1) / side, tn = (d2 + side - 1) / side, units = tm * tn * S;
     if (S > 1 && (units > kMaxSplitUnits || S > KT)) return;
     const int steps = (KT + S - 1) / S;
-    const int64_t t = (units + 255) / 256 * (per_step * steps + per_tile) + (S > 1 ? split_cost : 0);
+    const int64_t turn = per_step * steps + per_tile, rest = units % 256;
+    int64_t t = (units + 255) / 256 * turn + (S > 1 ? split_cost : 0);
+    if (rest && large && S == 1 && shape == kTiles128 && units > 512) t -= turn / 2 - turn * rest / 512;
+    if (rest && shape == kTiles256) t -= 46 * (256 - rest) / 256 * steps;
     if (t >= best_t) return;
     best_t = t;
     best = TilePlan{shape, (int)tm, (int)tn, (KT + steps - 1) / steps, steps, 0};  // (no empty part)
@@ -659,10 +665,7 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large) {
       offer(kTiles64, 64, 26, 200, S, 400 + 70 * S);
       offer(kTiles128, 128, 58, 400, S, 250 + 220 * S);
     }
-  if (large) {
-    const int64_t tiles = ((M + 255) / 256) * ((d2 + 255) / 256);
-    offer(kTiles256, 256, 125 + 50 * (tiles < 256 ? tiles : 256) / 256, 800, 1, 0);
-  }
+  if (large) offer(kTiles256, 256, 163, 650, 1, 0);
   return best;
 }
 

@@ -22,8 +22,8 @@
 //
 // Bound: few rows, the stream of the weights (a 4096 x 11008 linear at 45 rows: 23 us = 3.9 TB/s); from some hundred rows on
 // the copies through the L2 (0.58 us per 128 x 128 x 64 stage and compute unit, 56 GB/s each).  The seven linears of the 7B
-// layer: 45 rows 4940 us with the any-shape kernel, 160 us here; 777 rows 966 us with 256 x 256 tiles only, 505 us;
-// packed weights, 96 rows, three sites a request: 495 us with the stream kernel of decode.hip, 253 us.
+// layer: 45 rows 4940 us with the any-shape kernel, 158 us here; 777 rows 966 us with 256 x 256 tiles only, 472 us;
+// packed weights, 96 rows, three sites a request: 495 us with the stream kernel of decode.hip, 250 us.
 #include "shrink.h"
 #include "tiles.h"
 

@@ -639,6 +639,8 @@ int launch_tiles(const TParams& p, hipStream_t st) {
 // of the 7B and 13B layers and a 1088 x 2624 one.  A compute unit takes 0.26 us per stage of 64 k for a 64 x 64 tile
 // (two workgroups share it: half the rate each), 0.58 us for a 128 x 128 one and 1.2 .. 1.6 us (few .. all units busy:
 // the L2 is shared) for a 256 x 256 one (600 rows on 5120 x 13824: 110 us a call, 133 with 128 x 128; 2048 on 4096 x 4096: 86 and 79);
+// its 7.75 us a turn keep reductions of 64 to 512 with no row routed on the smaller tiles (3846 rows on 512 x 1040: 18.3 us, 20.5 with
+// 256 x 256; 1406 on 192 x 11008: 25.3 and 27.7) and take those with many rows of rank 32 off them (3390 on 64 x 2048: 23.5 and 19.7);
 // workgroups beyond 256 wait for a second turn; a last turn of few is shorter than a whole one (256 x 256, 1700 rows on 4096 x 11008: 301
 // workgroups, 2.6 us a step for both turns, 3.2 for two whole ones; of more than two turns of 128 x 128, 600 rows on 5120 x 13824: 540,
 // 2.7 turns; below that, 300 rows on 4096 x 11008: 258, 70.2 us against 66.5 with 64 x 64); cutting the reduction costs the
@@ -665,7 +667,7 @@ TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large) {
       offer(kTiles64, 64, 26, 200, S, 400 + 70 * S);
       offer(kTiles128, 128, 58, 400, S, 250 + 220 * S);
     }
-  if (large) offer(kTiles256, 256, 163, 650, 1, 0);
+  if (large) offer(kTiles256, 256, 163, 775, 1, 0);
   return best;
 }
 

@@ -267,6 +267,21 @@ def test_routed_linear_256_tiles(M, d1, d2, ranks, T, spread):
     assert_rows_close(Y, ref, torch.bfloat16)
 
 
+def test_tile_choice_counts_the_last_turn():
+    """256 x 256 tiles or smaller ones where the two are near: a last turn of few workgroups, short reductions."""
+    k = lambda *s: mb.milora_routed_linear_tile(*s, torch.bfloat16)
+    assert [k(*s) for s in ((2870, 4096, 11008), (600, 5120, 13824), (4072, 1024, 5120), (3390, 64, 2048))] == [256] * 4
+    assert [k(*s) for s in ((1530, 11008, 11008), (2048, 4096, 4096), (3846, 512, 1040), (1406, 192, 11008))] == [128] * 4
+    assert k(300, 4096, 11008) == 64
+
+
+@gpu
+@pytest.mark.parametrize("M,d1,d2", [(3390, 64, 2048), (3391, 64, 2064)])
+def test_routed_linear_256_tiles_of_fewer_rows(M, d1, d2):
+    """Sizes that both kernels take and the 256 x 256 one is chosen for: a ragged last row tile, whole and ragged columns."""
+    test_routed_linear_256_tiles(M, d1, d2, (16, 40), 6, "segments")
+
+
 @gpu
 def test_routed_linear_256_tiles_small_integers_bit_exact():
     d1, d2, T, r, M, site = 64, 272, 3, 4, 4200, 1

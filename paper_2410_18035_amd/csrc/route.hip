@@ -558,8 +558,8 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
   for (; left > 0; ++b, off = 0) {
     const int64_t n = attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
     if (n == 0) continue;
-    const int rows_n = __builtin_amdgcn_readfirstlane((int)(n - off < left ? n - off : left));
-    const T* rows = H + (size_t)(seq_start[b] + off) * d;
+    const uint32_t rows_n = __builtin_amdgcn_readfirstlane((int)(n - off < left ? n - off : left));
+    const T* rows = H + ((size_t)seq_start[b] + off) * d;  // (the row may lie beyond 2^31)
     const T* q = w_sa + (size_t)tenant_id[b] * d;
     int col[P];
 #pragma unroll
@@ -568,10 +568,10 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
       col[p] = (c < ncg ? c : ncg - 1) * VEC;  // past the row's end: its last piece, against zeros of w
     }
     Piece<T, VEC> x[2][R][P];
-    auto ask = [&](int t, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
+    auto ask = [&](uint32_t t, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int row = t + r < rows_n ? t + r : rows_n - 1;  // past the end: the last row, with no weight
+        const uint32_t row = t + r < rows_n ? t + r : rows_n - 1;  // past the end: the last row, with no weight
         const T* src = rows + (size_t)row * d;
 #pragma unroll
         for (int p = 0; p < P; ++p) v[r][p].load(src + col[p]);
@@ -591,7 +591,7 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
       }
     }
     float m_run = -INFINITY, l_run = 0.f;  // (l_run: of row lane % R of every batch)
-    auto batch = [&](int t, int buf, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
+    auto batch = [&](uint32_t t, int buf, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
       float u[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -646,7 +646,7 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
           for (int e = 0; e < VEC; ++e) acc[p][e] += a * v[r][p].get(e);
       }
     };
-    for (int t = 0; t < rows_n; t += 2 * R) {
+    for (uint32_t t = 0; t < rows_n; t += 2 * R) {
       ask(t + R, x[1]);
       batch(t, 0, x[0]);
       if (t + R >= rows_n) break;

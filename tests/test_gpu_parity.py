@@ -229,6 +229,28 @@ def test_route_self_attention_pieces_of_the_token_line(dtype, d, B, plen, shift)
         assert torch.equal(route_g, route), f"replay {rep}"
 
 
+@pytest.mark.parametrize("d", [1, 8])
+@pytest.mark.parametrize("pool", ["selfattn", "mean"])
+def test_route_rows_beyond_2_31(pool, d):
+    """Prompts that cross and that lie behind row 2^31 of H, in elements and in 16-byte pieces of a row."""
+    M_tok, T = (1 << 31) + 900, 3
+    ss = torch.tensor([(1 << 31) - 400, 5, (1 << 31) - 1], dtype=torch.int32)
+    sl = torch.tensor([1200, 30, 901], dtype=torch.int32)
+    tid = torch.tensor([2, 0, 1], dtype=torch.int32)
+    H = torch.empty(M_tok, d, dtype=torch.bfloat16, device=DEV)
+    lo = (1 << 31) - 500
+    g = torch.Generator(device=DEV).manual_seed(d)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    H[:100], H[lo:] = rnd(100, d), rnd(M_tok - lo, d)
+    Wr, w_sa = rnd(T, 7, d), rnd(T, d)
+    route, logits = mb.milora_route(H, ss.to(DEV), sl.to(DEV), tid.to(DEV), Wr, pool, w_sa=w_sa)
+    near = torch.cat([H[:100], H[lo:]])  # the rows that are used, and where they went
+    at = torch.tensor([100 + int(ss[0]) - lo, 5, 100 + int(ss[2]) - lo], dtype=torch.int32)
+    ref = oracle.route(np_of(near), at.numpy(), sl.numpy(), tid.numpy(), np_of(Wr), mb.POOL[pool], oracle.ACT_IDENTITY, w_sa=np_of(w_sa))
+    assert_routes_match(route, ref, torch.bfloat16)
+    np.testing.assert_allclose(to_f64(logits), ref.logits, atol=5e-5 * max(1.0, np.abs(ref.logits).max()))
+
+
 def test_route_padded_prompts_and_bad_requests():
     wl = small(dtype="bf16", d=512, T=4, B=6, prompt_len=(5, 64), pad_to=64, seed=5)
     H, ss, sl = synth.prompts(wl, 0, DEV)

@@ -229,6 +229,41 @@ def test_route_self_attention_pieces_of_the_token_line(dtype, d, B, plen, shift)
         assert torch.equal(route_g, route), f"replay {rep}"
 
 
+@pytest.mark.parametrize("B,n,d", [(700, 4, 1024), (64, 16, 4096), (9, 1, 256), (300, 1, 8192), (40, 203, 512)])
+def test_route_self_attention_requests_that_share_rows(B, n, d):
+    """Requests over the same rows, and requests of a row or a few each: the line of tokens is longer than H, a piece shorter than
+    a batch of rows.  Shared rows take no longer than rows of a request's own (ten times and more where pieces are as many as H
+    has rows for; four times leaves room for the clock)."""
+    T = 3
+    g = torch.Generator(device=DEV).manual_seed(B)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    Wr, w_sa = rnd(T, 7, d), rnd(T, d) * d ** -0.5
+    tid = torch.arange(B, dtype=torch.int32) % T
+    sl = torch.full((B,), n, dtype=torch.int32)
+    took = {}
+    for shared in (True, False):
+        H = rnd(n if shared else B * n, d)
+        ss = torch.zeros(B, dtype=torch.int32) if shared else torch.arange(B, dtype=torch.int32) * n
+        args = H, ss.to(DEV), sl.to(DEV), tid.to(DEV), Wr, "selfattn", "gelu"
+        ws = torch.full((mb.route_workspace_bytes(B, d, H.shape[0]),), 255, dtype=torch.uint8, device=DEV)
+        call = lambda: mb.milora_route(*args, w_sa=w_sa, workspace=ws)
+        route, logits = call()
+        ref = oracle.route(np_of(H), ss.numpy(), sl.numpy(), tid.numpy(), np_of(Wr), mb.POOL["selfattn"], oracle.ACT_GELU, w_sa=np_of(w_sa))
+        assert_routes_match(route, ref, torch.bfloat16, f"shared {shared}")
+        np.testing.assert_allclose(to_f64(logits), ref.logits, atol=5e-5 * max(1.0, np.abs(ref.logits).max()))
+        times = []
+        for _ in range(5):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(10):
+                call()
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1))
+        took[shared] = min(times)
+    assert took[True] <= 4 * took[False], took
+
+
 @pytest.mark.parametrize("d", [1, 8])
 @pytest.mark.parametrize("pool", ["selfattn", "mean"])
 def test_route_rows_beyond_2_31(pool, d):

@@ -499,7 +499,8 @@ __device__ __forceinline__ int64_t attn_tokens(const int32_t* seq_start, const i
                                                int64_t M_tok, int T_tenants) {
   const int64_t start = seq_start[b], n = seq_len[b];
   const int ten = tenant_id[b];
-  return span_ok(start, n, M_tok) && ten >= 0 && ten < T_tenants ? n : 0;
+  const bool ok = (n >= 1) & (start >= 0) & (start + n <= M_tok) & ((uint32_t)ten < (uint32_t)T_tenants);  // (no branches: many are in flight)
+  return ok ? n : 0;
 }
 
 template <typename T, int VEC, int P>
@@ -511,54 +512,67 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
   constexpr int R = P == 1 ? 8 : P == 2 ? 4 : 2;  // rows of a batch: two batches of P * R pieces are in registers
   constexpr int Lanes = 64 / R;      // lanes that share a row's sum
   __shared__ float red[2][kAttnMaxWaves][R];
-  __shared__ int64_t wave_sum[kAttnMaxWaves];
-  __shared__ int s_req, s_off;
+  __shared__ int64_t wave_sum[kAttnMaxWaves], s_base;
+  __shared__ int s_lo, s_hi;
   const int tid = threadIdx.x, lane = tid & 63, n_threads = blockDim.x, nw = n_threads >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- this workgroup's piece of the line ----
-  const int chunk = (B + n_threads - 1) / n_threads, b0 = tid * chunk, b1 = b0 + chunk < B ? b0 + chunk : B;
-  int64_t mine = 0;
-  for (int b = b0; b < b1; ++b) mine += attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
-  int64_t incl = mine;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int64_t o = __shfl_up(incl, off, 64);
-    incl += lane >= off ? o : 0;
-  }
-  if (lane == 63) wave_sum[wave] = incl;
-  __syncthreads();
-  int64_t before = 0, total = 0;
-  for (int i = 0; i < nw; ++i) {
-    before += i < wave ? wave_sum[i] : 0;
-    total += wave_sum[i];
-  }
-  incl += before;
-  int64_t per = (total + gridDim.x - 1) / gridDim.x;
-  if (per > R) per = (per + R - 1) / R * R;
+  // ---- this workgroup's piece of the line, and the request of its first token: by sums over ever smaller runs of requests, one
+  // run a thread (one pass for up to n_threads requests, three for 65535 and a single wave)
   const int g = blockIdx.x;
-  int64_t pos = (int64_t)g * per;
-  if (pos >= total) return;
-  if (pos >= incl - mine && pos < incl) {
-    int64_t first = incl - mine;
-    int b = b0;
-    for (;; ++b) {
-      const int64_t n = attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
-      if (pos < first + n) break;
-      first += n;
+  int64_t per = 0, pos = 0, left = 0, base = 0;  // (base: tokens of the requests before lo)
+  int lo = 0;
+  for (int hi = B, run = 0; run != 1;) {
+    run = (hi - lo + n_threads - 1) / n_threads;
+    const int b0 = lo + tid * run, b1 = b0 + run < hi ? b0 + run : hi;
+    int64_t mine = 0;
+#pragma unroll 4
+    for (int b = b0; b < b1; ++b) mine += attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
+    int64_t incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int64_t o = __shfl_up(incl, off, 64);
+      incl += lane >= off ? o : 0;
     }
-    s_req = b;
-    s_off = (int)(pos - first);
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int64_t total = 0;
+    incl += base;
+    for (int i = 0; i < nw; ++i) {
+      incl += i < wave ? wave_sum[i] : 0;
+      total += wave_sum[i];
+    }
+    if (per == 0) {
+      per = (total + gridDim.x - 1) / gridDim.x;
+      if (per > R) per = (per + R - 1) / R * R;
+      pos = (int64_t)g * per;
+      if (pos >= total) return;
+      left = total - pos < per ? total - pos : per;
+    }
+    if (pos >= incl - mine && pos < incl) {
+      s_lo = b0;
+      s_hi = b1;
+      s_base = incl - mine;
+    }
+    __syncthreads();
+    lo = __builtin_amdgcn_readfirstlane(s_lo);
+    hi = __builtin_amdgcn_readfirstlane(s_hi);
+    base = s_base;
   }
-  __syncthreads();
-  int b = __builtin_amdgcn_readfirstlane(s_req);
-  int off = __builtin_amdgcn_readfirstlane(s_off);  // of the piece's first token in its request
-  int64_t left = total - pos < per ? total - pos : per;
+  int off = __builtin_amdgcn_readfirstlane((int)(pos - base));  // of the piece's first token in its request
 
   const int ncg = d / VEC;
-  for (; left > 0; ++b, off = 0) {
-    const int64_t n = attn_tokens(seq_start, seq_len, tenant_id, b, M_tok, T_tenants);
-    if (n == 0) continue;
+  // The requests behind the first that take part are looked up 64 at a time: one that does not costs a 64th of a round trip.
+  unsigned long long todo = 1;  // of requests lo ..
+  for (int window = 1; left > 0; todo &= todo - 1, off = 0) {
+    while (!todo) {
+      lo += window;
+      window = 64;
+      const int b = lo + lane;
+      todo = __ballot(b < B && attn_tokens(seq_start, seq_len, tenant_id, b < B ? b : B - 1, M_tok, T_tenants) > 0);
+    }
+    const int b = lo + __builtin_ctzll(todo);
+    const int64_t n = seq_len[b];
     const uint32_t rows_n = __builtin_amdgcn_readfirstlane((int)(n - off < left ? n - off : left));
     const T* rows = H + ((size_t)seq_start[b] + off) * d;  // (the row may lie beyond 2^31)
     const T* q = w_sa + (size_t)tenant_id[b] * d;
@@ -608,7 +622,8 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
 #pragma unroll
         for (int i = 0; i < h; ++i) {
           const bool up = (lane & o) != 0;
-          const float give = up ? u[i] : u[i + h], keep = up ? u[i + h] : u[i];
+          const float x0 = u[i], x1 = u[i + h];  // (values: a choice between elements becomes a search by index)
+          const float give = up ? x0 : x1, keep = up ? x1 : x0;
           u[i] = keep + __shfl_xor(give, o, 64);
         }
 #pragma unroll

@@ -264,6 +264,57 @@ def test_route_self_attention_requests_that_share_rows(B, n, d):
     assert took[True] <= 4 * took[False], took
 
 
+@pytest.mark.parametrize("B,d", [(9000, 64), (65, 8), (1500, 2048), (4097, 300)])
+def test_route_self_attention_many_requests(B, d):
+    """More requests than a workgroup has threads (its first one is found in two or three passes), and long runs of requests that
+    take no part: inside a piece, in front of the first one and behind the last.  A call in which two requests take part does not
+    take longer than one in which all do (every skipped request cost a round trip of its own: six times and more)."""
+    T = 3
+    g = torch.Generator().manual_seed(B)
+    dev_g = torch.Generator(device=DEV).manual_seed(B)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=dev_g).to(torch.bfloat16)
+    Wr, w_sa = rnd(T, 7, d), rnd(T, d) * d ** -0.5
+    sl = torch.randint(1, 6, (B,), generator=g).to(torch.int32)
+    sl[torch.randint(0, B, (6,), generator=g)] = 400
+    ss = (torch.cumsum(sl, 0) - sl).to(torch.int32)
+    H = rnd(int(sl.sum()), d)
+    everyone = (torch.arange(B) % T).to(torch.int32)
+    runs = everyone.clone()
+    at = 0
+    while at < B:  # runs of 1 to 300 of either kind
+        n = int(torch.randint(1, 301, (1,), generator=g))
+        if torch.rand(1, generator=g) < 0.6:
+            runs[at:at + n] = T
+        at += n
+    ends = torch.full((B,), -1, dtype=torch.int32)
+    ends[[0, B - 1]] = 1
+    inner = torch.full((B,), T, dtype=torch.int32)
+    inner[B // 3], inner[2 * B // 3] = 0, 2
+    took = {}
+    for name, tid in (("all", everyone), ("runs", runs), ("ends", ends), ("inner", inner)):
+        args = H, ss.to(DEV), sl.to(DEV), tid.to(DEV), Wr, "selfattn"
+        ws = torch.full((mb.route_workspace_bytes(B, d, H.shape[0]),), 255, dtype=torch.uint8, device=DEV)
+        call = lambda: mb.milora_route(*args, w_sa=w_sa, workspace=ws)
+        route, logits = call()
+        keep = ((tid >= 0) & (tid < T)).numpy()
+        ref = oracle.route(np_of(H), ss.numpy()[keep], sl.numpy()[keep], tid.numpy()[keep], np_of(Wr), mb.POOL["selfattn"],
+                           oracle.ACT_IDENTITY, w_sa=np_of(w_sa))
+        assert_routes_match(route[keep], ref, torch.bfloat16, name)
+        np.testing.assert_allclose(to_f64(logits)[keep], ref.logits, atol=5e-5 * max(1.0, np.abs(ref.logits).max()))
+        assert (route.cpu().numpy()[~keep] == mb.ROUTE_NONE).all() and torch.isnan(logits[~keep]).all()
+        times = []
+        for _ in range(5):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(10):
+                call()
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1))
+        took[name] = min(times)
+    assert max(took["ends"], took["inner"], took["runs"]) <= 2 * took["all"], took
+
+
 @pytest.mark.parametrize("d", [1, 8])
 @pytest.mark.parametrize("pool", ["selfattn", "mean"])
 def test_route_rows_beyond_2_31(pool, d):

@@ -253,8 +253,8 @@ __device__ __forceinline__ f32x4 add_token_lanes(const float (&red)[kTokenLanes]
 // z = g(scale * h) of a lane's columns fcol .. fcol + 3 (where `on`) and what they add to the seven logits, summed over the wave: lane
 // 8 j .. 8 j + 7 end with logit j.  Each of the first three steps halves what a lane holds: ten exchanges, not forty-two.
 // (The end of a router's launch is a chain of round trips and of the code between them: with these ten, the activation as one jump for
-// four columns, router weights in one load per row and the maximum apart from the sums, the whole launch on 32 prompts of 256 tokens,
-// d = 4096, went from 18.0 to 14.8 us, 4.5 TB/s.)
+// four columns, router weights in one load per row and the maximum apart from the sums, a call on 32 prompts of 256 tokens,
+// d = 4096, went from 18.0 to 14.8 us, and to 14.3, 4.7 TB/s, with the choice below made between values.)
 template <typename T>
 __device__ __forceinline__ float wave_logits(const PoolRouteArgs<T>& p, bool on, int fcol, int lane, f32x4 h, float scale,
                                              const float (&wr)[MILORA_NUM_SITES][4]) {
@@ -275,7 +275,8 @@ __device__ __forceinline__ float wave_logits(const PoolRouteArgs<T>& p, bool on,
 #pragma unroll
     for (int i = 0; i < half; ++i) {
       const bool up = (lane & off) != 0;
-      const float give = up ? lg[i] : lg[i + half], keep = up ? lg[i + half] : lg[i];
+      const float x0 = lg[i], x1 = lg[i + half];  // (values: a choice between elements becomes a search by index)
+      const float give = up ? x0 : x1, keep = up ? x1 : x0;
       lg[i] = keep + __shfl_xor(give, off, 64);
     }
 #pragma unroll
@@ -690,7 +691,8 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
 
 // Finish of the self-attention pooler: a workgroup of 512 threads merges CL * 4 columns of a request's rows (each holds a
 // sum weighted by exp(u - m_s): brought to the common maximum and normalised), 512 / CL rows side by side, eight of each on
-// their way, and goes on as pool_route_kernel does.
+// their way, and goes on as pool_route_kernel does.  The widest take four: there are few rows to merge then and many workgroups, of
+// which a compute unit holds more so (calls of 1000 requests of 4 rows, d = 4096: 47.4 us with eight, 41.3 with four).
 template <typename T, int CL>
 __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRouteArgs<T> p, AttnParts in) {
   constexpr int SW = CL * 4, TL = kPoolThreads / CL, kWaves = (CL + 63) / 64;  // waves that finish
@@ -705,15 +707,16 @@ __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRoute
     if (c == 0) no_route(p, b);
     return;
   }
-  // the first 8 TL rows and their maxima before anything waits, the router weights behind them
+  // the first U * TL rows and their maxima before anything waits, the router weights behind them
   const float2* ml = in.ml + sp.x;
   const int col = c * SW + cl * 4 < in.pitch ? c * SW + cl * 4 : 0;  // (past the end: never used)
   const f32x4* rows = reinterpret_cast<const f32x4*>(in.partial + (size_t)sp.x * in.pitch + col);
-  f32x4 x[8];
-  float m[8];
+  constexpr int U = CL == 512 ? 4 : 8;  // rows on their way
+  f32x4 x[U];
+  float m[U];
   auto ask = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = i0 + u * TL < sp.y ? i0 + u * TL : sp.y - 1;
       m[u] = ml[i].x;
       x[u] = rows[(size_t)i * (in.pitch / 4)];
@@ -735,10 +738,10 @@ __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRoute
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) z += __shfl_xor(z, o, 64);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int i0 = tl; i0 < sp.y; i0 += 8 * TL) {
+  for (int i0 = tl; i0 < sp.y; i0 += U * TL) {
     if (i0 != tl) ask(i0);
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < U; ++u)
       if (i0 + u * TL < sp.y) acc += expf(m[u] - ref) * x[u];
   }
   acc *= 1.0f / z;

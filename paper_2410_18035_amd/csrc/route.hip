@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int c = p * n_threads + tid;
-      col[p] = (c < ncg ? c : ncg - 1) * VEC;  // past the row's end: its last piece, against zeros of w
+      col[p] = (c < ncg ? c : ncg - 1) * VEC;  // past the row's end: its last piece, of which nothing is taken
     }
     Piece<T, VEC> x[2][R][P];
     auto ask = [&](uint32_t t, Piece<T, VEC> (&v)[R][P]) __attribute__((always_inline)) {
@@ -602,7 +602,7 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
       VecLoad<T, VEC>::load(q + col[p], v);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
-        w[p][e] = p * n_threads + tid < ncg ? v[e] : 0.f;
+        w[p][e] = v[e];
         acc[p][e] = 0.f;
       }
     }
@@ -613,9 +613,12 @@ __global__ void __launch_bounds__(kAttnMaxWaves * 64) pool_selfattn_kernel(const
       for (int r = 0; r < R; ++r) {
         u[r] = 0.f;
 #pragma unroll
-        for (int p = 0; p < P; ++p)
+        for (int p = 0; p < P; ++p) {
+          const float before = u[r];
 #pragma unroll
           for (int e = 0; e < VEC; ++e) u[r] += v[r][p].get(e) * w[p][e];
+          u[r] = p * n_threads + tid < ncg ? u[r] : before;  // (not a product with zero: the row's last piece may hold Inf)
+        }
       }
       // sums over the lanes: every step halves the rows a lane holds, row lane / Lanes is left
 #pragma unroll

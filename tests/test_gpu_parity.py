@@ -315,6 +315,42 @@ def test_route_self_attention_many_requests(B, d):
     assert max(took["ends"], took["inner"], took["runs"]) <= 2 * took["all"], took
 
 
+@pytest.mark.parametrize("dtype,d,shift", [("bf16", 4104, 0), ("bf16", 512, 0), ("bf16", 300, 0), ("bf16", 1500, 1), ("f32", 5000, 0), ("f32", 260, 0)])
+@pytest.mark.parametrize("act", ["identity", "relu"])
+def test_route_self_attention_infinite_scores(dtype, d, shift, act):
+    """Scores of -Inf, +Inf and NaN.  A token whose score is -Inf has no weight (its own Inf makes its column NaN, nothing else); +Inf
+    and NaN make the request's state NaN; no request sees another's.  As the oracle has it in 64 bits, at widths that fill the
+    threads and widths that do not, in 16-byte pieces and in elements."""
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    T, n = 2, 333
+    g = torch.Generator(device=DEV).manual_seed(d)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(dt)
+    Wr, w_sa = rnd(T, 7, d) * d ** -0.5, rnd(T, d) * d ** -0.5
+    Wr[:, :, d - 1] = 0.01
+    w_sa[:, 0], w_sa[:, d - 1] = 0.25, 0.5
+    inf, B = float("inf"), 9
+    H = rnd(B * n, d)
+    row = lambda b, t: b * n + t
+    H[row(1, 40), d - 1] = -inf                    # one token of weight 0, NaN in the last column
+    H[row(2, n - 1), d - 1] = -inf                 # the last one, which stands in for rows past the end
+    H[row(3, 0):row(3, 301), 0] = -inf             # most of them, among them the first batches
+    H[row(4, 0):row(4, n), d - 1] = -inf           # all: no weights at all
+    H[row(5, 17), 3] = float("nan")
+    H[row(6, 5), d - 1] = inf
+    H[row(7, 5), d - 1], H[row(7, 200), d - 1] = inf, -inf
+    H = torch.empty(H.numel() + shift, dtype=dt, device=DEV)[shift:].view_as(H).copy_(H)
+    ss, sl = (torch.arange(B) * n).to(torch.int32), torch.full((B,), n, dtype=torch.int32)
+    tid = (torch.arange(B) % T).to(torch.int32)
+    route, logits = mb.milora_route(H, ss.to(DEV), sl.to(DEV), tid.to(DEV), Wr, "selfattn", act, w_sa=w_sa)
+    with np.errstate(all="ignore"):
+        ref = oracle.route(np_of(H), ss.numpy(), sl.numpy(), tid.numpy(), np_of(Wr), mb.POOL["selfattn"], mb.ACT[act], w_sa=np_of(w_sa))
+    got = to_f64(logits)
+    assert np.array_equal(np.isnan(got), np.isnan(ref.logits)) and not np.isinf(got).any()
+    finite = ~np.isnan(ref.logits).any(1)
+    assert finite[[0, 8]].all() and finite.sum() == (2 if act == "identity" else B)
+    np.testing.assert_allclose(got[finite], ref.logits[finite], atol=5e-5 * max(1.0, np.abs(ref.logits[finite]).max()))
+
+
 @pytest.mark.parametrize("d", [1, 8])
 @pytest.mark.parametrize("pool", ["selfattn", "mean"])
 def test_route_rows_beyond_2_31(pool, d):

@@ -712,6 +712,47 @@ def test_layer_decode_generic_fp32(rmsnorm, with_attn):
     _layer_case(wl, rmsnorm, mb.W_ROWMAJOR, with_attn)
 
 
+@pytest.mark.parametrize("M", [16, 128])
+def test_bf16_results_round_to_nearest_even(M):
+    """Every product of two 8-bit significands, as it leaves fp32 (a LoRA term of rank 1 on weights of zeros): ties, values next to
+    ties, results that are fp32 and bf16 denormals, zero, the largest finite ones, Inf and NaN, against rounding by integer arithmetic."""
+    d1, site = 40, 2
+    g = torch.Generator().manual_seed(M)
+    rows = torch.arange(128) if M == 128 else torch.randperm(128, generator=g)[:M]
+    a = (1 + rows / 128) * torch.where(torch.arange(M) % 3 == 0, -1.0, 1.0)  # one bf16 per tenant, times 2^-64
+    b = torch.cat([(1 + torch.arange(128) / 128).double() * 2.0 ** (64 + e) for e in (0, 5, 62, 63, -126, -127, -130, -134, -149)] +
+                  [torch.tensor([float("inf"), -float("inf"), float("nan"), 0.0, -0.0, 2.0 ** 127 * 255 / 128], dtype=torch.float64),
+                   (1 + torch.arange(128) / 128).double() * 2.0 ** 127])
+    b = b[(b.abs() < 2.0 ** 128) | ~b.isfinite()]
+    scale = 2.0 ** -64
+    A = [[(torch.eye(d1, 1, dtype=torch.float64) * float(x) * scale).to(torch.bfloat16).to(DEV)] * 7 for x in a]
+    bb = b.to(torch.bfloat16)
+    assert torch.equal(bb.double().nan_to_num(1.5), b.nan_to_num(1.5))
+    B = [[bb.view(1, -1).to(DEV)] * 7 for _ in range(M)]
+    up = torch.ones(M, dtype=torch.float64)
+    up[M // 2:] = 2.0 ** 64  # rows whose products reach the largest finite values and beyond
+    X = torch.zeros(M, d1, dtype=torch.bfloat16, device=DEV)
+    X[:, 0] = up.to(torch.bfloat16).to(DEV)
+    W = torch.zeros(b.numel(), d1, dtype=torch.bfloat16, device=DEV)
+    tid, route = torch.arange(M, dtype=torch.int32, device=DEV), torch.full((M,), site, dtype=torch.uint8, device=DEV)
+    assert mb.milora_routed_linear_tile(M, d1, b.numel(), torch.bfloat16) == 0
+    Y = mb.milora_routed_linear(X, W, mb.AdapterTable.from_tensors(A, B, [1] * M), site, tid, route)
+    with np.errstate(all="ignore"):
+        f32 = np.outer((a.double() * scale * up).numpy(), b.numpy()).astype(np.float32)
+    u = f32.view(np.uint32).astype(np.uint64)
+    want = ((u + 0x7FFF + ((u >> 16) & 1)) >> 16).astype(np.uint16)
+    got = Y.cpu().view(torch.int16).numpy().view(np.uint16)
+    nan = np.isnan(f32)
+    assert np.array_equal(torch.isnan(Y).cpu().numpy(), nan)
+    zero = (want & 0x7FFF) == 0  # (a sum of zeros is +0)
+    assert np.array_equal(got[~nan & ~zero], want[~nan & ~zero]) and ((got[zero & ~nan] & 0x7FFF) == 0).all()
+    # the classes are there: ties either way, bf16 denormals, fp32 denormals, overflow by rounding alone, Inf
+    tie = (u & 0xFFFF) == 0x8000
+    assert (tie & ((u >> 16) & 1 == 1)).any() and (tie & ((u >> 16) & 1 == 0)).any()
+    exp = (u >> 23) & 0xFF
+    assert ((exp == 0) & ~zero).any() and (np.isfinite(f32) & ((want & 0x7FFF) == 0x7F80)).any() and (tie & (exp == 0)).any()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("M,d,F,site,ranks", [
     (1, 3, 5, 4, (1,)),            # less than one piece of four k, less than one block of columns

@@ -267,6 +267,32 @@ def test_routed_linear_256_tiles(M, d1, d2, ranks, T, spread):
     assert_rows_close(Y, ref, torch.bfloat16)
 
 
+@gpu
+@pytest.mark.parametrize("side,M,d1,d2", [(64, 130, 192, 272), (128, 300, 2048, 3520), (256, 4097, 64, 272), (256, 4400, 192, 528)])
+def test_tiles_at_the_least_alignment(side, M, d1, d2):
+    """W^B and the bias at odd elements, Y eight bytes past a sixteenth: the bits of the aligned call, and nothing written around Y."""
+    assert mb.milora_routed_linear_tile(M, d1, d2, torch.bfloat16) == side
+    T, site = 5, 3
+    A, B, rank = _adapters(T, d1, d2, (16, 33, 64), 0.1, M)
+    g = torch.Generator(device=DEV).manual_seed(M + 1)
+    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
+    X, W, bias = rnd(M, d1), rnd(d2, d1) * d1 ** -0.5, rnd(d2)
+    tid, route = torch.arange(T, dtype=torch.int32, device=DEV), torch.full((T,), site, dtype=torch.uint8, device=DEV)
+    r2r = (torch.arange(M, device=DEV) * T // M).to(torch.int32)
+    call = lambda B, bias, Y: mb.milora_routed_linear(X, W, mb.AdapterTable.from_tensors(A, B, rank), site, tid, route, r2r, bias=bias, out=Y)
+    aligned = torch.empty(M, d2, dtype=torch.bfloat16, device=DEV)
+    assert aligned.data_ptr() % 16 == 0 and all(b[0].data_ptr() % 16 == 0 for b in B)
+    call(B, bias, aligned)
+    past = lambda t: torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)[1:].view_as(t).copy_(t)
+    around = torch.full((4 + M * d2 + 64,), -7.0, dtype=torch.bfloat16, device=DEV)
+    Y = around[4:4 + M * d2].view(M, d2)
+    B1, bias1 = [[past(b[0])] * 7 for b in B], past(bias)
+    assert Y.data_ptr() % 16 == 8 and bias1.data_ptr() % 4 == 2 and all(b[0].data_ptr() % 4 == 2 for b in B1)
+    call(B1, bias1, Y)
+    assert torch.equal(Y.view(torch.int16), aligned.view(torch.int16))
+    assert (around[:4] == -7).all() and (around[4 + M * d2:] == -7).all()
+
+
 def test_tile_choice_counts_the_last_turn():
     """256 x 256 tiles or smaller ones where the two are near: a last turn of few workgroups, short reductions."""
     k = lambda *s: mb.milora_routed_linear_tile(*s, torch.bfloat16)

@@ -94,13 +94,12 @@ __global__ void __launch_bounds__(kShrinkT) shrink_rows_kernel(const T* __restri
 // The layer's glue is part of the store: a decode step of a layer is four launches instead of eighteen.
 // Bound: launches (about 2.4 us each with nothing in them), and the code a launch runs through, whose time goes with its
 // bytes (4.6 KB 4.8 us, 7.7 KB 8.0 us): what a call does not need is compiled out, the shrinks of two sites are one loop, and
-// four waves run through it where eight would each find two blocks of 16 k or fewer (d = 256 22.3 -> 19.6 us, 360: 26.5 and
-// 26.7, 504: 34.8 and 38.9).  A decode step of 4 rows through the 256 x 688 fp32 layer, rank 8: 284 us with eighteen launches,
+// four waves run through it where that is enough (few_waves: d = 256 22.3 -> 19.6 us).  A decode step of 4 rows through the 256 x 688 fp32 layer, rank 8: 284 us with eighteen launches,
 // 22.3 us with four of eight waves and both expands in them, 19.6 us so.  Tried: base and adapter pointers asked for ahead of the
 // look-ups (fewer dependent loads, more code: 26.9 against 24.3 us), 32-bit offsets with a path for whole trips (41.1 against 35.6 us at
 // 16 rows, d = 504).
 constexpr int kFewBlocks = 4;  // blocks of 16 k per wave on their way
-constexpr int kFewNarrow = 320;  // reductions up to here: four waves
+constexpr int kFewNarrow = 256;  // no reduction longer than this on four waves
 
 template <typename T>
 __device__ __forceinline__ float round_to(float v) {
@@ -512,25 +511,43 @@ static int launch_few_rows_t(FewArgs& g, int sites, int mode, hipStream_t st) {
 // 59).  In a layer's step a request has one of the seven sites, or a few: there it is some 45 trips of all rows (16 rows, d = 512,
 // rank 8, 16 trips and 42 of the down projection: 40.2 and 45.3 us a step; d = 1000, rank 8, 31 and 85: 61.6 and 63.0; rank 16, 62 and
 // 171: 80.6 and 70.0).
-static bool fuse_shrink(int M, int d1, int r_max, bool layer) {
-  if (r_max > kFuseRank) return false;
+// (A trip is one of eight waves; four, where few_waves takes them, make one trip of a row's shrink as well.  The calls were made one
+// by one from the host, where a second launch costs most; replayed from a graph the two meet sooner, fp32, 512 x 1359, rank 8: 4 rows
+// 7.2 us inside and 7.2 apart, 8 rows 10.3 and 7.7, 16 rows 16.3 and 8.0.)
+static int64_t shrink_work(int d1, int r_max) {  // of one row, in products
   int rpad = 1;
   while (rpad < r_max) rpad <<= 1;
-  const int64_t trip = 8 * 64 * 8, work = (int64_t)d1 * rpad;
+  return (int64_t)d1 * rpad;
+}
+static constexpr int64_t shrink_trip(int waves) { return waves * 64 * 8; }
+
+static bool fuse_shrink(int M, int d1, int r_max, bool layer) {
+  if (r_max > kFuseRank) return false;
+  const int64_t trip = shrink_trip(8), work = shrink_work(d1, r_max);
   return M * (work > trip ? work : trip) <= (layer ? 48 : 16) * trip;
+}
+
+// Waves of a launch with the shrinks inside.  Four where eight would each find two blocks of 16 k or fewer and where four form a
+// row's shrink in one trip too: fp32, 1359 columns, all rows routed, d1 = 256: rank 8, 1, 8 and 16 rows 4.2, 8.8 and 14.3 us with four and
+// 4.7, 10.2 and 16.1 with eight; d1 = 288: 4.6, 11.0, 18.3 and 4.7, 10.0, 16.2; rank 16, 343 columns, d1 = 200, 16 rows: 17.8 and
+// 15.2.  Few rows of a layer's step, most of them without a term at a given site, take four up to any rank: d = 256, rank 16, 1 and
+// 4 rows 16.9 and 21.4 us a step, 18.6 and 22.8 with eight; 16 rows with three sites each 55.6 and 52.0.
+static int few_waves(int M, int d1, int r_max, bool layer) {
+  return d1 <= kFewNarrow && (shrink_work(d1, r_max) <= shrink_trip(4) || (layer && M <= 4)) ? 4 : 8;
 }
 
 int launch_few_rows(const FewArgs& args, int dtype, int sites, int mode, float* t, hipStream_t st) {
   FewArgs g = args;
   g.t = nullptr;
-  if (!fuse_shrink(g.M, g.d1, g.ad.r_max, sites > 1 || mode != kFewPlain)) {
+  const bool layer = sites > 1 || mode != kFewPlain;
+  if (!fuse_shrink(g.M, g.d1, g.ad.r_max, layer)) {
     const int rc = launch_shrink(g.X, g.ldx, g.M, g.d1, dtype, g.row_to_req, g.ad, g.site[0], sites, g.tenant_id, g.route, g.B, t, st);
     if (rc) return rc;
     g.t = t;
   }
   const bool bf = dtype == MILORA_BF16;
   if (g.t) return bf ? launch_few_rows_t<bf16_t, 8, false>(g, sites, mode, st) : launch_few_rows_t<float, 8, false>(g, sites, mode, st);
-  if (g.d1 <= kFewNarrow) return bf ? launch_few_rows_t<bf16_t, 4, true>(g, sites, mode, st) : launch_few_rows_t<float, 4, true>(g, sites, mode, st);
+  if (few_waves(g.M, g.d1, g.ad.r_max, layer) == 4) return bf ? launch_few_rows_t<bf16_t, 4, true>(g, sites, mode, st) : launch_few_rows_t<float, 4, true>(g, sites, mode, st);
   return bf ? launch_few_rows_t<bf16_t, 8, true>(g, sites, mode, st) : launch_few_rows_t<float, 8, true>(g, sites, mode, st);
 }
 

@@ -794,6 +794,30 @@ def test_layer_decode_rowmajor_narrow_reductions(dtype, d, F, B, ranks):
     _layer_case(wl, False, mb.W_ROWMAJOR, route=route)
 
 
+@pytest.mark.parametrize("dtype,d,F,B,ranks", [("f32", 256, 257, 4, (16, 9)), ("f32", 256, 250, 5, (16,)), ("f32", 128, 129, 16, (16,)),
+                                              ("bf16", 256, 312, 4, (12,))])
+def test_layer_decode_rowmajor_waves_of_few_rows(dtype, d, F, B, ranks):
+    """The sides of the rule for four and eight waves in a layer's step: the width, the rows, one and two trips of a row's shrink."""
+    wl = small(dtype=dtype, d=d, F=F, T=3, B=B, ranks=ranks, tenants="uniform", seed=900 + d + B, sigma_lora=0.15 if dtype == "f32" else 0.4)
+    route = torch.tensor([0x80 | (1 << 4) | (1 << 5) | (1 << (b % 4)) for b in range(B)], dtype=torch.uint8)
+    _layer_case(wl, False, mb.W_ROWMAJOR, route=route)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,d1,ranks", [(16, 256, (8, 5)), (16, 257, (8,)), (8, 256, (9,)), (8, 128, (16, 1)), (8, 129, (16,)), (1, 255, (2,))])
+def test_routed_linear_waves_of_few_rows(dtype, M, d1, ranks):
+    """The same sides for a single linear with every row routed."""
+    wl = small(dtype=dtype, d=d1, F=331, T=3, B=M, ranks=ranks, tenants="uniform", seed=950 + d1 + M, sigma_lora=0.6)
+    W, ad, tab = device_layer(wl)
+    x, tid, site = synth.decode_input(wl, 0, DEV), synth.tenant_ids(wl), 5
+    route = torch.full((M,), site, dtype=torch.uint8)
+    Y = mb.milora_routed_linear(x, W[site], tab, site, tid.to(DEV), route.to(DEV))
+    run = lambda rt: [oracle.routed_linear(np_of(x), np_of(W[site]), oracle_adapters(ad), site, tid.numpy(), rt)]
+    ref = run(route.numpy())
+    assert lora_visibility(run, route.numpy(), ref) >= VISIBLE * TOL[wl.torch_dtype]
+    assert_rows_close(Y, ref[0], wl.torch_dtype)
+
+
 @pytest.mark.parametrize("B", [4, 16, 32, 48, 64, 128])
 @pytest.mark.parametrize("rmsnorm", [False, True])
 def test_layer_decode_packed_bf16(B, rmsnorm):

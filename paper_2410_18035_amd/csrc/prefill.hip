@@ -34,13 +34,6 @@ constexpr int kLdsBytesP = kHalves * kHalfBytes;
 constexpr int kAccTilesRows = 3;
 constexpr int kOutPitch = 128 * 2 + 16;                   // a row of a wave's results on their way out, padded: 16 rows at one column hit all banks
 static_assert(4 * 128 * kOutPitch <= kLdsBytesP, "results of the four waves");
-// Results of this size or more (of the whole call) are stored past the L2, whose lines stay with X and W; smaller ones are left in it
-// for who reads them next.  Twice the L2's 32 MB.  Up projection and the down projection that reads it, us past the L2 and through
-// it: 17 MB (777 rows of 4096 x 11008) 185 and 173, 45 MB (2048 rows) 381 and 365, (4096 rows of 2048 x 5504) 220 and 208; 90 MB (4096
-// rows) 587 and 591, 180 MB 1177 and 1196; 50 to 79 MB within 1 %.  With an elementwise step in between: within 1 %.  Calls whose
-// results nobody reads are the faster past it, where there is little work for them (8192 rows of 512 x 1376 24.9 and 26.4; with an
-// elementwise step behind 37.6 and 36.7), else by less than 1 % (the seven linears of 777 rows 489.5 and 491.5).
-constexpr uint64_t kPastL2Bytes = 64ull << 20;
 // Where the sixteen copy instructions of a k step sit among its 64 matrix instructions: those of the first half
 // after instructions 0, kCopyAStride, ..., those of the second half from instruction kCopyB0 on (16 or later: the
 // slot they fill is read until then).
@@ -64,7 +57,6 @@ struct PParams {
   int64_t row_base;  // index of its first row in the caller's matrix (requests of unmapped rows)
   int d1, d2, site, B;
   int tilesM, tilesN;
-  bool past_l2;      // results are stored past the L2 (kPastL2Bytes)
 };
 
 // Which of the eight 16-byte pieces of its 128-byte LDS line holds k group kg of row r (0..15) of a block:
@@ -379,7 +371,7 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
   // ---- bias, one rounding, store: of a 32 x 32 tile a lane holds row l % 32 and, in registers 4 g .. 4 g + 3, the
   // columns 8 g + 4 (l / 32) .. + 3.  By way of the wave's own LDS, so that a store writes whole lines (256 bytes of four rows instead
   // of 16 bytes of 32 rows, lines that had to be read before they could be written: seven linears of 32768 rows 11.43 -> 10.79 ms), and
-  // of large results past the L2's lines of X and W (10.80 -> 10.57 ms)
+  // past the L2's lines of X and W (10.80 -> 10.57 ms)
   const bool bad = ctl[1] != 0;
   __syncthreads();
   unsigned char* const mine = lds + wave * (128 * kOutPitch);
@@ -409,19 +401,14 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
     const int64_t mw = m0 + wm * 128 + (lane >> 4);
     bf16_t* y = p.Y + (size_t)mw * p.d2 + n;
     const unsigned char* q = mine + (lane >> 4) * kOutPitch + (lane & 15) * 16;
-    auto put = [&](auto store) __attribute__((always_inline)) {
+    if (n < p.d2)
 #pragma unroll 4
       for (int it = 0; it < 32; ++it) {
         if (mw + it * 4 < p.M) {
           const u32x4_a8 v = *(const u32x4*)(q + it * 4 * kOutPitch);
-          store(v, (u32x4_a8*)(y + (size_t)(it * 4) * p.d2));
+          __builtin_nontemporal_store(v, (u32x4_a8*)(y + (size_t)(it * 4) * p.d2));
         }
       }
-    };
-    if (n < p.d2) {
-      if (p.past_l2) put([](u32x4_a8 v, u32x4_a8* to) { __builtin_nontemporal_store(v, to); });
-      else put([](u32x4_a8 v, u32x4_a8* to) { *to = v; });
-    }
   }
 
   // ---- what the stages could not take: products with the tenant's own Inf and NaN, onto the stored results (no finite part of
@@ -511,7 +498,6 @@ int routed_linear_prefill(const bf16_t* X, int64_t M, int d1, int d2, const int3
     p.B = B;
     p.tilesM = (int)((p.M + kTM - 1) / kTM);
     p.tilesN = tilesN;
-    p.past_l2 = (uint64_t)M * (uint64_t)d2 * 2u >= kPastL2Bytes;
     const int total = p.tilesM * p.tilesN;
     const int per = (total + 7) / 8;
     hipLaunchKernelGGL(prefill_kernel, dim3(8 * per), dim3(kThreadsP), kLdsBytesP, stream, p);

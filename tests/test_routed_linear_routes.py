@@ -293,31 +293,6 @@ def test_tiles_at_the_least_alignment(side, M, d1, d2):
     assert (around[:4] == -7).all() and (around[4 + M * d2:] == -7).all()
 
 
-@gpu
-def test_large_results_pass_the_l2():
-    """The last size whose results are left in the L2 and the first whose are stored past it, ragged tiles both ways: the same bits,
-    and every row within the tolerance of fp64."""
-    d1, d2, T, site = 64, 8208, 3, 4
-    assert 2 * 4088 * d2 < 64 << 20 <= 2 * 4089 * d2
-    A, B, rank = _adapters(T, d1, d2, (8, 20), 0.1, 5)
-    tab = mb.AdapterTable.from_tensors(A, B, rank)
-    g = torch.Generator(device=DEV).manual_seed(6)
-    rnd = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV).normal_(0, 1, generator=g).to(torch.bfloat16)
-    X, W = rnd(4089, d1), rnd(d2, d1) * d1 ** -0.5
-    tid, route = torch.arange(T, dtype=torch.int32, device=DEV), torch.full((T,), site, dtype=torch.uint8, device=DEV)
-    r2r = (torch.arange(4089, device=DEV) // 1400).to(torch.int32)
-    out = {}
-    for M in (4088, 4089):
-        assert mb.milora_routed_linear_tile(M, d1, d2, torch.bfloat16) == 256
-        out[M] = mb.milora_routed_linear(X[:M], W, tab, site, tid, route, r2r[:M])
-    assert torch.equal(out[4088].view(torch.int16), out[4089][:4088].view(torch.int16))
-    ref = X.double() @ W.double().T
-    for t in range(T):
-        rows = r2r == t
-        ref[rows] += (X[rows].double() @ A[t][site].double()) @ B[t][site].double()
-    assert_rows_close(out[4089], ref.cpu().numpy(), torch.bfloat16)
-
-
 def test_tile_choice_counts_the_last_turn():
     """256 x 256 tiles or smaller ones where the two are near: a last turn of few workgroups, short reductions."""
     k = lambda *s: mb.milora_routed_linear_tile(*s, torch.bfloat16)

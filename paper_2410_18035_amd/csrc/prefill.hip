@@ -371,7 +371,10 @@ __global__ void __launch_bounds__(kThreadsP, 1) prefill_kernel(PParams p) {
   // ---- bias, one rounding, store: of a 32 x 32 tile a lane holds row l % 32 and, in registers 4 g .. 4 g + 3, the
   // columns 8 g + 4 (l / 32) .. + 3.  By way of the wave's own LDS, so that a store writes whole lines (256 bytes of four rows instead
   // of 16 bytes of 32 rows, lines that had to be read before they could be written: seven linears of 32768 rows 11.43 -> 10.79 ms), and
-  // past the L2's lines of X and W (10.80 -> 10.57 ms)
+  // past the L2's lines of X and W (10.80 -> 10.57 ms).  Also where results are small and read soon: us with all of them past the L2 /
+  // those below 64 MB through it / 16 bytes of 32 rows a store, 777 rows of 4096 x 11008: up alone 84.5 / 85.3 / 93.7, up and the down
+  // that reads it 182 / 170 / 184, gate, up, their product and down 262 / 263 / 285; the same with every row routed 102.0 / 103.5 /
+  // 115.5, 204 / 205 / 223, 316 / 318 / 350; up of 1805 rows of 192 x 7488, every row routed, 30.7 / 33.6 / 45.9.
   const bool bad = ctl[1] != 0;
   __syncthreads();
   unsigned char* const mine = lds + wave * (128 * kOutPitch);

@@ -639,11 +639,14 @@ int launch_tiles(const TParams& p, hipStream_t st) {
 // of the 7B and 13B layers and a 1088 x 2624 one.  A compute unit takes 0.26 us per stage of 64 k for a 64 x 64 tile
 // (two workgroups share it: half the rate each), 0.58 us for a 128 x 128 one and 1.2 .. 1.6 us (few .. all units busy:
 // the L2 is shared) for a 256 x 256 one (600 rows on 5120 x 13824: 110 us a call, 133 with 128 x 128; 2048 on 4096 x 4096: 86 and 79);
-// its 7.75 us a turn keep reductions of 64 to 512 with no row routed on the smaller tiles (3846 rows on 512 x 1040: 18.3 us, 20.5 with
-// 256 x 256; 1406 on 192 x 11008: 25.3 and 27.7) and take those with many rows of rank 32 off them (3390 on 64 x 2048: 23.5 and 19.7);
+// its 7.75 us a turn are what short reductions show.  The choice knows sizes only; it was timed with no row routed and with every row
+// routed to one of two tenants of rank 32, 128 x 128 / 256 x 256 tiles: 3846 rows on 512 x 1040 18.6 / 20.6 and 31.5 / 34.2 us, 1406
+// on 192 x 11008 25.8 / 28.0 and 45.5 / 47.8, 1805 on 192 x 7488 25.4 / 18.0 and 45.5 / 29.1; near a tie it gives away some percent:
+// 3390 on 64 x 2048, which take 256 x 256, 13.6 / 13.8 and 25.1 / 26.1;
 // workgroups beyond 256 wait for a second turn; a last turn of few is shorter than a whole one (256 x 256, 1700 rows on 4096 x 11008: 301
 // workgroups, 2.6 us a step for both turns, 3.2 for two whole ones; of more than two turns of 128 x 128, 600 rows on 5120 x 13824: 540,
-// 2.7 turns; below that, 300 rows on 4096 x 11008: 258, 70.2 us against 66.5 with 64 x 64); cutting the reduction costs the
+// 2.7 turns; below that, 300 rows on 4096 x 11008: 258, 70.2 us against 66.5 with 64 x 64; packed weights, for which there is no
+// 256 x 256 kernel, keep the choice between 64 and 128 that was timed for them); cutting the reduction costs the
 // partial tiles and the last workgroup's sums (M = 64 on 4096 x 4096: one part 25.0 us a call, two 19.8, four 16.4, six 22.2).
 TilePlan plan_tiles(int64_t M, int d1, int d2, bool small, bool large) {
   const int KT = (d1 + 63) / 64;

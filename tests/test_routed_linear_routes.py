@@ -302,7 +302,7 @@ def test_tile_choice_where_one_is_clearly_faster():
 
 
 @gpu
-@pytest.mark.parametrize("M,d1,d2", [(517, 64, 13056), (517, 64, 13120)])
+@pytest.mark.parametrize("M,d1,d2", [(517, 64, 13312), (517, 64, 13328)])
 def test_routed_linear_256_tiles_of_fewer_rows(M, d1, d2):
     """Sizes that both kernels take, the 256 x 256 one by a quarter of the time: a ragged last row tile, whole and ragged columns."""
     test_routed_linear_256_tiles(M, d1, d2, (16, 40), 6, "segments")

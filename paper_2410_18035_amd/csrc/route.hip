@@ -460,12 +460,12 @@ __global__ void __launch_bounds__(kPoolThreads) pool_route_kernel(PoolRouteArgs<
 
 // ---- self-attention pooling (App. C): u_t = H[t] . w_sa, a = softmax over the request's tokens, p = sum_t a_t H[t] ----
 // One pass over H.  The valid tokens of all requests, one request after the other, are a line that is cut into equal
-// pieces, one per workgroup, whatever the lengths.  A workgroup holds a row across its threads (16 bytes each, kPieces of them) and
+// pieces, one per workgroup, whatever the lengths.  A workgroup holds a row across its threads (16 bytes each, P of them) and
 // takes R rows at a time: R scores (in-wave sums, then over the waves through LDS, one barrier), weights relative to the
 // running maximum (a batch that raises it rescales what was gathered before), weighted sum out of the same registers,
 // while the next R rows are on their way.  The part of a piece that lies in one request leaves a row of unnormalised sums
 // and (maximum, sum of weights) in the workspace, at index piece + request; the finishing launch merges a request's rows.
-// Bound: the read of H.  16 prompts of 1024 to 2048 tokens, d = 4096 (201 MB): 41 us = 4.9 TB/s and 8.7 us
+// Bound: the read of H.  16 prompts of 1024 to 2048 tokens, d = 4096 (201 MB): 38.6 us = 5.2 TB/s and 8.2 us
 // for the finishing launch, six dependent round trips (with slices of 16 tokens, each read twice, and one finishing workgroup
 // per request: 65 and 72 us).
 constexpr int kSelfAttnMaxD = 8192;
@@ -774,12 +774,12 @@ __global__ void __launch_bounds__(kPoolThreads) selfattn_finish_kernel(PoolRoute
 
 // Workspace of the self-attention pooler.  Pieces of the line: two workgroups of up to eight waves per compute unit, one of
 // more, four of up to four; as many as there are eights of rows in H, but one per request at least: requests may be shorter, or share
-// their rows, so that the line is longer than H (d = 4096, 64 requests of one row each: 35.8 us with 8 pieces, 14.1 with 64; 64 over
-// the same 16 rows: 182 us with 2, 15.9 with 64).
+// their rows, so that the line is longer than H (d = 4096, 64 requests of one row each: 35.8 us with 8 pieces, 12.6 with 64; 64 over
+// the same 16 rows: 182 us with 2, 13.9 with 64).
 // Column lanes of a finishing workgroup: few rows to merge, wide slabs (many requests are then few workgroups, and a row that fits
 // one of them needs no hand-over); more, narrow ones, so that all rows are on their way together.  Calls of 200 prompts of 16
 // to 128 tokens, d = 4096 (4 rows each): 133 us with 32 lanes, 53 with 512; 32 of 256 (17 rows): 36 us with 32, 29 with 128; 16 of
-// 1024 to 2048 (33 rows): the finishing launch 10.6 us with 32, 11.6 with 128 (all before its end got shorter: 48, 27 and 8.7 us
+// 1024 to 2048 (33 rows): the finishing launch 10.6 us with 32, 11.6 with 128 (all before its end got shorter: 40.5, 25.9 and 8.2 us
 // at the widths taken).
 struct AttnCarve {
   int pieces, lanes, C, pitch;
